@@ -4,8 +4,10 @@ For one level the header defines a traits struct ``Lv<L>`` with static
 device functions, all straight-line code with compile-time indices so that
 per-atom state stays in registers:
 
-  acc_moments<G>(m, f, x, y, z)        m[e] += f[mu_e] x^a y^b z^c   (entry group G)
-  pair_grad<G>(mb, f, fp, x, y, z, ...) gradient of sum_e mb[e] f_mu x^a y^b z^c w.r.t. d
+  acc_moments<G>(m, f, x, y, z)        m[e] += f[mu_e] x^a y^b z^c   (entry group G; binary32)
+  acc_part<P>(m, f, x, y, z)           the same for the entries of part P (binary64)
+  pair_grad<G>(mb, f, fp, x, y, z, ...) gradient of sum_e mb[e] f_mu x^a y^b z^c w.r.t. d (binary32)
+  pair_part<P>(mb, f, h, x, y, z, ...)  the same for part P by nested Horner schemes (binary64)
   fwd(M, C)                             connected contractions C_q from moments
   products(C, xi, Cb, B)                basis values, site energy, adjoints of C_q
   rev<G>(M, Cb, mb)                     mb[e] += sum_q Cb_q dC_q/dm_e   (entries of group G)
@@ -219,6 +221,203 @@ def _emit_pair_functions(w: _W, prog: Program, groups):
             w(f"u = fma(fp[{mu}], s{mu}, u);")
         w.pop()
         w("}")
+
+
+# Most moment entries one wave of the binary64 moment kernel accumulates: two registers each, with
+# the pair's own values within the 256 that two waves per SIMD leave a lane (no copies to and from
+# accumulation registers).
+MOMENT_PART_CAP = 84
+
+
+def moment_parts(prog: Program, cap=MOMENT_PART_CAP):
+    """The moment entries cut into parts of at most cap entries, each a list of (mu, a) slices (all
+    entries of one radial function and x exponent), in order.  Level 16: mu = 0 (84) and the rest
+    (46); level 20: 81, 84, 84, 46."""
+    size = defaultdict(int)
+    for mu, a, _, _ in prog.layout.items:
+        size[mu, a] += 1
+    parts, fill = [], 0
+    for key in sorted(size):
+        if not parts or fill + size[key] > cap:
+            parts.append([])
+            fill = 0
+        parts[-1].append(key)
+        fill += size[key]
+    return parts
+
+
+def part_entries(prog: Program, parts):
+    """Moment entries of each part, in the order (mu, a, b, c)."""
+    at = {it: e for e, it in enumerate(prog.layout.items)}
+    return [[at[it] for it in sorted(at) if it[:2] in part] for part in (set(p) for p in parts)]
+
+
+def _emit_moment_parts(w: _W, prog: Program, parts):
+    """acc_part<P>(m, f, x, y, z): m[k] += f_mu x^a y^b z^c for the entries PART_ENTRY[P][k].  For
+    each (mu, a, b) the run over c multiplies the weighted monomial f_mu x^a y^b z^c by z and adds
+    it; the last entry of a run takes its factor z in the addition.  Three running products are
+    live, one multiplication less per run than forming every monomial."""
+    ents = {}
+    for e, (mu, a, b, c) in enumerate(prog.layout.items):
+        ents.setdefault((mu, a), {}).setdefault(b, {})[c] = e
+    order = part_entries(prog, parts)
+    width = max(len(o) for o in order)
+    w(f"static constexpr int NPART = {len(parts)};")
+    w(f"static constexpr int PART_SIZE[NPART] = {{{', '.join(str(len(o)) for o in order)}}};")
+    w(f"static constexpr int PART_MAX = {width};")
+    # radial functions of every part but the last (what the last part's wave hands to the others
+    # in the pair-gradient kernel)
+    w(f"static constexpr int NMU_SHARED = {max([mu for p in parts[:-1] for mu, _ in p], default=-1) + 1};")
+    rows = ["{" + ", ".join(str(e) for e in o + [-1] * (width - len(o))) + "}" for o in order]
+    w(f"static constexpr int PART_ENTRY[NPART][PART_MAX] = {{{', '.join(rows)}}};")
+    for pi, part in enumerate(parts):
+        slot = {e: k for k, e in enumerate(order[pi])}
+        w("template <class R>")
+        w(f"static __device__ __forceinline__ void acc_part_p{pi}(R* __restrict__ m, const R* __restrict__ f, R x, R y, R z) {{")
+        w.push()
+        for mu in sorted({k[0] for k in part}):
+            avals = sorted(a for m2, a in part if m2 == mu)
+            w(f"{{  // mu = {mu}")
+            w.push()
+            w(f"R wx = f[{mu}];")
+            at = 0
+            for a in avals:
+                while at < a:
+                    w("wx *= x;")
+                    at += 1
+                bs = sorted(ents[mu, a])
+                assert bs == list(range(len(bs)))
+                w("{")
+                w.push()
+                w("R wy = wx;")
+                for b in bs:
+                    if b:
+                        w("wy *= y;")
+                    cs = sorted(ents[mu, a][b])
+                    assert cs == list(range(len(cs)))
+                    k = [slot[ents[mu, a][b][c]] for c in cs]
+                    w(f"m[{k[0]}] += wy;")
+                    if len(cs) > 1:
+                        w("{")
+                        w.push()
+                        cur = "wy"
+                        if len(cs) > 2:
+                            w("R wz = wy * z;")
+                            for c in cs[1:-1]:
+                                if c > 1:
+                                    w("wz *= z;")
+                                w(f"m[{k[c]}] += wz;")
+                            cur = "wz"
+                        w(f"m[{k[-1]}] = fma({cur}, z, m[{k[-1]}]);")
+                        w.pop()
+                        w("}")
+                w.pop()
+                w("}")
+            w.pop()
+            w("}")
+        w.pop()
+        w("}")
+    w("template <int P, class R>")
+    w("static __device__ __forceinline__ void acc_part(R* __restrict__ m, const R* __restrict__ f, R x, R y, R z) {")
+    w.push()
+    for p in range(len(parts)):
+        w(f"{'if' if p == 0 else 'else if'} constexpr (P == {p}) acc_part_p{p}<R>(m, f, x, y, z);")
+    w.pop()
+    w("}")
+
+
+def _emit_horner(w: _W, coef, pre):
+    """Value and gradient of sum coef[a, b, c] x^a y^b z^c in {pre}v, {pre}x, {pre}y, {pre}z by
+    Horner's scheme nested over x, y and z, each step carrying the derivative (d <- d t + v before
+    v <- v t + c).  A coefficient is read once and enters one multiply-add; about two multiply-adds
+    per coefficient in all.  Depth first, so that nine partial values are live at most.  Missing
+    coefficients are zero; the names of derivatives that vanish are not declared (returned: the
+    names declared, by direction)."""
+    top = max(a for a, _, _ in coef)
+    P = {}
+
+    def step(state, key, var, add):
+        """state[key] <- state[key] var + add (add may be None)."""
+        cur = state.get(key)
+        if cur is None:
+            if add is not None:
+                state[key] = f"{pre}{key}"
+                w(f"R {pre}{key} = {add};")
+        elif add is None:
+            w(f"{cur} = {cur} * {var};")
+        else:
+            w(f"{cur} = fma({cur}, {var}, {add});")
+
+    for a in range(top, -1, -1):
+        bs = [b for (a2, b, _) in coef if a2 == a]
+        M = {}
+        if bs:
+            w(f"R {pre}mv{a}, {pre}my{a}, {pre}mz{a};")
+        for b in range(max(bs) if bs else -1, -1, -1):
+            cs = [c for (a2, b2, c) in coef if (a2, b2) == (a, b)]
+            I = {}
+            tag = f"{a}_{b}"
+            for c in range(max(cs) if cs else -1, -1, -1):
+                k = coef.get((a, b, c))
+                v = I.get("v")
+                if v is not None:
+                    if "d" in I:
+                        w(f"{pre}id{tag} = fma({pre}id{tag}, z, {v});")
+                    else:
+                        w(f"R {pre}id{tag} = {v};")
+                        I["d"] = f"{pre}id{tag}"
+                    w(f"{v} = {f'fma({v}, z, {k})' if k else f'{v} * z'};")
+                elif k:
+                    I["v"] = f"{pre}iv{tag}"
+                    w(f"R {pre}iv{tag} = {k};")
+            for key, var, add in (("my", "y", M.get("mv")), ("mv", "y", I.get("v")), ("mz", "y", I.get("d"))):
+                cur, name = M.get(key), f"{pre}{key}{a}"
+                if cur is None:
+                    if add is not None:
+                        w(f"{name} = {add};")
+                        M[key] = name
+                elif add is None:
+                    w(f"{name} = {name} * {var};")
+                else:
+                    w(f"{name} = fma({name}, {var}, {add});")
+        step(P, "x", "x", P.get("v"))
+        step(P, "v", "x", M.get("mv"))
+        step(P, "y", "x", M.get("my"))
+        step(P, "z", "x", M.get("mz"))
+    return P
+
+
+def _emit_part_gradients(w: _W, prog: Program, parts):
+    """pair_part<P>: with the adjoints mb of part P's entries (in PART_ENTRY order), per radial
+    function g += f_mu grad P_mu and u += h_mu P_mu, P_mu = sum_e mb_e x^a y^b z^c."""
+    items = prog.layout.items
+    order = part_entries(prog, parts)
+    for pi, ents in enumerate(order):
+        w("template <class R>")
+        w(f"static __device__ __forceinline__ void pair_part_p{pi}(const R* __restrict__ mb, const R* __restrict__ f,")
+        w("    const R* __restrict__ h, R x, R y, R z, R& gx, R& gy, R& gz, R& u) {")
+        w.push()
+        for mu in sorted({items[e][0] for e in ents}):
+            coef = {items[e][1:]: f"mb[{k}]" for k, e in enumerate(ents) if items[e][0] == mu}
+            w("{")
+            w.push()
+            names = _emit_horner(w, coef, "p")
+            for d in "xyz":
+                if d in names:
+                    w(f"g{d} = fma(f[{mu}], {names[d]}, g{d});")
+            w(f"u = fma(h[{mu}], {names['v']}, u);")
+            w.pop()
+            w("}")
+        w.pop()
+        w("}")
+    w("template <int P, class R>")
+    w("static __device__ __forceinline__ void pair_part(const R* __restrict__ mb, const R* __restrict__ f,")
+    w("    const R* __restrict__ h, R x, R y, R z, R& gx, R& gy, R& gz, R& u) {")
+    w.push()
+    for p in range(len(parts)):
+        w(f"{'if' if p == 0 else 'else if'} constexpr (P == {p}) pair_part_p{p}<R>(mb, f, h, x, y, z, gx, gy, gz, u);")
+    w.pop()
+    w("}")
 
 
 def _degree(keys, nu):
@@ -536,6 +735,9 @@ def emit_level(level: int, n_groups: int = 1, rtan_budget: int = RTAN_REG_BUDGET
     w("static constexpr double MFACT[NMOM] = {" + ", ".join(
         "%d." % (math.factorial(a) * math.factorial(b) * math.factorial(c)) for (_, a, b, c) in prog.layout.items) + "};")
     _emit_pair_functions(w, prog, groups)
+    parts = moment_parts(prog)
+    _emit_moment_parts(w, prog, parts)
+    _emit_part_gradients(w, prog, parts)
     _emit_components_forward(w, prog)
     _emit_components_reverse(w, prog, groups)
     _emit_products(w, prog)

@@ -372,6 +372,7 @@ SysArgs make_sys_args(const mtp_model* m, const mtp_system* sys, const mtp_nlist
   a.off = nl.off;
   a.nj = nl.j;
   a.shift = nl.shift;
+  a.npairs = (int)nl.n_pairs;
   a.radial = (const double*)m->radial.p;
   for (int k = 0; k < 9; ++k) a.H[k] = sys->cell[k];
   a.cells = nullptr;
@@ -451,7 +452,7 @@ int run_energy_chain(mtp_model* m, const mtp_system* sys, const mtp_nlist& nl, d
   long blk = 0;
   for (int i0 = 0; i0 < n; i0 += chunk) {
     const int cn = std::min(chunk, n - i0);
-    for (int g = 0; g < L.ngroup; ++g) {
+    for (int g = 0; g < K.nmgroup; ++g) {
       ProfScope ps(&m->prof, P_MOMENTS, s);
       K.moments(g, a, i0, cn, mom, ld, s);
     }
@@ -462,9 +463,9 @@ int run_energy_chain(mtp_model* m, const mtp_system* sys, const mtp_nlist& nl, d
         K.program(mom, ld, i0, cn, sys->species, (const double*)m->linear.p, (const double*)m->shift.p, m->nsp,
                   e_atom, mbar, s);
       }
-      {
+      for (int g = 0; g < K.nbgroup; ++g) {
         ProfScope ps(&m->prof, P_BACKWARD, s);
-        K.backward(0, a, i0, cn, mbar, ld, w.g, 0, w.wpart + 6 * blk, nullptr, w.fown, s);
+        K.backward(g, a, i0, cn, mbar, ld, w.g, w.wpart + 6 * blk, nullptr, w.fown, s);
       }
       blk += pair_blocks(cn, a.split);
       continue;
@@ -480,9 +481,9 @@ int run_energy_chain(mtp_model* m, const mtp_system* sys, const mtp_nlist& nl, d
         ProfScope ps(&m->prof, P_PROG_REV, s);
         K.prog_rev(g, mom, ld, cn, cbar, mbar, s);
       }
-      for (int g = 0; g < L.ngroup; ++g) {
+      for (int g = 0; g < K.nbgroup; ++g) {
         ProfScope ps(&m->prof, P_BACKWARD, s);
-        K.backward(g, a, i0, cn, mbar, ld, w.g, g > 0, w.wpart + 6 * blk, nullptr, w.fown, s);
+        K.backward(g, a, i0, cn, mbar, ld, w.g, w.wpart + 6 * blk, nullptr, w.fown, s);
       }
       blk += pair_blocks(cn, a.split);
     }
@@ -691,7 +692,7 @@ extern "C" int mtp_param_grad(mtp_model* m, const mtp_system* sys, const mtp_nli
   for (int i0 = 0; i0 < n; i0 += chunk, ++c) {
     const int cn = std::min(chunk, n - i0);
     const long cblk = (cn + kLaneBlockHost - 1) / kLaneBlockHost;
-    for (int g = 0; g < L.ngroup; ++g) {
+    for (int g = 0; g < L.chain[0].nmgroup; ++g) {
       ProfScope ps(&m->prof, P_MOMENTS, s);
       L.chain[0].moments(g, a, i0, cn, mom, ld, s);
     }

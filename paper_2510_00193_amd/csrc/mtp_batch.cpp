@@ -110,7 +110,7 @@ static long pair_launches(const mtp_batch* b) {
   const LevelOps& L = b->m->ops;
   const long ld = chunk_of(b);
   const long nchunks = ((long)b->n + ld - 1) / ld;
-  return nchunks * (3L * L.ngroup + L.adj.ntgroup + L.adj.nagroup) + 1;
+  return nchunks * (2L * L.chain[2].nmgroup + L.chain[2].nbgroup + L.adj.ntgroup + L.adj.nagroup) + 1;
 }
 
 static int set_schedule(mtp_batch* b, int sorted, int chunk, int persistent) {
@@ -161,6 +161,7 @@ static void run_impl(mtp_batch* b, const double* e_target, const double* f_targe
   a.off = (const int*)b->off.p;
   a.nj = (const int*)b->nj.p;
   a.shift = (const int*)b->shift.p;
+  a.npairs = (int)b->npairs;
   a.radial = (const double*)m->radial.p;
   a.cells = (const double*)b->cells.p;
   a.cfg = (const int*)b->cfg.p;
@@ -191,7 +192,7 @@ static void run_impl(mtp_batch* b, const double* e_target, const double* f_targe
   // ---- forward: energies, pair gradients, per-atom virials
   for (long i0 = 0; i0 < n; i0 += ld) {
     const int cn = (int)std::min(ld, (long)n - i0);
-    for (int gi = 0; gi < L.ngroup; ++gi) {
+    for (int gi = 0; gi < K.nmgroup; ++gi) {
       ProfScope ps(&m->prof, P_MOMENTS, s);
       a.queue = q();
       K.moments(gi, a, (int)i0, cn, b->mom.p, ld, s);
@@ -205,10 +206,10 @@ static void run_impl(mtp_batch* b, const double* e_target, const double* f_targe
       ProfScope ps(&m->prof, P_PROG_REV, s);
       K.prog_rev(gi, b->mom.p, ld, cn, b->cbar.p, b->mbar.p, s);
     }
-    for (int gi = 0; gi < L.ngroup; ++gi) {
+    for (int gi = 0; gi < K.nbgroup; ++gi) {
       ProfScope ps(&m->prof, P_BACKWARD, s);
       a.queue = q();
-      K.backward(gi, a, (int)i0, cn, b->mbar.p, ld, g, gi > 0, wpart + 6 * blk, wa, (double*)b->fown.p, s);
+      K.backward(gi, a, (int)i0, cn, b->mbar.p, ld, g, wpart + 6 * blk, wa, (double*)b->fown.p, s);
     }
     blk += (cn + kLaneBlockHost - 1) / kLaneBlockHost;
   }
@@ -249,7 +250,7 @@ static void run_impl(mtp_batch* b, const double* e_target, const double* f_targe
     const int cn = (int)std::min(ld, (long)n - i0);
     const long cblk = (cn + kLaneBlockHost - 1) / kLaneBlockHost;
     if (ld < n) {  // the forward state of this chunk was overwritten by later chunks
-      for (int gi = 0; gi < L.ngroup; ++gi) {
+      for (int gi = 0; gi < K.nmgroup; ++gi) {
         ProfScope ps(&m->prof, P_MOMENTS, s);
         a.queue = q();
         K.moments(gi, a, (int)i0, cn, b->mom.p, ld, s);

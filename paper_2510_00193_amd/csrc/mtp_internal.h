@@ -18,6 +18,7 @@ struct SysArgs {
   const int* off;         // [N+1]
   const int* nj;          // [P]
   const int* shift;       // [P] packed int8 x3
+  int npairs;             // P (below 2^31)
   const double* radial;   // [nsp][nsp][nmu][ncheb]
   double H[9];            // rows = lattice vectors (single system)
   const double* cells;    // [n_cfg][9] per-configuration cells (batches), or null
@@ -47,13 +48,16 @@ struct ChainOps {
                    const double* xi, const double* shift, int nsp, double* e_atom, void* cbar,
                    double* bout, hipStream_t s);
   void (*prog_rev)(int g, const void* m, long ld, int n, const void* cb, void* mb, hipStream_t s);
+  // passes grp = 0 (stores), 1, ... (add) over the pairs, in order on one stream
   // fown (optional, [atom][3]): (+)= the atom's own pair-gradient sum, for launch_gather_forces
   void (*backward)(int grp, const SysArgs& a, int i0, int n, const void* mb, long ld, double* g,
-                   int acc, double* wpart, double* watom, double* fown, hipStream_t s);
+                   double* wpart, double* watom, double* fown, hipStream_t s);
   // forward + products + reverse in one kernel (single-group levels, one system; else null):
   // writes e_atom[i0 + k] and the moment adjoints
   void (*program)(const void* m, long ld, int i0, int n, const int* species, const double* xi,
                   const double* shift, int nsp, double* e_atom, void* mb, hipStream_t s);
+  int nmgroup;  // launches of moments (g < nmgroup)
+  int nbgroup;  // passes of backward (grp < nbgroup), each over a range of the moment adjoints
 };
 
 // Parameter-adjoint launchers of one level (binary64).

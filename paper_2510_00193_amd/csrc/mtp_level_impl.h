@@ -43,25 +43,27 @@ struct TileLoop {
     else return nblocks;
   }
 };
-// K lanes per atom: a tile holds kLaneBlock / K atoms
-#define MTP_FOR_TILES_K(a, n, K, b)                                                                    \
-  __shared__ int tile_slot_;                                                                           \
-  const TileLoop<PERSIST> tiles_{(int)(((long)(n) * (K) + kLaneBlock - 1) / kLaneBlock), &tile_slot_}; \
+// tiles of kLaneBlock / k atoms (k lanes per atom)
+__host__ __device__ inline int split_tiles(int n, int k) { return (int)(((long)n * k + kLaneBlock - 1) / kLaneBlock); }
+// K lanes per atom, NP workgroups (parts) per tile: b counts tile * NP + part
+#define MTP_FOR_TILES_K(a, n, K, NP, b)                                                                \
+  __shared__ int tile_slot_[1]; /* no storage unless PERSIST uses it */                                \
+  const TileLoop<PERSIST> tiles_{split_tiles(n, K) * (NP), tile_slot_};                                \
   for (int b = tiles_.first(a); b < tiles_.nblocks; b = tiles_.next(a))
-#define MTP_FOR_TILES(a, n, b) MTP_FOR_TILES_K(a, n, 1, b)
+#define MTP_FOR_TILES(a, n, b) MTP_FOR_TILES_K(a, n, 1, 1, b)
 
 // Sum over the K consecutive lanes of an atom (K = 1, 2, 4, 8) by DPP lane exchanges inside
 // quads and half-rows; every lane of the group ends with the same value (each step adds two
 // equal partial sums in either order, which is exact commutativity).
 template <int CTRL>
 __device__ __forceinline__ double dpp_exchange(double v) {
-  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xF, 0xF, false);
-  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xF, 0xF, false);
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xF, 0xF, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xF, 0xF, true);
   return __hiloint2double(hi, lo);
 }
 template <int CTRL>
 __device__ __forceinline__ float dpp_exchange(float v) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, false));
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, true));
 }
 template <int K, class R>
 __device__ __forceinline__ R group_sum(R v) {
@@ -69,6 +71,18 @@ __device__ __forceinline__ R group_sum(R v) {
   if constexpr (K >= 2) v += dpp_exchange<0xB1>(v);   // quad_perm [1, 0, 3, 2]
   if constexpr (K >= 4) v += dpp_exchange<0x4E>(v);   // quad_perm [2, 3, 0, 1]
   if constexpr (K >= 8) v += dpp_exchange<0x141>(v);  // row_half_mirror
+  return v;
+}
+
+// Sum over the 64 lanes of a wave in a fixed order (every lane gets it): DPP exchanges inside
+// 16-lane rows (quads, half-row mirror, row mirror), two cross-row exchanges.
+__device__ __forceinline__ double wave_sum(double v) {
+  v += dpp_exchange<0xB1>(v);   // quad_perm [1, 0, 3, 2]
+  v += dpp_exchange<0x4E>(v);   // quad_perm [2, 3, 0, 1]
+  v += dpp_exchange<0x141>(v);  // row_half_mirror
+  v += dpp_exchange<0x140>(v);  // row_mirror
+  v += __shfl_xor(v, 16, 64);
+  v += __shfl_xor(v, 32, 64);
   return v;
 }
 
@@ -139,52 +153,166 @@ struct RegMoments {
   __device__ __forceinline__ R operator()(int e) const { return m[e]; }
 };
 
-// radial coefficient table staged in LDS (in the arithmetic type of the kernel)
+// radial coefficient table staged in LDS (in the arithmetic type of the kernel); dynamic shared
+// memory of radial_bytes at the launch, so that a small table leaves room for more waves
 template <class R>
-__device__ __forceinline__ void stage_radial(const SysArgs& a, R* sh) {
+__device__ __forceinline__ R* stage_radial(const SysArgs& a) {
+  extern __shared__ __align__(16) double radial_table_[];
+  R* sh = reinterpret_cast<R*>(radial_table_);
   const int n = a.nsp * a.nsp * a.nmu * a.ncheb;
   for (int k = threadIdx.x; k < n; k += blockDim.x) sh[k] = (R)a.radial[k];
   __syncthreads();
+  return sh;
+}
+template <class R>
+inline unsigned radial_bytes(const SysArgs& a) {
+  return (unsigned)(a.nsp * a.nsp * a.nmu * a.ncheb * (int)sizeof(R));
 }
 
-// Walk the CSR row of atom i with software prefetch: the partner indices are loaded two pairs
-// ahead and the partner position/species one pair ahead, so the gather latency overlaps the
-// arithmetic of the current pair.  body(p, j, zj, dx, dy, dz, r) sees the exact displacement.
-// With K lanes per atom, lane sub of the atom takes pairs sub, sub + K, sub + 2K, ... of the row.
-template <int K = 1, class F>
-__device__ __forceinline__ void for_pairs(const SysArgs& a, int i, int sub, const double* H, double rix,
-                                          double riy, double riz, F&& body) {
-  const int p0 = a.off[i] + sub, p1 = a.off[i + 1];
-  if (p0 >= p1) return;
-  int jA = a.nj[p0], shA = a.shift[p0];
-  double xA = a.pos[3 * jA], yA = a.pos[3 * jA + 1], zA = a.pos[3 * jA + 2];
-  int sA = a.species[jA];
-  int jB = 0, shB = 0;
-  if (p0 + K < p1) {
-    jB = a.nj[p0 + K];
-    shB = a.shift[p0 + K];
+// One lane per atom: the lanes of a wave read 64 different rows of the list, so each 4-byte read
+// of a list array touches 64 cache lines, and the lines of the four waves of a CU do not stay in
+// its 32 KB L1 until the next pair; the refills bounded the pair loops (the loads issued a whole
+// pair ahead were still waited for: with the instructions cut by a quarter the pair-gradient kernel
+// stayed at 1.14 ms at a million atoms, staged rows took it to 0.95).  So a lane copies its row, kRowStage pairs at a time with
+// 16-byte reads, to a column of its own in LDS (16 KB per wave) and reads the pairs from there.
+constexpr int kRowStage = 32;
+struct alignas(8) ListEntry {
+  int j, shift;
+};
+
+// The four list entries from pair p on.  Entries past the end of the list repeat its last one;
+// entries past the row's end belong to other rows and are not used.
+__device__ __forceinline__ void load_entries(const SysArgs& a, int p, ListEntry* e) {
+  typedef int v4i __attribute__((ext_vector_type(4), aligned(4)));
+  const int last = a.npairs - 4;
+  if (last < 0) {  // the whole list holds fewer than four pairs
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int q = min(p + k, a.npairs - 1);
+      e[k] = ListEntry{a.nj[q], a.shift[q]};
+    }
+    return;
   }
-  for (int p = p0; p < p1; p += K) {
-    const int j = jA, sh = shA, sj = sA;
-    const double xj = xA, yj = yA, zj = zA;
-    if (p + K < p1) {
-      xA = a.pos[3 * jB];
-      yA = a.pos[3 * jB + 1];
-      zA = a.pos[3 * jB + 2];
-      sA = a.species[jB];
-      jA = jB;
-      shA = shB;
+  const int b = min(p, last), d = min(p - b, 3);
+  v4i j = *reinterpret_cast<const v4i*>(a.nj + b);
+  v4i s = *reinterpret_cast<const v4i*>(a.shift + b);
+  if (d & 1) {  // the end of the list: entry k is element k + d of what was read
+    j = v4i{j[1], j[2], j[3], j[3]};
+    s = v4i{s[1], s[2], s[3], s[3]};
+  }
+  if (d & 2) {
+    j = v4i{j[2], j[3], j[3], j[3]};
+    s = v4i{s[2], s[3], s[3], s[3]};
+  }
+#pragma unroll
+  for (int k = 0; k < 4; ++k) e[k] = ListEntry{j[k], s[k]};
+}
+
+// Copy pairs [p, p + m) of a row to the lane's LDS column (stride kLaneBlock); m <= kRowStage.
+__device__ __forceinline__ void stage_row(const SysArgs& a, int p, int m, ListEntry* __restrict__ col) {
+  ListEntry e[kRowStage];
+#pragma unroll
+  for (int k = 0; k < kRowStage; k += 4)
+    if (k < m) load_entries(a, p + k, e + k);
+#pragma unroll
+  for (int k = 0; k < kRowStage; ++k)
+    if (k < m) col[k * kLaneBlock] = e[k];
+}
+
+// Displacement, then prefetch() (the next pair's loads, into the registers this pair's position just
+// left: no copies, which would wait for the loads), then distance and the body (see for_pairs).  The
+// barriers keep the scheduler from moving the loads.
+template <class R, class P, class F>
+__device__ __forceinline__ void one_pair(const SysArgs& a, int p, int j, int sh, int sj, const double* H, double rix,
+                                         double riy, double riz, double xj, double yj, double zj, P&& prefetch,
+                                         F&& body) {
+  int n1, n2, n3;
+  unpack_shift(sh, n1, n2, n3);
+  double dx, dy, dz;
+  pair_displacement(rix, riy, riz, xj, yj, zj, n1, n2, n3, H, dx, dy, dz);
+  const int zj_ = clamp_species(sj, a.nsp);
+  __builtin_amdgcn_sched_barrier(0);
+  prefetch();
+  __builtin_amdgcn_sched_barrier(0);
+  double r, rinv;
+  if constexpr (std::is_same_v<R, double>) {
+    root_and_inverse(dist2_exact(dx, dy, dz), r, rinv);
+  } else {
+    r = sqrt(dist2_exact(dx, dy, dz));
+    rinv = 0.0;  // not used
+  }
+  body(p, j, zj_, dx, dy, dz, r, rinv);
+}
+
+// Wait for every outstanding vector memory operation (vmcnt 0; the other counters at their
+// maximum).  Before a pair loop: the waits inside it are then counted for the loop's own
+// operations alone, not for the path that enters it.
+__device__ __forceinline__ void drain_loads() { __builtin_amdgcn_s_waitcnt(0x0F70); }
+
+// Walk the CSR row of atom i with software prefetch: the partner position and species are loaded
+// one pair ahead, so the gather latency overlaps the arithmetic of the current pair.  The prefetch
+// index is clamped to the row instead of guarded: a loop body without branches around its memory
+// operations lets the waits count them exactly, so the wait for a pair's loads does not also wait
+// for younger stores (guarded loads and stores make every wait a full drain).
+// body(p, j, zj, dx, dy, dz, r, rinv) sees the exact displacement; R is the arithmetic type of the
+// kernel (binary32 kernels round the correctly rounded r).
+// With K lanes per atom, lane sub of the atom takes pairs sub, sub + K, sub + 2K, ... of the row
+// (the lanes of an atom read consecutive list entries); with one, lst is the wave's LDS stage.
+template <int K = 1, class R = double, class F>
+__device__ __forceinline__ void for_pairs(const SysArgs& a, ListEntry* lst, int i, int sub, const double* H,
+                                          double rix, double riy, double riz, F&& body) {
+  const int p0 = a.off[i] + sub, p1 = a.off[i + 1];
+  if constexpr (K == 1) {
+    ListEntry* col = lst + (threadIdx.x & (kLaneBlock - 1));
+    for (int b = p0; b < p1; b += kRowStage) {
+      const int m = min(kRowStage, p1 - b);
+      stage_row(a, b, m, col);
+      ListEntry cur = col[0], nxt = col[(m > 1) * kLaneBlock];
+      double xA = a.pos[3 * cur.j], yA = a.pos[3 * cur.j + 1], zA = a.pos[3 * cur.j + 2];
+      int sA = a.species[cur.j];
+      int k = 0;
+      drain_loads();
+      do {
+        one_pair<R>(
+            a, b + k, cur.j, cur.shift, sA, H, rix, riy, riz, xA, yA, zA,
+            [&]() {
+              cur = nxt;
+              xA = a.pos[3 * cur.j];
+              yA = a.pos[3 * cur.j + 1];
+              zA = a.pos[3 * cur.j + 2];
+              sA = a.species[cur.j];
+              nxt = col[min(k + 2, m - 1) * kLaneBlock];
+            },
+            body);
+        ++k;
+      } while (k < m);
     }
-    if (p + 2 * K < p1) {
-      jB = a.nj[p + 2 * K];
-      shB = a.shift[p + 2 * K];
-    }
-    int n1, n2, n3;
-    unpack_shift(sh, n1, n2, n3);
-    double dx, dy, dz;
-    pair_displacement(rix, riy, riz, xj, yj, zj, n1, n2, n3, H, dx, dy, dz);
-    const double r = sqrt(dist2_exact(dx, dy, dz));
-    body(p, j, clamp_species(sj, a.nsp), dx, dy, dz, r);
+  } else {
+    if (p0 >= p1) return;
+    int jA = a.nj[p0], shA = a.shift[p0];
+    const int pB = min(p0 + K, p1 - 1);
+    int jB = a.nj[pB], shB = a.shift[pB];
+    double xA = a.pos[3 * jA], yA = a.pos[3 * jA + 1], zA = a.pos[3 * jA + 2];
+    int sA = a.species[jA];
+    int p = p0;
+    drain_loads();
+    do {
+      one_pair<R>(
+          a, p, jA, shA, sA, H, rix, riy, riz, xA, yA, zA,
+          [&]() {
+            xA = a.pos[3 * jB];
+            yA = a.pos[3 * jB + 1];
+            zA = a.pos[3 * jB + 2];
+            sA = a.species[jB];
+            jA = jB;
+            shA = shB;
+            const int pn = min(p + 2 * K, p1 - 1);
+            jB = a.nj[pn];
+            shB = a.shift[pn];
+          },
+          body);
+      p += K;
+    } while (p < p1);
   }
 }
 
@@ -205,39 +333,71 @@ __device__ __forceinline__ void cell_of(const SysArgs& a, int i, double* H) {
   }
 }
 
-// K lanes per atom (single systems): each accumulates every K-th pair of the row, the partial
-// moments are summed over the atom's lanes and its first lane writes them.
-template <class L, int G, class R, bool BATCH, int NC, bool PERSIST = false, int K = 1>
-__global__ __launch_bounds__(kLaneBlock) void k_moments(SysArgs a, int i0, int n,
-                                                        R* __restrict__ mout, long ld) {
-  static_assert(K == 1 || !BATCH, "batches take one lane per atom");
-  __shared__ R csh[kMaxRadial];
-  stage_radial(a, csh);
-  MTP_FOR_TILES_K(a, n, K, b) {
-  const int li = b * (kLaneBlock / K) + (int)threadIdx.x / K, sub = (int)threadIdx.x % K;
-  if (li >= n) continue;
-  const int i = sweep_atom<BATCH>(a, i0 + li);
+// One part of the moments (binary64) or one group of the layout (binary32) of one atom: K lanes
+// per atom (single systems) each accumulate every K-th pair of the row, the partial moments are
+// summed over the atom's lanes and its first lane writes them.
+template <class L, int P, class R, bool BATCH, int NC, int K>
+__device__ __forceinline__ void moments_of_atom(const SysArgs& a, const R* csh, ListEntry* lst, int i, int li, int sub,
+                                                R* __restrict__ mout, long ld) {
+  constexpr bool PARTS = std::is_same_v<R, double>;
+  constexpr int LO = PARTS ? 0 : L::GROUP_LO[PARTS ? 0 : P];
+  constexpr int NE = PARTS ? L::PART_SIZE[PARTS ? P : 0] : L::GROUP_HI[PARTS ? 0 : P] - LO;
   double H[9];
   cell_of<BATCH>(a, i, H);
-  constexpr int LO = L::GROUP_LO[G], HI = L::GROUP_HI[G], NG = HI - LO;
-  R m[NG];
+  R m[NE];
 #pragma unroll
-  for (int e = 0; e < NG; ++e) m[e] = R(0);
+  for (int e = 0; e < NE; ++e) m[e] = R(0);
   const double rix = a.pos[3 * i], riy = a.pos[3 * i + 1], riz = a.pos[3 * i + 2];
   const int zi = clamp_species(a.species[i], a.nsp);
   const R* cz = csh + zi * a.nsp * L::NMU * a.ncheb;
-  for_pairs<K>(a, i, sub, H, rix, riy, riz, [&](int, int, int zj, double dx, double dy, double dz, double r) {
+  for_pairs<K, R>(a, lst, i, sub, H, rix, riy, riz, [&](int, int, int zj, double dx, double dy, double dz, double r, double) {
     R f[L::NMU];
     radial_values<R, L::NMU, NC>((R)r, (R)a.sa, (R)a.sb, (R)a.rcut, cz + zj * L::NMU * a.ncheb, a.ncheb, f);
-    L::template acc_moments<G>(m, f, (R)dx, (R)dy, (R)dz);
+    if constexpr (PARTS) L::template acc_part<P>(m, f, (R)dx, (R)dy, (R)dz);
+    else L::template acc_moments<P>(m, f, (R)dx, (R)dy, (R)dz);
   });
   if constexpr (K > 1) {
 #pragma unroll
-    for (int e = 0; e < NG; ++e) m[e] = group_sum<K>(m[e]);
+    for (int e = 0; e < NE; ++e) {
+      m[e] = group_sum<K>(m[e]);
+      asm volatile("" : "+v"(m[e]));  // finished here: the last addition is not moved to the store (spills)
+    }
   }
   if (sub == 0) {
 #pragma unroll
-    for (int e = 0; e < NG; ++e) mout[(long)(LO + e) * ld + li] = m[e];
+    for (int e = 0; e < NE; ++e) mout[(long)(PARTS ? L::PART_ENTRY[PARTS ? P : 0][PARTS ? e : 0] : LO + e) * ld + li] = m[e];
+  }
+}
+
+// Moments of 64 / K atoms per workgroup (one wave).  In binary64 the entries are cut into NPART
+// parts of at most 84 that different waves accumulate over the same pairs: one wave with all 130
+// entries of level 16 filled the registers of a SIMD by itself, moved a third of its accumulators
+// through accumulation registers for every pair and stood waiting on its loads a quarter of the
+// time.  The parts repeat a pair's geometry and radial functions, but two waves share a SIMD:
+// 0.73 -> 0.59 ms at 1,024,000 atoms of level 16 (the vector unit is busy three quarters of it),
+// 1.93 -> 1.17 ms at level 20 (545,505 atoms; it took three passes before).
+// Binary32: group G of the layout.
+template <class L, int G, class R, bool BATCH, int NC, bool PERSIST = false, int K = 1>
+__global__ __launch_bounds__(kLaneBlock) __attribute__((amdgpu_waves_per_eu(std::is_same_v<R, double> ? 2 : 1)))
+void k_moments(SysArgs a, int i0, int n, R* __restrict__ mout, long ld) {
+  static_assert(K == 1 || !BATCH, "batches take one lane per atom");
+  constexpr int NP = std::is_same_v<R, double> ? L::NPART : 1;
+  __shared__ ListEntry lst[K == 1 ? kRowStage * kLaneBlock : 1];
+  const R* csh = stage_radial<R>(a);
+  MTP_FOR_TILES_K(a, n, K, NP, b) {
+  // parts of a tile in consecutive workgroups: they read the same rows
+  const int li = (b / NP) * (kLaneBlock / K) + (int)threadIdx.x / K, sub = (int)threadIdx.x % K;
+  if (li >= n) continue;
+  const int i = sweep_atom<BATCH>(a, i0 + li);
+  if constexpr (NP == 1) {
+    moments_of_atom<L, G, R, BATCH, NC, K>(a, csh, lst, i, li, sub, mout, ld);
+  } else {
+    static_assert(NP <= 4, "moment parts");
+    const int part = b % NP;
+    if (part == 0) moments_of_atom<L, 0, R, BATCH, NC, K>(a, csh, lst, i, li, sub, mout, ld);
+    else if (part == 1) moments_of_atom<L, 1, R, BATCH, NC, K>(a, csh, lst, i, li, sub, mout, ld);
+    else if (NP > 2 && part == 2) moments_of_atom<L, (NP > 2 ? 2 : 0), R, BATCH, NC, K>(a, csh, lst, i, li, sub, mout, ld);
+    else if (NP > 3) moments_of_atom<L, (NP > 3 ? 3 : 0), R, BATCH, NC, K>(a, csh, lst, i, li, sub, mout, ld);
   }
   }
 }
@@ -329,84 +489,16 @@ __global__ __launch_bounds__(kLaneBlock) void k_program(const R* __restrict__ mo
 }
 
 // ---------------------------------------------------------------------------- backward pairs
-// g[p] (+)= dE_i/dd_ij restricted to the entries of group G; per-workgroup virial partials;
-// fown[i] (+)= sum of the atom's own g over its row (the first half of its force), when given.
-// K lanes per atom (single systems): each takes every K-th pair of the row; the own sums are
-// combined over the atom's lanes, the virial partial over the workgroup as before.
-template <class L, int G, class R, bool BATCH, int NC, bool PERSIST = false, int K = 1>
-__global__ __launch_bounds__(kLaneBlock) void k_backward(SysArgs a, int i0, int n,
-                                                         const R* __restrict__ mbar, long ld,
-                                                         double* __restrict__ g, int accumulate,
-                                                         double* __restrict__ wpart,
-                                                         double* __restrict__ watom,
-                                                         double* __restrict__ fown) {
-  static_assert(K == 1 || !BATCH, "batches take one lane per atom");
-  __shared__ R csh[kMaxRadial];
-  __shared__ double red[kLaneBlock];
-  stage_radial(a, csh);
-  MTP_FOR_TILES_K(a, n, K, b) {
-  const int li = b * (kLaneBlock / K) + (int)threadIdx.x / K, sub = (int)threadIdx.x % K;
-  constexpr int LO = L::GROUP_LO[G], HI = L::GROUP_HI[G], NG = HI - LO;
-  double w[6] = {0, 0, 0, 0, 0, 0};
-  double fo[3] = {0, 0, 0};  // sum of the atom's own pair gradients
-  if (li < n) {
-    const int i = sweep_atom<BATCH>(a, i0 + li);
-    double H[9];
-    cell_of<BATCH>(a, i, H);
-    R mb[NG];
-    // adjoints scaled by a! b! c! for the scaled monomials of pair_grad
-#pragma unroll
-    for (int e = 0; e < NG; ++e) mb[e] = mbar[(long)(LO + e) * ld + li] * R(L::MFACT[LO + e]);
-    const double rix = a.pos[3 * i], riy = a.pos[3 * i + 1], riz = a.pos[3 * i + 2];
-    const int zi = clamp_species(a.species[i], a.nsp);
-    const R* cz = csh + zi * a.nsp * L::NMU * a.ncheb;
-    // the gradient of a pair is stored at the start of the next pair's body, after that
-    // pair's list and position loads: the wait for those loads at the end of the body then
-    // does not also wait for a store issued just before it (one counter covers both)
-    int pq = -1;
-    double qx = 0.0, qy = 0.0, qz = 0.0;
-    for_pairs<K>(a, i, sub, H, rix, riy, riz, [&](int p, int, int zj, double dx, double dy, double dz, double r) {
-      if (pq >= 0) {
-        g[3L * pq] = qx;
-        g[3L * pq + 1] = qy;
-        g[3L * pq + 2] = qz;
-      }
-      R f[L::NMU], fp[L::NMU];
-      radial<R, L::NMU, NC>((R)r, (R)a.sa, (R)a.sb, (R)a.rcut, cz + zj * L::NMU * a.ncheb, a.ncheb, f, fp);
-      R rgx = R(0), rgy = R(0), rgz = R(0), ru = R(0);
-      L::template pair_grad<G>(mb, f, fp, (R)dx, (R)dy, (R)dz, rgx, rgy, rgz, ru);
-      const double ur = (double)ru / r;
-      const double gx = fma(ur, dx, (double)rgx);
-      const double gy = fma(ur, dy, (double)rgy);
-      const double gz = fma(ur, dz, (double)rgz);
-      if (accumulate) {
-        g[3L * p] += gx;
-        g[3L * p + 1] += gy;
-        g[3L * p + 2] += gz;
-      } else {
-        pq = p;
-        qx = gx;
-        qy = gy;
-        qz = gz;
-      }
-      fo[0] += gx;
-      fo[1] += gy;
-      fo[2] += gz;
-      w[0] -= dx * gx;
-      w[1] -= dy * gy;
-      w[2] -= dz * gz;
-      w[3] -= dx * gy;
-      w[4] -= dx * gz;
-      w[5] -= dy * gz;
-    });
-    if (pq >= 0) {
-      g[3L * pq] = qx;
-      g[3L * pq + 1] = qy;
-      g[3L * pq + 2] = qz;
-    }
+// The end of a pair-gradient tile: per-atom virials (batches), the atoms' own gradient sums and the
+// workgroup's virial partial.  With ADD (a later pass over the pairs) everything is added to.
+template <bool BATCH, int K, bool ADD>
+__device__ __forceinline__ void finish_gradients(bool live, int i, int sub, int tile, double* w, double* fo,
+                                                 double* __restrict__ wpart, double* __restrict__ watom,
+                                                 double* __restrict__ fown) {
+  if (live) {
     if constexpr (BATCH) {
 #pragma unroll
-      for (int k = 0; k < 6; ++k) watom[6L * i + k] = accumulate ? watom[6L * i + k] + w[k] : w[k];
+      for (int k = 0; k < 6; ++k) watom[6L * i + k] = ADD ? watom[6L * i + k] + w[k] : w[k];
     }
     if constexpr (K > 1) {
 #pragma unroll
@@ -414,16 +506,295 @@ __global__ __launch_bounds__(kLaneBlock) void k_backward(SysArgs a, int i0, int 
     }
     if (fown && sub == 0) {
 #pragma unroll
-      for (int k = 0; k < 3; ++k) fown[3L * i + k] = accumulate ? fown[3L * i + k] + fo[k] : fo[k];
+      for (int k = 0; k < 3; ++k) fown[3L * i + k] = ADD ? fown[3L * i + k] + fo[k] : fo[k];
     }
   }
-  // with accumulate, the launches of the moment groups run one after another on one stream and
-  // each adds its share to the same per-workgroup partial
+  // one wave holds the tile's sums: register butterflies (fixed order)
 #pragma unroll
-  for (int k = 0; k < 6; ++k) {
-    const double s = block_sum<kLaneBlock>(w[k], red);
-    if (threadIdx.x == 0) wpart[6L * b + k] = accumulate ? wpart[6L * b + k] + s : s;
+  for (int k = 0; k < 6; ++k) w[k] = wave_sum(w[k]);
+  if ((threadIdx.x & (kLaneBlock - 1)) == 0) {
+#pragma unroll
+    for (int k = 0; k < 6; ++k) wpart[6L * tile + k] = ADD ? wpart[6L * tile + k] + w[k] : w[k];
   }
+}
+
+// own sum and virial of one pair gradient
+__device__ __forceinline__ void add_gradient(double dx, double dy, double dz, double gx, double gy, double gz,
+                                             double* fo, double* w) {
+  fo[0] += gx;
+  fo[1] += gy;
+  fo[2] += gz;
+  w[0] -= dx * gx;
+  w[1] -= dy * gy;
+  w[2] -= dz * gz;
+  w[3] -= dx * gy;
+  w[4] -= dx * gz;
+  w[5] -= dy * gz;
+}
+
+// g[p] (+)= dE_i/dd_ij restricted to the entries of group G (binary32; binary64 levels of one part
+// take the whole adjoint by pair_part); per-workgroup virial partials;
+// fown[i] (+)= sum of the atom's own g over its row (the first half of its force), when given.
+// K lanes per atom (single systems): each takes every K-th pair of the row; the own sums are
+// combined over the atom's lanes, the virial partial over the workgroup as before.
+template <class L, int G, class R, bool BATCH, int NC, bool PERSIST = false, int K = 1>
+__global__ __launch_bounds__(kLaneBlock) __attribute__((amdgpu_waves_per_eu(std::is_same_v<R, double> ? 2 : 1)))
+void k_backward(SysArgs a, int i0, int n, const R* __restrict__ mbar, long ld, double* __restrict__ g,
+                double* __restrict__ wpart, double* __restrict__ watom, double* __restrict__ fown) {
+  static_assert(K == 1 || !BATCH, "batches take one lane per atom");
+  constexpr bool PARTS = std::is_same_v<R, double>;
+  constexpr bool accumulate = G > 0;  // the first pass stores, later ones add
+  constexpr int LO = PARTS ? 0 : L::GROUP_LO[PARTS ? 0 : G];
+  constexpr int NG = PARTS ? L::NMOM : L::GROUP_HI[PARTS ? 0 : G] - LO;
+  static_assert(!PARTS || L::NPART == 1, "levels of several parts take k_backward_stages");
+  __shared__ ListEntry lst[K == 1 ? kRowStage * kLaneBlock : 1];
+  const R* csh = stage_radial<R>(a);
+  MTP_FOR_TILES_K(a, n, K, 1, b) {
+  const int li = b * (kLaneBlock / K) + (int)threadIdx.x / K, sub = (int)threadIdx.x % K;
+  double w[6] = {0, 0, 0, 0, 0, 0};
+  double fo[3] = {0, 0, 0};  // sum of the atom's own pair gradients
+  int i = 0;
+  if (li < n) {
+    i = sweep_atom<BATCH>(a, i0 + li);
+    double H[9];
+    cell_of<BATCH>(a, i, H);
+    R mb[NG];
+    // binary32: adjoints scaled by a! b! c! for the scaled monomials of pair_grad
+#pragma unroll
+    for (int e = 0; e < NG; ++e) {
+      mb[e] = mbar[(long)(PARTS ? L::PART_ENTRY[0][PARTS ? e : 0] : LO + e) * ld + li];
+      if constexpr (!PARTS) mb[e] *= R(L::MFACT[LO + e]);
+    }
+    const double rix = a.pos[3 * i], riy = a.pos[3 * i + 1], riz = a.pos[3 * i + 2];
+    const int zi = clamp_species(a.species[i], a.nsp);
+    const R* cz = csh + zi * a.nsp * L::NMU * a.ncheb;
+    for_pairs<K, R>(a, lst, i, sub, H, rix, riy, riz, [&](int p, int, int zj, double dx, double dy, double dz, double r, double rinv) {
+      double old[3] = {0.0, 0.0, 0.0};  // loaded ahead of the arithmetic
+      if constexpr (accumulate) {
+#pragma unroll
+        for (int k = 0; k < 3; ++k) old[k] = g[3L * p + k];
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      R f[L::NMU], fp[L::NMU];
+      radial<R, L::NMU, NC>((R)r, (R)a.sa, (R)a.sb, (R)a.rcut, cz + zj * L::NMU * a.ncheb, a.ncheb, f, fp);
+      R rgx = R(0), rgy = R(0), rgz = R(0), ru = R(0);
+      double ur;
+      if constexpr (PARTS) {
+        L::template pair_part<0>(mb, f, fp, dx, dy, dz, rgx, rgy, rgz, ru);
+        ur = ru * rinv;
+      } else {
+        L::template pair_grad<G>(mb, f, fp, (R)dx, (R)dy, (R)dz, rgx, rgy, rgz, ru);
+        ur = (double)ru / r;
+      }
+      const double gx = fma(ur, dx, (double)rgx);
+      const double gy = fma(ur, dy, (double)rgy);
+      const double gz = fma(ur, dz, (double)rgz);
+      // stored after the next pair's loads were issued, so that no wait for a load covers it
+      g[3L * p] = accumulate ? old[0] + gx : gx;
+      g[3L * p + 1] = accumulate ? old[1] + gy : gy;
+      g[3L * p + 2] = accumulate ? old[2] + gz : gz;
+      add_gradient(dx, dy, dz, gx, gy, gz, fo, w);
+    });
+  }
+  finish_gradients<BATCH, K, accumulate>(li < n, i, sub, b, w, fo, wpart, watom, fown);
+  }
+}
+
+// Levels whose adjoints do not fit the 256 registers that two waves per SIMD leave a lane (above
+// 84 entries): the entries stay cut into the parts of the moment kernel, and the NPART waves of a
+// workgroup pass the pairs of the same 64 / K atoms along a pipeline.  The wave of the last
+// (smallest) part forms a pair's geometry and all radial functions, evaluates its own part and
+// leaves displacement, gradient so far and the radial factors of the other parts in an LDS slot;
+// each further wave adds its part one step later, the wave of part 0 stores the gradient and
+// takes the sums.  One barrier per step; a ring of NPART slots keeps the stages apart.  All lanes
+// run the same number of steps (the longest row of the tile); a lane past its row repeats its
+// last pair and its result is dropped.
+// One wave holding all 130 adjoints of level 16 filled a SIMD, read 100 accumulation registers per
+// pair and stood waiting a quarter of its time: 1.27 ms at 1,024,000 atoms with the monomial form and
+// list reads pair by pair, 0.95 with Horner's scheme and staged rows, 0.85 as a pipeline; at level 20
+// (545,505 atoms) 4.7 ms in three passes, 2.4 in two, 1.27 here.  The first stage bounds a step
+// (250 vector instructions against 195 of the second at level 16).
+template <class L>
+struct StageSlots {
+  static constexpr int WIDTH = 3 + L::NMU_SHARED;  // 16-byte fields: (dx, dy) (dz, gx) (gy, gz) (f, h) ...
+  double2 v[L::NPART][WIDTH][kLaneBlock];
+};
+
+// between two steps: this wave's LDS writes are done, then every wave of the workgroup arrives
+__device__ __forceinline__ void step_barrier() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt 0; vector memory operations stay in flight
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
+// First stage (part NPART - 1): T steps.
+template <class L, bool BATCH, int NC, int K>
+__device__ __forceinline__ void gradient_stage_first(const SysArgs& a, const double* csh, ListEntry* lst,
+                                                     StageSlots<L>& slots, int i, int li, int sub, int lane, int p0,
+                                                     int len, int T, const double* __restrict__ mbar, long ld) {
+  constexpr int P = L::NPART - 1, NE = L::PART_SIZE[P];
+  double H[9];
+  cell_of<BATCH>(a, i, H);
+  double mb[NE];
+#pragma unroll
+  for (int e = 0; e < NE; ++e) mb[e] = mbar[(long)L::PART_ENTRY[P][e] * ld + li];
+  const double rix = a.pos[3 * i], riy = a.pos[3 * i + 1], riz = a.pos[3 * i + 2];
+  const int zi = clamp_species(a.species[i], a.nsp);
+  const double* cz = csh + zi * a.nsp * L::NMU * a.ncheb;
+  int slot = 0;
+  auto body = [&](int, int, int zj, double dx, double dy, double dz, double r, double rinv) {
+    double f[L::NMU], h[L::NMU];
+    radial<double, L::NMU, NC>(r, a.sa, a.sb, a.rcut, cz + zj * L::NMU * a.ncheb, a.ncheb, f, h);
+#pragma unroll
+    for (int mu = 0; mu < L::NMU; ++mu) h[mu] *= rinv;
+    double gx = 0.0, gy = 0.0, gz = 0.0, u = 0.0;
+    L::template pair_part<P>(mb, f, h, dx, dy, dz, gx, gy, gz, u);
+    auto& v = slots.v[slot];
+    v[0][lane] = double2{dx, dy};
+    v[1][lane] = double2{dz, fma(u, dx, gx)};
+    v[2][lane] = double2{fma(u, dy, gy), fma(u, dz, gz)};
+#pragma unroll
+    for (int mu = 0; mu < L::NMU_SHARED; ++mu) v[3 + mu][lane] = double2{f[mu], h[mu]};
+    slot = slot + 1 < L::NPART ? slot + 1 : 0;
+    step_barrier();
+  };
+  if constexpr (K == 1) {
+    ListEntry* col = lst + lane;
+    for (int b = 0; b < T; b += kRowStage) {
+      const int m = min(kRowStage, len - b), kn = min(kRowStage, T - b);
+      if (m > 0) stage_row(a, p0 + b, m, col);
+      else col[0] = ListEntry{i, 0};  // a lane past its row
+      const int last = max(m - 1, 0);
+      ListEntry cur = col[0], nxt = col[min(1, last) * kLaneBlock];
+      double xA = a.pos[3 * cur.j], yA = a.pos[3 * cur.j + 1], zA = a.pos[3 * cur.j + 2];
+      int sA = a.species[cur.j];
+      drain_loads();
+      for (int k = 0; k < kn; ++k) {
+        one_pair<double>(
+            a, 0, 0, cur.shift, sA, H, rix, riy, riz, xA, yA, zA,
+            [&]() {
+              cur = nxt;
+              xA = a.pos[3 * cur.j];
+              yA = a.pos[3 * cur.j + 1];
+              zA = a.pos[3 * cur.j + 2];
+              sA = a.species[cur.j];
+              nxt = col[min(k + 2, last) * kLaneBlock];
+            },
+            body);
+      }
+    }
+  } else if (T > 0) {
+    // entry t of the lane; a lane without pairs reads some entry of the (non-empty) list
+    auto at = [&](int t) { return len > 0 ? p0 + min(t, len - 1) * K : 0; };
+    int jA = a.nj[at(0)], shA = a.shift[at(0)];
+    int jB = a.nj[at(1)], shB = a.shift[at(1)];
+    double xA = a.pos[3 * jA], yA = a.pos[3 * jA + 1], zA = a.pos[3 * jA + 2];
+    int sA = a.species[jA];
+    drain_loads();
+    for (int t = 0; t < T; ++t) {
+      one_pair<double>(
+          a, 0, 0, shA, sA, H, rix, riy, riz, xA, yA, zA,
+          [&]() {
+            xA = a.pos[3 * jB];
+            yA = a.pos[3 * jB + 1];
+            zA = a.pos[3 * jB + 2];
+            sA = a.species[jB];
+            shA = shB;
+            jB = a.nj[at(t + 2)];
+            shB = a.shift[at(t + 2)];
+          },
+          body);
+    }
+  }
+#pragma unroll
+  for (int k = 1; k < L::NPART; ++k) step_barrier();
+}
+
+// Stage S > 0 (part NPART - 1 - S).
+template <class L, int S, bool BATCH, int K>
+__device__ __forceinline__ void gradient_stage(StageSlots<L>& slots, bool live, int i, int li, int sub, int lane, int tile,
+                                               int p0, int len, int T, const double* __restrict__ mbar, long ld,
+                                               double* __restrict__ g, double* __restrict__ wpart,
+                                               double* __restrict__ watom, double* __restrict__ fown) {
+  constexpr int P = L::NPART - 1 - S, NE = L::PART_SIZE[P];
+  double mb[NE];
+#pragma unroll
+  for (int e = 0; e < NE; ++e) mb[e] = mbar[(long)L::PART_ENTRY[P][e] * ld + li];
+  double w[6] = {0, 0, 0, 0, 0, 0}, fo[3] = {0, 0, 0};
+#pragma unroll
+  for (int k = 0; k < S; ++k) step_barrier();
+  int slot = 0;
+  for (int t = 0; t < T; ++t) {
+    auto& v = slots.v[slot];
+    const double2 v0 = v[0][lane], v1 = v[1][lane], v2 = v[2][lane];
+    double f[L::NMU_SHARED], h[L::NMU_SHARED];
+#pragma unroll
+    for (int mu = 0; mu < L::NMU_SHARED; ++mu) {
+      const double2 fh = v[3 + mu][lane];
+      f[mu] = fh.x;
+      h[mu] = fh.y;
+    }
+    const double dx = v0.x, dy = v0.y, dz = v1.x;
+    double gx = v1.y, gy = v2.x, gz = v2.y, u = 0.0;
+    L::template pair_part<P>(mb, f, h, dx, dy, dz, gx, gy, gz, u);
+    gx = fma(u, dx, gx);
+    gy = fma(u, dy, gy);
+    gz = fma(u, dz, gz);
+    if constexpr (P > 0) {
+      v[1][lane].y = gx;
+      v[2][lane] = double2{gy, gz};
+    } else if (t < len) {
+      const long p = p0 + t * K;
+      g[3 * p] = gx;
+      g[3 * p + 1] = gy;
+      g[3 * p + 2] = gz;
+      add_gradient(dx, dy, dz, gx, gy, gz, fo, w);
+    }
+    slot = slot + 1 < L::NPART ? slot + 1 : 0;
+    step_barrier();
+  }
+#pragma unroll
+  for (int k = S + 1; k < L::NPART; ++k) step_barrier();
+  if constexpr (P == 0) finish_gradients<BATCH, K, false>(live, i, sub, tile, w, fo, wpart, watom, fown);
+}
+
+template <class L, bool BATCH, int NC, bool PERSIST = false, int K = 1>
+__global__ __launch_bounds__(kLaneBlock * L::NPART) __attribute__((amdgpu_waves_per_eu(2)))
+void k_backward_stages(SysArgs a, int i0, int n, const double* __restrict__ mbar, long ld, double* __restrict__ g,
+                       double* __restrict__ wpart, double* __restrict__ watom, double* __restrict__ fown) {
+  static_assert(K == 1 || !BATCH, "batches take one lane per atom");
+  static_assert(L::NPART <= 4, "pair-gradient stages");
+  __shared__ ListEntry lst[K == 1 ? kRowStage * kLaneBlock : 1];
+  __shared__ StageSlots<L> slots;
+  const double* csh = stage_radial<double>(a);
+  const int lane = (int)threadIdx.x & (kLaneBlock - 1);
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kLaneBlock);
+  MTP_FOR_TILES_K(a, n, K, 1, b) {
+    const int li = b * (kLaneBlock / K) + lane / K, sub = lane % K;
+    const bool live = li < n;
+    const int ls = live ? li : 0;  // lanes past the last atom read the first one's data
+    const int i = sweep_atom<BATCH>(a, i0 + ls);
+    const int p0 = live ? a.off[i] + sub : 0, p1 = live ? a.off[i + 1] : 0;
+    const int len = p1 > p0 ? (p1 - p0 + K - 1) / K : 0;
+    int T = len;  // longest row: the same in every wave
+#pragma unroll
+    for (int s = 32; s > 0; s >>= 1) T = max(T, __shfl_xor(T, s, 64));
+    T = __builtin_amdgcn_readfirstlane(T);
+    // the stages alternate over the workgroup's waves from tile to tile (they differ in work, and
+    // a wave's SIMD follows from its number)
+    const int stage = (wave + b) % L::NPART;
+    if (stage == 0)
+      gradient_stage_first<L, BATCH, NC, K>(a, csh, lst, slots, i, ls, sub, lane, p0, len, T, mbar, ld);
+    else if (stage == 1)
+      gradient_stage<L, 1, BATCH, K>(slots, live, i, ls, sub, lane, b, p0, len, T, mbar, ld, g, wpart, watom, fown);
+    else if (L::NPART > 2 && stage == 2)
+      gradient_stage<L, (L::NPART > 2 ? 2 : 1), BATCH, K>(slots, live, i, ls, sub, lane, b, p0, len, T, mbar, ld, g, wpart,
+                                                          watom, fown);
+    else if (L::NPART > 3)
+      gradient_stage<L, (L::NPART > 3 ? 3 : 1), BATCH, K>(slots, live, i, ls, sub, lane, b, p0, len, T, mbar, ld, g, wpart,
+                                                          watom, fown);
+    if constexpr (PERSIST) __syncthreads();
   }
 }
 
@@ -434,8 +805,8 @@ template <class L, int G, bool PERSIST = false>
 __global__ __launch_bounds__(kLaneBlock) void k_tan_moments(SysArgs a, const double* __restrict__ fbar,
                                                             int i0, int n, double* __restrict__ mdot,
                                                             long ld) {
-  __shared__ double csh[kMaxRadial];
-  stage_radial(a, csh);
+  __shared__ ListEntry lst[kRowStage * kLaneBlock];
+  const double* csh = stage_radial<double>(a);
   MTP_FOR_TILES(a, n, b) {
   const int li = b * kLaneBlock + threadIdx.x;
   if (li >= n) continue;
@@ -449,11 +820,11 @@ __global__ __launch_bounds__(kLaneBlock) void k_tan_moments(SysArgs a, const dou
   const double rix = a.pos[3 * i], riy = a.pos[3 * i + 1], riz = a.pos[3 * i + 2];
   const double fix = fbar[3 * i], fiy = fbar[3 * i + 1], fiz = fbar[3 * i + 2];
   const int zi = clamp_species(a.species[i], a.nsp);
-  for_pairs(a, i, 0, H, rix, riy, riz, [&](int, int j, int zj, double dx, double dy, double dz, double r) {
+  for_pairs(a, lst, i, 0, H, rix, riy, riz, [&](int, int j, int zj, double dx, double dy, double dz, double r, double rinv) {
     double f[L::NMU], fp[L::NMU];
     radial<double, L::NMU>(r, a.sa, a.sb, a.rcut, csh + (zi * a.nsp + zj) * L::NMU * a.ncheb, a.ncheb, f, fp);
     const double ex = fbar[3 * j] - fix, ey = fbar[3 * j + 1] - fiy, ez = fbar[3 * j + 2] - fiz;
-    const double rdot = (dx * ex + dy * ey + dz * ez) / r;
+    const double rdot = (dx * ex + dy * ey + dz * ez) * rinv;
     L::template tan_moments<G>(md, f, fp, dx, dy, dz, ex, ey, ez, rdot);
   });
 #pragma unroll
@@ -516,12 +887,6 @@ __global__ __launch_bounds__(kLaneBlock) void k_tan_reverse(const double* __rest
   }
 }
 
-__device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-  for (int s = 32; s > 0; s >>= 1) v += __shfl_xor(v, s, 64);
-  return v;
-}
-
 // Radial-coefficient gradient: per pair (i, j) with species (s, t),
 //   dc[s][t][mu][b] += Q_b (ebar S_mu - A_mu) - Q'_b (rhat . delta) S_mu,
 // accumulated per lane for one neighbour species at a time (following the per-species pair
@@ -581,9 +946,10 @@ __global__ __launch_bounds__(kLaneBlock) void k_adj_pairs(SysArgs a, const doubl
       double dx, dy, dz;
       pair_displacement(rix, riy, riz, a.pos[3 * j], a.pos[3 * j + 1], a.pos[3 * j + 2], n1, n2,
                         n3, H, dx, dy, dz);
-      const double r = sqrt(dist2_exact(dx, dy, dz));
+      double r, rinv;
+      root_and_inverse(dist2_exact(dx, dy, dz), r, rinv);
       const double ex = fbar[3 * j] - fix, ey = fbar[3 * j + 1] - fiy, ez = fbar[3 * j + 2] - fiz;
-      const double rdot = (dx * ex + dy * ey + dz * ez) / r;
+      const double rdot = (dx * ex + dy * ey + dz * ez) * rinv;
       double S[NMU], A[NMU];
 #pragma unroll
       for (int mu = 0; mu < NMU; ++mu) S[mu] = A[mu] = 0.0;
@@ -646,17 +1012,16 @@ __global__ __launch_bounds__(kLaneBlock) void k_adj_pairs(SysArgs a, const doubl
 // ---------------------------------------------------------------------------- launchers
 // The pair kernels come in Chebyshev-count specialisations for the common sizes 8 and 10 and a
 // runtime-count form for the rest.
-inline int split_tiles(int n, int k) { return (int)(((long)n * k + kLaneBlock - 1) / kLaneBlock); }
-
 template <class L, int G, class R, bool BATCH, bool PERSIST, int K = 1>
 void launch_moments_gp(const SysArgs& a, int i0, int n, void* m, long ld, hipStream_t s) {
-  const int nb = pair_grid(a, split_tiles(n, K));
+  const int nb = pair_grid(a, split_tiles(n, K) * (std::is_same_v<R, double> ? L::NPART : 1));
+  const unsigned sh = radial_bytes<R>(a);
   if (a.ncheb == 8)
-    hipLaunchKernelGGL((k_moments<L, G, R, BATCH, 8, PERSIST, K>), dim3(nb), dim3(kLaneBlock), 0, s, a, i0, n, (R*)m, ld);
+    hipLaunchKernelGGL((k_moments<L, G, R, BATCH, 8, PERSIST, K>), dim3(nb), dim3(kLaneBlock), sh, s, a, i0, n, (R*)m, ld);
   else if (a.ncheb == 10)
-    hipLaunchKernelGGL((k_moments<L, G, R, BATCH, 10, PERSIST, K>), dim3(nb), dim3(kLaneBlock), 0, s, a, i0, n, (R*)m, ld);
+    hipLaunchKernelGGL((k_moments<L, G, R, BATCH, 10, PERSIST, K>), dim3(nb), dim3(kLaneBlock), sh, s, a, i0, n, (R*)m, ld);
   else
-    hipLaunchKernelGGL((k_moments<L, G, R, BATCH, 0, PERSIST, K>), dim3(nb), dim3(kLaneBlock), 0, s, a, i0, n, (R*)m, ld);
+    hipLaunchKernelGGL((k_moments<L, G, R, BATCH, 0, PERSIST, K>), dim3(nb), dim3(kLaneBlock), sh, s, a, i0, n, (R*)m, ld);
 }
 // persistent variants exist for batches only (a single system uses one grid of its tiles);
 // split lanes for single systems in binary64 only
@@ -677,32 +1042,37 @@ void launch_rev_g(const void* m, long ld, int n, const void* cb, void* mb, hipSt
   hipLaunchKernelGGL((k_program_rev<L, G, R>), dim3(nb), dim3(kLaneBlock), 0, s, (const R*)m, ld, n,
                      (const R*)cb, (R*)mb);
 }
-template <class L, int G, class R, bool BATCH, bool PERSIST, int K = 1>
-void launch_backward_gp(const SysArgs& a, int i0, int n, const void* mb, long ld, double* g,
-                        int acc, double* wpart, double* watom, double* fown, hipStream_t s) {
+template <class L, int G, class R, bool BATCH, bool PERSIST, int K, int NC>
+void launch_backward_nc(const SysArgs& a, int i0, int n, const void* mb, long ld, double* g, double* wpart,
+                        double* watom, double* fown, hipStream_t s) {
   const int nb = pair_grid(a, split_tiles(n, K));
-  if (a.ncheb == 8)
-    hipLaunchKernelGGL((k_backward<L, G, R, BATCH, 8, PERSIST, K>), dim3(nb), dim3(kLaneBlock), 0, s, a, i0, n,
-                       (const R*)mb, ld, g, acc, wpart, watom, fown);
-  else if (a.ncheb == 10)
-    hipLaunchKernelGGL((k_backward<L, G, R, BATCH, 10, PERSIST, K>), dim3(nb), dim3(kLaneBlock), 0, s, a, i0, n,
-                       (const R*)mb, ld, g, acc, wpart, watom, fown);
+  const unsigned sh = radial_bytes<R>(a);
+  if constexpr (std::is_same_v<R, double> && L::NPART > 1)
+    hipLaunchKernelGGL((k_backward_stages<L, BATCH, NC, PERSIST, K>), dim3(nb), dim3(kLaneBlock * L::NPART), sh, s, a,
+                       i0, n, (const double*)mb, ld, g, wpart, watom, fown);
   else
-    hipLaunchKernelGGL((k_backward<L, G, R, BATCH, 0, PERSIST, K>), dim3(nb), dim3(kLaneBlock), 0, s, a, i0, n,
-                       (const R*)mb, ld, g, acc, wpart, watom, fown);
+    hipLaunchKernelGGL((k_backward<L, G, R, BATCH, NC, PERSIST, K>), dim3(nb), dim3(kLaneBlock), sh, s, a, i0, n,
+                       (const R*)mb, ld, g, wpart, watom, fown);
+}
+template <class L, int G, class R, bool BATCH, bool PERSIST, int K = 1>
+void launch_backward_gp(const SysArgs& a, int i0, int n, const void* mb, long ld, double* g, double* wpart,
+                        double* watom, double* fown, hipStream_t s) {
+  if (a.ncheb == 8) launch_backward_nc<L, G, R, BATCH, PERSIST, K, 8>(a, i0, n, mb, ld, g, wpart, watom, fown, s);
+  else if (a.ncheb == 10) launch_backward_nc<L, G, R, BATCH, PERSIST, K, 10>(a, i0, n, mb, ld, g, wpart, watom, fown, s);
+  else launch_backward_nc<L, G, R, BATCH, PERSIST, K, 0>(a, i0, n, mb, ld, g, wpart, watom, fown, s);
 }
 // the virial partials: one per workgroup, split_tiles(n, a.split) of them for a single system
 template <class L, int G, class R, bool BATCH>
 void launch_backward_g(const SysArgs& a, int i0, int n, const void* mb, long ld, double* g,
-                       int acc, double* wpart, double* watom, double* fown, hipStream_t s) {
+                       double* wpart, double* watom, double* fown, hipStream_t s) {
   if constexpr (BATCH) {
-    if (a.queue) return launch_backward_gp<L, G, R, BATCH, true>(a, i0, n, mb, ld, g, acc, wpart, watom, fown, s);
+    if (a.queue) return launch_backward_gp<L, G, R, BATCH, true>(a, i0, n, mb, ld, g, wpart, watom, fown, s);
   } else if constexpr (std::is_same_v<R, double>) {
-    if (a.split == 2) return launch_backward_gp<L, G, R, BATCH, false, 2>(a, i0, n, mb, ld, g, acc, wpart, watom, fown, s);
-    if (a.split == 4) return launch_backward_gp<L, G, R, BATCH, false, 4>(a, i0, n, mb, ld, g, acc, wpart, watom, fown, s);
-    if (a.split == 8) return launch_backward_gp<L, G, R, BATCH, false, 8>(a, i0, n, mb, ld, g, acc, wpart, watom, fown, s);
+    if (a.split == 2) return launch_backward_gp<L, G, R, BATCH, false, 2>(a, i0, n, mb, ld, g, wpart, watom, fown, s);
+    if (a.split == 4) return launch_backward_gp<L, G, R, BATCH, false, 4>(a, i0, n, mb, ld, g, wpart, watom, fown, s);
+    if (a.split == 8) return launch_backward_gp<L, G, R, BATCH, false, 8>(a, i0, n, mb, ld, g, wpart, watom, fown, s);
   }
-  launch_backward_gp<L, G, R, BATCH, false>(a, i0, n, mb, ld, g, acc, wpart, watom, fown, s);
+  launch_backward_gp<L, G, R, BATCH, false>(a, i0, n, mb, ld, g, wpart, watom, fown, s);
 }
 
 template <class L, class R, bool BATCH, size_t... Gs>
@@ -717,9 +1087,9 @@ void dispatch_rev(int g, const void* m, long ld, int n, const void* cb, void* mb
 }
 template <class L, class R, bool BATCH, size_t... Gs>
 void dispatch_backward(int g, const SysArgs& a, int i0, int n, const void* mb, long ld,
-                       double* gout, int acc, double* wpart, double* watom, double* fown, hipStream_t s,
+                       double* gout, double* wpart, double* watom, double* fown, hipStream_t s,
                        std::index_sequence<Gs...>) {
-  ((g == (int)Gs ? launch_backward_g<L, (int)Gs, R, BATCH>(a, i0, n, mb, ld, gout, acc, wpart, watom, fown, s)
+  ((g == (int)Gs ? launch_backward_g<L, (int)Gs, R, BATCH>(a, i0, n, mb, ld, gout, wpart, watom, fown, s)
                  : void()),
    ...);
 }
@@ -727,7 +1097,7 @@ void dispatch_backward(int g, const SysArgs& a, int i0, int n, const void* mb, l
 template <class L, class R, bool BATCH>
 struct EnergyChain {
   static void moments(int g, const SysArgs& a, int i0, int n, void* m, long ld, hipStream_t s) {
-    dispatch_moments<L, R, BATCH>(g, a, i0, n, m, ld, s, std::make_index_sequence<L::NGROUP>{});
+    dispatch_moments<L, R, BATCH>(g, a, i0, n, m, ld, s, std::make_index_sequence<nmgroup()>{});
   }
   static void prog_fwd(const void* m, long ld, int i0, int n, const int* perm, const int* species,
                        const double* xi, const double* shift, int nsp, double* e_atom, void* cbar,
@@ -740,10 +1110,14 @@ struct EnergyChain {
     dispatch_rev<L, R>(g, m, ld, n, cb, mb, s, std::make_index_sequence<L::NGROUP>{});
   }
   static void backward(int grp, const SysArgs& a, int i0, int n, const void* mb, long ld, double* gout,
-                       int acc, double* wpart, double* watom, double* fown, hipStream_t s) {
-    dispatch_backward<L, R, BATCH>(grp, a, i0, n, mb, ld, gout, acc, wpart, watom, fown, s,
-                                   std::make_index_sequence<L::NGROUP>{});
+                       double* wpart, double* watom, double* fown, hipStream_t s) {
+    dispatch_backward<L, R, BATCH>(grp, a, i0, n, mb, ld, gout, wpart, watom, fown, s,
+                                   std::make_index_sequence<nbgroup()>{});
   }
+  // launches of the moment kernel (in binary64 one covers all its parts)
+  static constexpr int nmgroup() { return std::is_same_v<R, double> ? 1 : L::NGROUP; }
+  // passes of the pair-gradient kernel over the pairs
+  static constexpr int nbgroup() { return std::is_same_v<R, double> ? 1 : L::NGROUP; }
   static void program(const void* m, long ld, int i0, int n, const int* species, const double* xi,
                       const double* shift, int nsp, double* e_atom, void* mb, hipStream_t s) {
     if constexpr (L::NGROUP == 1) {
@@ -753,7 +1127,8 @@ struct EnergyChain {
     }
   }
   static ChainOps ops() {
-    return ChainOps{&moments, &prog_fwd, &prog_rev, &backward, L::NGROUP == 1 && !BATCH ? &program : nullptr};
+    return ChainOps{&moments, &prog_fwd, &prog_rev, &backward, L::NGROUP == 1 && !BATCH ? &program : nullptr,
+                    nmgroup(), nbgroup()};
   }
 };
 
@@ -764,9 +1139,9 @@ struct AdjImpl {
                             hipStream_t s) {
     const int nb = pair_grid(a, (n + kLaneBlock - 1) / kLaneBlock);
     if (a.queue)
-      hipLaunchKernelGGL((k_tan_moments<L, G, true>), dim3(nb), dim3(kLaneBlock), 0, s, a, fbar, i0, n, md, ld);
+      hipLaunchKernelGGL((k_tan_moments<L, G, true>), dim3(nb), dim3(kLaneBlock), radial_bytes<double>(a), s, a, fbar, i0, n, md, ld);
     else
-      hipLaunchKernelGGL((k_tan_moments<L, G, false>), dim3(nb), dim3(kLaneBlock), 0, s, a, fbar, i0, n, md, ld);
+      hipLaunchKernelGGL((k_tan_moments<L, G, false>), dim3(nb), dim3(kLaneBlock), radial_bytes<double>(a), s, a, fbar, i0, n, md, ld);
   }
   template <size_t... Gs>
   static void tan_moments_d(int g, const SysArgs& a, const double* fbar, int i0, int n, double* md, long ld,
