@@ -65,41 +65,6 @@ def entry_groups(prog: Program, n_groups):
     return [(bounds[k], bounds[k + 1]) for k in range(len(bounds) - 1)]
 
 
-# Most moment entries one adjoint pair group holds: the pair kernel of the parameter adjoint
-# keeps the adjoint and its tangent of every entry of its group in registers, next to the
-# per-lane radial-gradient sums of the group's mu values (64: no spills at levels 16 and 20,
-# one pass fewer than 48 at level 20; 100 spills).
-ADJ_GROUP_CAP = 64
-
-
-def adj_entry_groups(prog: Program, cap=ADJ_GROUP_CAP):
-    """Split the flat moment layout (mu-major) into contiguous ranges of at most cap entries
-    for the adjoint pair kernel: a mu segment longer than cap is cut into equal parts, and
-    consecutive short segments share a range while they fit."""
-    mus = [it[0] for it in prog.layout.items]
-    assert mus == sorted(mus), "the moment layout is mu-major"
-    segs = []
-    for e, mu in enumerate(mus):
-        if segs and segs[-1][2] == mu:
-            segs[-1][1] = e + 1
-        else:
-            segs.append([e, e + 1, mu])
-    out, open_range = [], False  # open_range: the last range holds whole short segments
-    for lo, hi, _ in segs:
-        n = hi - lo
-        if n > cap:
-            k = -(-n // cap)
-            cuts = [lo + round(q * n / k) for q in range(k + 1)]
-            out += [(cuts[q], cuts[q + 1]) for q in range(k)]
-            open_range = False
-        elif open_range and out[-1][1] - out[-1][0] + n <= cap:
-            out[-1] = (out[-1][0], hi)
-        else:
-            out.append((lo, hi))
-            open_range = True
-    return out
-
-
 def _ref(r, mvar="me"):
     kind, k = r
     if kind == "m":
@@ -252,6 +217,15 @@ def part_entries(prog: Program, parts):
     return [[at[it] for it in sorted(at) if it[:2] in part] for part in (set(p) for p in parts)]
 
 
+def _emit_part_tables(w: _W, pre, order):
+    """Number, sizes and entries of parts: N{pre}PART, {pre}PART_SIZE, {pre}PART_ENTRY (-1 past a part's end)."""
+    width = max(len(o) for o in order)
+    rows = ["{" + ", ".join(str(e) for e in o + [-1] * (width - len(o))) + "}" for o in order]
+    w(f"static constexpr int N{pre}PART = {len(order)}, {pre}PART_MAX = {width};")
+    w(f"static constexpr int {pre}PART_SIZE[N{pre}PART] = {{{', '.join(str(len(o)) for o in order)}}};")
+    w(f"static constexpr int {pre}PART_ENTRY[N{pre}PART][{pre}PART_MAX] = {{{', '.join(rows)}}};")
+
+
 def _emit_moment_parts(w: _W, prog: Program, parts):
     """acc_part<P>(m, f, x, y, z): m[k] += f_mu x^a y^b z^c for the entries PART_ENTRY[P][k].  For
     each (mu, a, b) the run over c multiplies the weighted monomial f_mu x^a y^b z^c by z and adds
@@ -261,15 +235,10 @@ def _emit_moment_parts(w: _W, prog: Program, parts):
     for e, (mu, a, b, c) in enumerate(prog.layout.items):
         ents.setdefault((mu, a), {}).setdefault(b, {})[c] = e
     order = part_entries(prog, parts)
-    width = max(len(o) for o in order)
-    w(f"static constexpr int NPART = {len(parts)};")
-    w(f"static constexpr int PART_SIZE[NPART] = {{{', '.join(str(len(o)) for o in order)}}};")
-    w(f"static constexpr int PART_MAX = {width};")
+    _emit_part_tables(w, "", order)
     # radial functions of every part but the last (what the last part's wave hands to the others
     # in the pair-gradient kernel)
     w(f"static constexpr int NMU_SHARED = {max([mu for p in parts[:-1] for mu, _ in p], default=-1) + 1};")
-    rows = ["{" + ", ".join(str(e) for e in o + [-1] * (width - len(o))) + "}" for o in order]
-    w(f"static constexpr int PART_ENTRY[NPART][PART_MAX] = {{{', '.join(rows)}}};")
     for pi, part in enumerate(parts):
         slot = {e: k for k, e in enumerate(order[pi])}
         w("template <class R>")
@@ -326,13 +295,14 @@ def _emit_moment_parts(w: _W, prog: Program, parts):
     w("}")
 
 
-def _emit_horner(w: _W, coef, pre):
+def _emit_horner(w: _W, coef, pre, gradient=True):
     """Value and gradient of sum coef[a, b, c] x^a y^b z^c in {pre}v, {pre}x, {pre}y, {pre}z by
     Horner's scheme nested over x, y and z, each step carrying the derivative (d <- d t + v before
     v <- v t + c).  A coefficient is read once and enters one multiply-add; about two multiply-adds
     per coefficient in all.  Depth first, so that nine partial values are live at most.  Missing
     coefficients are zero; the names of derivatives that vanish are not declared (returned: the
-    names declared, by direction)."""
+    names declared, by direction).  Without gradient only the value (one multiply-add per
+    coefficient)."""
     top = max(a for a, _, _ in coef)
     P = {}
 
@@ -352,7 +322,7 @@ def _emit_horner(w: _W, coef, pre):
         bs = [b for (a2, b, _) in coef if a2 == a]
         M = {}
         if bs:
-            w(f"R {pre}mv{a}, {pre}my{a}, {pre}mz{a};")
+            w(f"R {pre}mv{a}" + (f", {pre}my{a}, {pre}mz{a};" if gradient else ";"))
         for b in range(max(bs) if bs else -1, -1, -1):
             cs = [c for (a2, b2, c) in coef if (a2, b2) == (a, b)]
             I = {}
@@ -361,7 +331,9 @@ def _emit_horner(w: _W, coef, pre):
                 k = coef.get((a, b, c))
                 v = I.get("v")
                 if v is not None:
-                    if "d" in I:
+                    if not gradient:
+                        pass
+                    elif "d" in I:
                         w(f"{pre}id{tag} = fma({pre}id{tag}, z, {v});")
                     else:
                         w(f"R {pre}id{tag} = {v};")
@@ -371,6 +343,8 @@ def _emit_horner(w: _W, coef, pre):
                     I["v"] = f"{pre}iv{tag}"
                     w(f"R {pre}iv{tag} = {k};")
             for key, var, add in (("my", "y", M.get("mv")), ("mv", "y", I.get("v")), ("mz", "y", I.get("d"))):
+                if key != "mv" and not gradient:
+                    continue
                 cur, name = M.get(key), f"{pre}{key}{a}"
                 if cur is None:
                     if add is not None:
@@ -380,10 +354,12 @@ def _emit_horner(w: _W, coef, pre):
                     w(f"{name} = {name} * {var};")
                 else:
                     w(f"{name} = fma({name}, {var}, {add});")
-        step(P, "x", "x", P.get("v"))
+        if gradient:
+            step(P, "x", "x", P.get("v"))
         step(P, "v", "x", M.get("mv"))
-        step(P, "y", "x", M.get("my"))
-        step(P, "z", "x", M.get("mz"))
+        if gradient:
+            step(P, "y", "x", M.get("my"))
+            step(P, "z", "x", M.get("mz"))
     return P
 
 
@@ -699,7 +675,6 @@ def _emit_dispatchers(w: _W, n_groups: int):
 def emit_level(level: int, n_groups: int = 1, rtan_budget: int = RTAN_REG_BUDGET) -> str:
     prog = build_program(level)
     groups = entry_groups(prog, n_groups)
-    agroups = adj_entry_groups(prog)
     w = _W()
     w(f"// Generated MTP level-{level} program.  Do not edit; produced by codegen/emit.py.")
     w("#pragma once")
@@ -715,20 +690,9 @@ def emit_level(level: int, n_groups: int = 1, rtan_budget: int = RTAN_REG_BUDGET
     w(f"static constexpr int TRIPLES = {prog.triple_count()};")
     w("static constexpr int GROUP_LO[NGROUP] = {" + ", ".join(str(g[0]) for g in groups) + "};")
     w("static constexpr int GROUP_HI[NGROUP] = {" + ", ".join(str(g[1]) for g in groups) + "};")
-    # ranges of the adjoint pair kernel and the mu values [AMU_LO, AMU_HI] each one touches
-    w(f"static constexpr int NAGROUP = {len(agroups)};")
-    w("static constexpr int AGROUP_LO[NAGROUP] = {" + ", ".join(str(g[0]) for g in agroups) + "};")
-    w("static constexpr int AGROUP_HI[NAGROUP] = {" + ", ".join(str(g[1]) for g in agroups) + "};")
-    w("static constexpr int AMU_LO[NAGROUP] = {" + ", ".join(str(prog.layout.items[g[0]][0]) for g in agroups) + "};")
-    w("static constexpr int AMU_HI[NAGROUP] = {" + ", ".join(str(prog.layout.items[g[1] - 1][0]) for g in agroups) + "};")
-    # ranges of the moment-tangent kernel
-    tgroups = tangent_moment_groups(groups, agroups, prog.level)
     rparts = rev_tan_parts(prog, rtan_budget)
     # parts of the reverse-tangent program, run in order (one kernel each)
     w(f"static constexpr int NRTPART = {len(rparts)};")
-    w(f"static constexpr int NTGROUP = {len(tgroups)};")
-    w("static constexpr int TGROUP_LO[NTGROUP] = {" + ", ".join(str(g[0]) for g in tgroups) + "};")
-    w("static constexpr int TGROUP_HI[NTGROUP] = {" + ", ".join(str(g[1]) for g in tgroups) + "};")
     w("// flat moment layout: (mu, a, b, c) of component e")
     w("static constexpr int ENTRIES[NMOM][4] = {" + ", ".join("{%d, %d, %d, %d}" % it for it in prog.layout.items) + "};")
     # a! b! c! of each entry: pair_grad takes the moment adjoints scaled by it
@@ -742,7 +706,7 @@ def emit_level(level: int, n_groups: int = 1, rtan_budget: int = RTAN_REG_BUDGET
     _emit_components_reverse(w, prog, groups)
     _emit_products(w, prog)
     _emit_dispatchers(w, len(groups))
-    emit_tangent_parts(w, prog, groups, agroups, rparts)
+    emit_tangent_parts(w, prog, rparts)
     w.pop()
     w("};")
     return w.text()
@@ -774,115 +738,196 @@ def write_level(level: int, out_dir: str, n_groups: int = 1) -> str:
 # every value (forward-over-reverse).
 
 
-def _emit_tangent_pair_functions(w: _W, prog: Program, groups):
-    items = prog.layout.items
-    for gi, (lo, hi) in enumerate(groups):
-        ents = list(range(lo, hi))
-        gnu = max(a + b + c for (_, a, b, c) in (items[e] for e in ents))
-        order = sorted({items[e][1:] for e in ents}, key=lambda t: (t[0] + t[1] + t[2], -t[0], -t[1]))
-        # ---------------- tangent of the moments along delta
+# Most entries one wave of the moment-tangent kernel accumulates (84, as in the moment kernel, spills
+# up to 184 bytes per lane next to the tangents of the running products; 66 gives two parts at
+# level 16 and five at level 20).
+TANGENT_PART_CAP = 66
+
+
+def _emit_tangent_moment_parts(w: _W, prog: Program, parts):
+    """tan_part<P>(md, f, fd, x, y, z, ex, ey, ez): md[k] += the tangent of f_mu x^a y^b z^c along
+    (ex, ey, ez) for the entries TPART_ENTRY[P][k], fd_mu the tangent of f_mu.  Runs as in acc_part,
+    each running product (value, tangent): (w, wd) x = (w x, wd x + w ex)."""
+    ents = {}
+    for e, (mu, a, b, c) in enumerate(prog.layout.items):
+        ents.setdefault((mu, a), {}).setdefault(b, {})[c] = e
+    order = part_entries(prog, parts)
+    _emit_part_tables(w, "T", order)
+
+    def times(dst, src, var):
+        w(f"{dst}d = fma({src}d, {var}, {src} * e{var});")
+        w(f"{dst} = {src} * {var};")
+
+    for pi, part in enumerate(parts):
+        slot = {e: k for k, e in enumerate(order[pi])}
         w("template <class R>")
-        w(f"static __device__ __forceinline__ void tan_moments_g{gi}(R* __restrict__ md, const R* __restrict__ f,")
-        w("    const R* __restrict__ fp, R x, R y, R z, R ex, R ey, R ez, R rdot) {")
+        w(f"static __device__ __forceinline__ void tan_part_p{pi}(R* __restrict__ md, const R* __restrict__ f,")
+        w("    const R* __restrict__ fd, R x, R y, R z, R ex, R ey, R ez) {")
         w.push()
-        _emit_monomials_with_tangent(w, order)
-        by_mono = defaultdict(list)
-        for e in ents:
-            mu, a, b, c = items[e]
-            by_mono[(a, b, c)].append((e, mu))
-        for abc in order:
-            for e, mu in by_mono[abc]:
-                w(f"md[{e - lo}] = fma(f[{mu}], {_tmono_name(abc)}, fma(fp[{mu}] * rdot, {_mono_name(abc)}, md[{e - lo}]));")
+        for mu in sorted({k[0] for k in part}):
+            w(f"{{  // mu = {mu}")
+            w.push()
+            w(f"R wx = f[{mu}], wxd = fd[{mu}];")
+            at = 0
+            for a in sorted(a for m2, a in part if m2 == mu):
+                while at < a:
+                    times("wx", "wx", "x")
+                    at += 1
+                w("{")
+                w.push()
+                w("R wy = wx, wyd = wxd;")
+                for b in sorted(ents[mu, a]):
+                    if b:
+                        times("wy", "wy", "y")
+                    k = [slot[ents[mu, a][b][c]] for c in sorted(ents[mu, a][b])]
+                    w(f"md[{k[0]}] += wyd;")
+                    if len(k) > 1:
+                        w("{")
+                        w.push()
+                        cur = "wy"
+                        if len(k) > 2:
+                            w("R wz, wzd;")
+                            for c in range(1, len(k) - 1):
+                                times("wz", cur, "z")
+                                cur = "wz"
+                                w(f"md[{k[c]}] += wzd;")
+                        w(f"md[{k[-1]}] = fma({cur}d, z, fma({cur}, ez, md[{k[-1]}]));")
+                        w.pop()
+                        w("}")
+                w.pop()
+                w("}")
+            w.pop()
+            w("}")
         w.pop()
         w("}")
+    w("template <int P, class R>")
+    w("static __device__ __forceinline__ void tan_part(R* __restrict__ md, const R* __restrict__ f, const R* __restrict__ fd,")
+    w("    R x, R y, R z, R ex, R ey, R ez) {")
+    w.push()
+    for p in range(len(parts)):
+        w(f"{'if' if p == 0 else 'else if'} constexpr (P == {p}) tan_part_p{p}<R>(md, f, fd, x, y, z, ex, ey, ez);")
+    w.pop()
+    w("}")
 
 
-def _emit_adj_pair_functions(w: _W, prog: Program, agroups):
-    """Per-mu sums of the adjoint pair term over one adjoint group:
-    S_mu = sum_e mb_e mono_e ;  A_mu = sum_e (mbd_e mono_e + mb_e dmono_e)."""
-    items = prog.layout.items
-    for gi, (lo, hi) in enumerate(agroups):
-        ents = list(range(lo, hi))
-        order = sorted({items[e][1:] for e in ents}, key=lambda t: (t[0] + t[1] + t[2], -t[0], -t[1]))
-        by_mono = defaultdict(list)
-        for e in ents:
-            mu, a, b, c = items[e]
-            by_mono[(a, b, c)].append((e, mu))
-        w(f"// adjoint group {gi}: entries [{lo}, {hi})")
+# The adjoint pair pass evaluates, per pair and radial function, S_mu = P_mu (coefficients mb), its
+# derivative along (ex, ey, ez), and V_mu = the polynomial of coefficients ebar mb - mbd.  A slice
+# (mu, a) of a gradient polynomial costs about two multiply-adds per entry, of a value polynomial
+# one; forming a pair's geometry about ADJ_GEOMETRY.
+ADJ_STAGE_CAP = 90     # coefficients a wave holds (two registers each, of 256)
+ADJ_GEOMETRY = 75
+
+
+def adj_stages(prog: Program, cap=ADJ_STAGE_CAP):
+    """The slices (kind, mu, a), kind 0 gradient or 1 value, cut into stages of one wave each: in
+    order, at most cap coefficients per stage, as few stages as the cap allows and the largest cost
+    (the first stage also forms the geometry) as small as the order allows."""
+    size = defaultdict(int)
+    for mu, a, _, _ in prog.layout.items:
+        size[mu, a] += 1
+    seq = []
+    for mu in sorted({k[0] for k in size}, reverse=True):
+        for a in sorted((k[1] for k in size if k[0] == mu), reverse=True):
+            seq += [(0, mu, a), (1, mu, a)]
+
+    def fill(limit):
+        out, regs, cost = [[]], 0, ADJ_GEOMETRY
+        for kind, mu, a in seq:
+            n = size[mu, a]
+            c = n if kind else 2 * n
+            if out[-1] and (regs + n > cap or cost + c > limit):
+                out.append([])
+                regs = cost = 0
+            out[-1].append((kind, mu, a))
+            regs += n
+            cost += c
+        return out
+
+    costs = range(ADJ_GEOMETRY, ADJ_GEOMETRY + 3 * prog.n_mom + 1)
+    fewest = len(fill(costs[-1]))
+    return next(f for f in map(fill, costs) if len(f) == fewest)
+
+
+def _emit_adj_stages(w: _W, prog: Program, stages):
+    """adj_stage<B>(c, x, y, z, ex, ey, ez, S, X): with the coefficients c of stage B (entry
+    ADJ_ENTRY[B][k], ADJ_VALUE[B][k] = 1 for those of a value polynomial), S_mu += P_mu and
+    X_mu += V_mu - (ex, ey, ez) . grad P_mu over its slices."""
+    at = {it: e for e, it in enumerate(prog.layout.items)}
+    lists = []
+    for st in stages:
+        keys = [(kind, it) for kind in (0, 1) for it in sorted(at) if (kind, it[0], it[1]) in set(st)]
+        lists.append(keys)
+    width = max(len(k) for k in lists)
+    w(f"static constexpr int NASTAGE = {len(stages)};")
+    w(f"static constexpr int ADJ_MAX = {width};")
+    w(f"static constexpr int ADJ_SIZE[NASTAGE] = {{{', '.join(str(len(k)) for k in lists)}}};")
+    for name, val in (("ADJ_ENTRY", lambda kind, it: at[it]), ("ADJ_VALUE", lambda kind, it: kind)):
+        rows = ["{" + ", ".join([str(val(*k)) for k in keys] + ["-1"] * (width - len(keys))) + "}" for keys in lists]
+        w(f"static constexpr int {name}[NASTAGE][ADJ_MAX] = {{{', '.join(rows)}}};")
+    for name, fn in (("ADJ_MU_LO", min), ("ADJ_MU_HI", max)):
+        w(f"static constexpr int {name}[NASTAGE] = {{{', '.join(str(fn(k[1] for k in st)) for st in stages)}}};")
+    for bi, keys in enumerate(lists):
         w("template <class R>")
-        w(f"static __device__ __forceinline__ void adj_pair_g{gi}(const R* __restrict__ mb, const R* __restrict__ mbd,")
-        w("    R x, R y, R z, R ex, R ey, R ez, R* __restrict__ S, R* __restrict__ A) {")
+        w(f"static __device__ __forceinline__ void adj_stage_s{bi}(const R* __restrict__ c, R x, R y, R z, R ex, R ey, R ez,")
+        w("    R* __restrict__ S, R* __restrict__ X) {")
         w.push()
-        # ADJ_CHAINS independent partial sums per mu shorten the dependent fma chains
-        mus = sorted({items[e][0] for e in ents})
-        nch = {mu: min(ADJ_CHAINS, sum(1 for e in ents if items[e][0] == mu)) for mu in mus}
-        for mu in mus:
-            w(" ".join(f"R s{mu}_{k} = R(0), a{mu}_{k} = R(0);" for k in range(nch[mu])))
-        _emit_monomials_with_tangent(w, order)
-        seen = defaultdict(int)
-        for abc in order:
-            for e, mu in by_mono[abc]:
-                k = seen[mu] % nch[mu]
-                seen[mu] += 1
-                w(f"s{mu}_{k} = fma(mb[{e - lo}], {_mono_name(abc)}, s{mu}_{k});")
-                w(f"a{mu}_{k} = fma(mbd[{e - lo}], {_mono_name(abc)}, fma(mb[{e - lo}], {_tmono_name(abc)}, a{mu}_{k}));")
-        for mu in mus:
-            w(f"S[{mu}] += " + _pair_sum([f"s{mu}_{k}" for k in range(nch[mu])]) + ";")
-            w(f"A[{mu}] += " + _pair_sum([f"a{mu}_{k}" for k in range(nch[mu])]) + ";")
+        for mu in sorted({it[0] for _, it in keys}):
+            for kind in (0, 1):
+                coef = {it[1:]: f"c[{k}]" for k, (kd, it) in enumerate(keys) if kd == kind and it[0] == mu}
+                if not coef:
+                    continue
+                w("{")
+                w.push()
+                names = _emit_horner(w, coef, "p", gradient=kind == 0)
+                if kind == 0:
+                    w(f"S[{mu}] += {names['v']};")
+                    for d in "xyz":
+                        if d in names:
+                            w(f"X[{mu}] = fma(-e{d}, {names[d]}, X[{mu}]);")
+                else:
+                    w(f"X[{mu}] += {names['v']};")
+                w.pop()
+                w("}")
         w.pop()
         w("}")
+    w("template <int B, class R>")
+    w("static __device__ __forceinline__ void adj_stage(const R* __restrict__ c, R x, R y, R z, R ex, R ey, R ez,")
+    w("    R* __restrict__ S, R* __restrict__ X) {")
+    w.push()
+    for b in range(len(stages)):
+        w(f"{'if' if b == 0 else 'else if'} constexpr (B == {b}) adj_stage_s{b}<R>(c, x, y, z, ex, ey, ez, S, X);")
+    w.pop()
+    w("}")
 
 
-ADJ_CHAINS = 4
-
-
-def _pair_sum(names):
-    """Balanced sum expression of names."""
-    if len(names) == 1:
-        return names[0]
-    h = len(names) // 2
-    return f"({_pair_sum(names[:h])} + {_pair_sum(names[h:])})"
-
-
-def _tmono_name(abc):
-    a, b, c = abc
-    return f"tmono_{a}_{b}_{c}"
-
-
-def _emit_monomials_with_tangent(w, order):
-    """mono = x^a y^b z^c and tmono = grad(mono) . (ex, ey, ez), built by one factor at a time."""
-    have = set()
-    need = set()
-    # close the set downwards along the construction chain
-    for abc in order:
-        a, b, c = abc
-        for k in range(c + 1):
-            need.add((a, b, k))
-        for k in range(b + 1):
-            need.add((a, k, 0))
-        for k in range(a + 1):
-            need.add((k, 0, 0))
-    for abc in sorted(need, key=lambda t: (t[0] + t[1] + t[2], -t[0], -t[1])):
-        a, b, c = abc
-        name, tname = _mono_name(abc), _tmono_name(abc)
-        if a + b + c == 0:
-            w(f"const R {name} = R(1);")
-            w(f"const R {tname} = R(0);")
-            have.add(abc)
-            continue
-        if c > 0:
-            low, var, ev = (a, b, c - 1), "z", "ez"
-        elif b > 0:
-            low, var, ev = (a, b - 1, 0), "y", "ey"
-        else:
-            low, var, ev = (a - 1, 0, 0), "x", "ex"
-        assert low in have
-        w(f"const R {name} = {_mono_name(low)} * {var};")
-        if low == (0, 0, 0):
-            w(f"const R {tname} = {ev};")
-        else:
-            w(f"const R {tname} = fma({_tmono_name(low)}, {var}, {_mono_name(low)} * {ev});")
-        have.add(abc)
+def _emit_whole_tangents(w: _W, prog: Program, parts, stages):
+    """tan_moments<0> and adj_pair<0>: every part of the moment tangent, and every stage of the
+    adjoint pair sums, over the whole layout (one range) with A_mu = sum_e (mbd_e mono_e +
+    mb_e dmono_e) in place of X_mu (ebar = 0)."""
+    w(f"static constexpr int NTGROUP = 1, TGROUP_LO[1] = {{0}}, TGROUP_HI[1] = {{{prog.n_mom}}};")
+    w(f"static constexpr int NAGROUP = 1, AGROUP_LO[1] = {{0}}, AGROUP_HI[1] = {{{prog.n_mom}}};")
+    w("template <int G, class R>")
+    w("static __device__ __forceinline__ void tan_moments(R* __restrict__ md, const R* __restrict__ f, const R* __restrict__ fp,")
+    w("    R x, R y, R z, R ex, R ey, R ez, R rdot) {")
+    w.push()
+    w("R fd[NMU];")
+    w("for (int mu = 0; mu < NMU; ++mu) fd[mu] = fp[mu] * rdot;")
+    for p in range(len(parts)):
+        w(f"{{ R loc[TPART_MAX] = {{}}; tan_part_p{p}<R>(loc, f, fd, x, y, z, ex, ey, ez);")
+        w(f"  for (int k = 0; k < TPART_SIZE[{p}]; ++k) md[TPART_ENTRY[{p}][k]] += loc[k]; }}")
+    w.pop()
+    w("}")
+    w("template <int G, class R>")
+    w("static __device__ __forceinline__ void adj_pair(const R* __restrict__ mb, const R* __restrict__ mbd, R x, R y, R z,")
+    w("    R ex, R ey, R ez, R* __restrict__ S, R* __restrict__ A) {")
+    w.push()
+    w("R X[NMU] = {};")
+    for b in range(len(stages)):
+        w(f"{{ R c[ADJ_MAX]; for (int k = 0; k < ADJ_SIZE[{b}]; ++k) c[k] = ADJ_VALUE[{b}][k] ? -mbd[ADJ_ENTRY[{b}][k]] : mb[ADJ_ENTRY[{b}][k]];")
+        w(f"  adj_stage_s{b}<R>(c, x, y, z, ex, ey, ez, S, X); }}")
+    w("for (int mu = 0; mu < NMU; ++mu) A[mu] -= X[mu];")
+    w.pop()
+    w("}")
 
 
 def _tref(r):
@@ -1174,56 +1219,23 @@ def _emit_products_tangent(w: _W, prog: Program):
     w("}")
 
 
-def _emit_tangent_dispatchers(w: _W, n_rtparts: int, n_agroups: int, n_tgroups: int):
-    sigs = (
-        ("tan_moments", "R* __restrict__ md, const R* __restrict__ f, const R* __restrict__ fp, R x, R y, R z, "
-                        "R ex, R ey, R ez, R rdot", "md, f, fp, x, y, z, ex, ey, ez, rdot", "class R", "<R>"),
-        ("adj_pair", "const R* __restrict__ mb, const R* __restrict__ mbd, R x, R y, R z, R ex, R ey, R ez, "
-                     "R* __restrict__ S, R* __restrict__ A", "mb, mbd, x, y, z, ex, ey, ez, S, A", "class R", "<R>"),
-        ("rev_tan", "const MA& M, const MA& Md, const CB& Cb, const CB& Cbd, "
-                    "const OUT& out, long ld", "M, Md, Cb, Cbd, out, ld", "class R, class MA, class CB, class OUT",
-         "<R, MA, CB>"),
-    )
-    for name, params, args, tparams, targs in sigs:
-        w(f"template <int G, {tparams}>")
-        w(f"static __device__ __forceinline__ void {name}({params}) {{")
-        w.push()
-        count = {"adj_pair": n_agroups, "tan_moments": n_tgroups, "rev_tan": n_rtparts}[name]
-        tag = "p" if name == "rev_tan" else "g"
-        for g in range(count):
-            kw = "if constexpr" if g == 0 else "else if constexpr"
-            w(f"{kw} (G == {g}) {name}_{tag}{g}{targs}({args});")
-        w.pop()
-        w("}")
+def _emit_tangent_dispatchers(w: _W, n_rtparts: int):
+    w("template <int G, class R, class MA, class CB, class OUT>")
+    w("static __device__ __forceinline__ void rev_tan(const MA& M, const MA& Md, const CB& Cb, const CB& Cbd, const OUT& out, long ld) {")
+    w.push()
+    for g in range(n_rtparts):
+        w(f"{'if' if g == 0 else 'else if'} constexpr (G == {g}) rev_tan_p{g}<R, MA, CB>(M, Md, Cb, Cbd, out, ld);")
+    w.pop()
+    w("}")
 
 
-# Extra cuts of the chain's groups for the moment-tangent kernel, by level.  Measured at level
-# 20: the second group (entries 98-196, the higher-order moments) spilled 208 bytes per lane
-# in that kernel and took 2.6 ms of the batch step; cut at entry 148, its two passes take 1.85.
-TANGENT_EXTRA_CUTS = {20: (148,)}
-
-
-def tangent_moment_groups(groups, agroups, level=None):
-    """Ranges of the moment-tangent kernel: the adjoint ranges where the chain has one group
-    (its whole layout does not fit in registers next to the tangent monomials), else the
-    chain's groups (measured faster at level 20 than seven passes over the pairs), cut further
-    at the level's extra cuts."""
-    if len(groups) == 1:
-        return agroups
-    cuts = TANGENT_EXTRA_CUTS.get(level, ())
-    out = []
-    for lo, hi in groups:
-        inner = sorted(c for c in cuts if lo < c < hi)
-        bounds = [lo] + inner + [hi]
-        out += [(bounds[k], bounds[k + 1]) for k in range(len(bounds) - 1)]
-    return out
-
-
-def emit_tangent_parts(w: _W, prog: Program, groups, agroups, rparts):
-    tgroups = tangent_moment_groups(groups, agroups, prog.level)
-    _emit_tangent_pair_functions(w, prog, tgroups)
-    _emit_adj_pair_functions(w, prog, agroups)
+def emit_tangent_parts(w: _W, prog: Program, rparts):
+    stages = adj_stages(prog)
+    parts = moment_parts(prog, TANGENT_PART_CAP)
+    _emit_tangent_moment_parts(w, prog, parts)
+    _emit_adj_stages(w, prog, stages)
+    _emit_whole_tangents(w, prog, parts, stages)
     _emit_components_forward_tangent(w, prog)
     _emit_components_reverse_tangent(w, prog, rparts)
     _emit_products_tangent(w, prog)
-    _emit_tangent_dispatchers(w, len(rparts), len(agroups), len(tgroups))
+    _emit_tangent_dispatchers(w, len(rparts))

@@ -379,8 +379,6 @@ SysArgs make_sys_args(const mtp_model* m, const mtp_system* sys, const mtp_nlist
   a.cfg = nullptr;
   a.perm = nullptr;
   a.ebar = nullptr;
-  a.plink = nullptr;
-  a.pfirst = nullptr;
   a.sa = 2.0 / (m->rcut - m->rmin);
   a.sb = -(m->rmin + m->rcut) / (m->rcut - m->rmin);
   a.rcut = m->rcut;
@@ -396,12 +394,15 @@ SysArgs make_sys_args(const mtp_model* m, const mtp_system* sys, const mtp_nlist
 // Small systems leave SIMDs idle with one lane per atom (a wave per 64 atoms, one wave per
 // SIMD at these register counts): the lanes per atom double while the waves still fit on the
 // SIMDs (4 per compute unit) at once.
+int lanes_for(int ncu, int n) {
+  int k = 1;
+  while (k < 8 && (long)n * 2 * k <= (long)kLaneBlockHost * 4 * ncu) k *= 2;
+  return k;
+}
+
 int pair_split(const mtp_model* m, int n) {
   if (m->precision != MTP_FP64) return 1;
-  if (m->split > 0) return m->split;
-  int k = 1;
-  while (k < 8 && (long)n * 2 * k <= (long)kLaneBlockHost * 4 * m->ncu) k *= 2;
-  return k;
+  return m->split > 0 ? m->split : lanes_for(m->ncu, n);
 }
 
 long pair_blocks(int n, int split) { return ((long)n * split + kLaneBlockHost - 1) / kLaneBlockHost; }
@@ -665,33 +666,26 @@ extern "C" int mtp_param_grad(mtp_model* m, const mtp_system* sys, const mtp_nli
   const int chunk = std::max(1, std::min(m->chunk, n));
   const long ld = chunk;
   const int nchunks = (n + chunk - 1) / chunk;
-  long nblk = 0;
-  for (int i0 = 0; i0 < n; i0 += chunk) nblk += (std::min(chunk, n - i0) + kLaneBlockHost - 1) / kLaneBlockHost;
-  const long nparts = nblk * L.adj.nagroup;
+  // the adjoint runs in binary64 whatever the model's precision
+  const int split = m->split > 0 ? m->split : lanes_for(m->ncu, n);
+  const long nparts = pair_blocks(n, split);
   if ((rc = m->mom.reserve((size_t)L.nmom * ld * 8)) || (rc = m->cbar.reserve((size_t)L.ncomp * ld * 8)) ||
       (rc = m->mbar.reserve((size_t)L.nmom * ld * 8)) || (rc = m->mdot.reserve((size_t)L.nmom * ld * 8)) ||
       (rc = m->cbard.reserve((size_t)L.ncomp * ld * 8)) || (rc = m->mbard.reserve((size_t)L.nmom * ld * 8)) ||
       (rc = m->xout.reserve((size_t)na * ld * 8)) || (rc = m->eatom.reserve((size_t)n * 8)) ||
       (rc = m->dxi_part.reserve((size_t)na * nchunks * 8)) || (rc = m->cpart.reserve((size_t)nparts * K * 8)) ||
+      (rc = m->rec.reserve((size_t)std::max<long long>(use.n_pairs, 1) * L.adj.record * 8)) ||
       (rc = m->rsum.reserve((size_t)std::max<long>(na, K) * kRowParts * 8)))
     return rc;
   SysArgs a = make_sys_args(m, sys, use);
-  if (m->nsp > 1 && use.n_pairs > 0) {
-    // neighbour species per pair, for the per-species passes of the adjoint pair kernel
-    if ((rc = m->plink.reserve((size_t)use.n_pairs * 4)) || (rc = m->pfirst.reserve((size_t)n * m->nsp * 4)))
-      return rc;
-    launch_pair_links(use.off, use.j, sys->species, m->nsp, n, (int*)m->plink.p, (int*)m->pfirst.p, s);
-    a.plink = (const int*)m->plink.p;
-    a.pfirst = (const int*)m->pfirst.p;
-  }
+  a.split = split;
   double *mom = (double*)m->mom.p, *cbar = (double*)m->cbar.p, *mbar = (double*)m->mbar.p;
   double *mdot = (double*)m->mdot.p, *cbard = (double*)m->cbard.p, *mbard = (double*)m->mbard.p;
   double *xout = (double*)m->xout.p, *dxp = (double*)m->dxi_part.p, *cpart = (double*)m->cpart.p;
-  long part = 0;
+  double* rec = (double*)m->rec.p;
   int c = 0;
   for (int i0 = 0; i0 < n; i0 += chunk, ++c) {
     const int cn = std::min(chunk, n - i0);
-    const long cblk = (cn + kLaneBlockHost - 1) / kLaneBlockHost;
     for (int g = 0; g < L.chain[0].nmgroup; ++g) {
       ProfScope ps(&m->prof, P_MOMENTS, s);
       L.chain[0].moments(g, a, i0, cn, mom, ld, s);
@@ -705,9 +699,9 @@ extern "C" int mtp_param_grad(mtp_model* m, const mtp_system* sys, const mtp_nli
       ProfScope ps(&m->prof, P_PROG_REV, s);
       L.chain[0].prog_rev(g, mom, ld, cn, cbar, mbar, s);
     }
-    for (int g = 0; g < L.adj.ntgroup; ++g) {
+    {
       ProfScope ps(&m->prof, P_TANGENT, s);
-      L.adj.tan_moments(g, a, fbar, i0, cn, mdot, ld, s);
+      L.adj.tan_moments(a, fbar, i0, cn, mdot, ld, s);
     }
     {
       ProfScope ps(&m->prof, P_TANGENT, s);
@@ -717,18 +711,21 @@ extern "C" int mtp_param_grad(mtp_model* m, const mtp_system* sys, const mtp_nli
       ProfScope ps(&m->prof, P_TANGENT, s);
       L.adj.tan_reverse[g](mom, mdot, ld, cn, cbar, cbard, mbard, s);
     }
-    for (int g = 0; g < L.adj.nagroup; ++g) {
+    {
       ProfScope ps(&m->prof, P_ADJ_PAIRS, s);
-      L.adj.adj_pairs(g, a, fbar, i0, cn, mbar, mbard, ld, ebar, cpart + part * K, s);
-      part += cblk;
+      L.adj.adj_pairs(a, fbar, i0, cn, mbar, mbard, ld, ebar, rec, s);
     }
     ProfScope ps(&m->prof, P_REDUCE, s);
-    launch_rowsum(xout, ld, 1, cn, na, dxp + c, nchunks, s, (double*)m->rsum.p);
+    launch_rowsum(xout, ld, 1, cn, na, nchunks > 1 ? dxp + c : d_linear, nchunks, s, (double*)m->rsum.p);
+  }
+  {
+    ProfScope ps(&m->prof, P_ADJ_PAIRS, s);
+    L.adj.adj_radial(a, n, rec, cpart, s);
   }
   {
     ProfScope ps(&m->prof, P_REDUCE, s);
-    launch_rowsum(dxp, nchunks, 1, nchunks, na, d_linear, 1, s);
-    launch_rowsum(cpart, 1, K, part, (int)K, d_radial, 1, s, (double*)m->rsum.p);
+    if (nchunks > 1) launch_rowsum(dxp, nchunks, 1, nchunks, na, d_linear, 1, s);
+    launch_rowsum(cpart, 1, K, nparts, (int)K, d_radial, 1, s, (double*)m->rsum.p);
     launch_species_grad(sys->species, n, m->nsp, ebar, d_shift, s);
   }
   HIP_TRY(hipGetLastError());

@@ -60,7 +60,7 @@ struct mtp_model {
   DevBuf nl_off, nl_j, nl_shift, nl_rev;               // internally built neighbour list
   DevBuf mom, cbar, mbar, bvals, g, fown, eatom, wpart;  // per-chunk / per-pair workspace
   DevBuf mdot, cbard, mbard, xout, dxi_part, cpart;   // parameter-adjoint workspace
-  DevBuf plink, pfirst;                                 // per-species pair chains (adjoint)
+  DevBuf rec;                                           // pair records of the adjoint
   DevBuf rsum;                                          // partials of long row sums
   DevBuf scratch;
   DevBuf flag;                                          // status word of the list check
@@ -86,6 +86,8 @@ struct ChainWork {
   int chunk = 1;
   long wblocks = 0;
 };
+// lanes per atom that let n atoms' waves cover the SIMDs of ncu compute units once
+int lanes_for(int ncu, int n);
 // lanes per atom of the binary64 single-system pair kernels for a system of n atoms
 int pair_split(const mtp_model* m, int n);
 // workgroups of a pair kernel over n atoms with `split` lanes per atom (one virial partial each)

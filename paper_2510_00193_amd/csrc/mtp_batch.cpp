@@ -37,8 +37,9 @@ struct mtp_batch {
   const double* pos = nullptr;
   const int* species = nullptr;
   DevBuf atom_off, cfg, cells, cinv, reach, off, nj, shift, rev, perm;
-  DevBuf plink, pfirst;            // per-species pair chains (fixed with the lists)
+  DevBuf rec;                      // pair records of the adjoint
   std::vector<int> h_off;          // host copy of the CSR offsets (neighbour counts)
+  DevBuf perm_sp;                  // atoms by species, then by neighbour count (radial sums of the adjoint)
   // workspace
   DevBuf eatom, watom, g, fown, forces, energy, virial, mom, cbar, mbar, mdot, cbard, mbard, xout, dxi_part,
       cpart, wpart, ebar_cfg, fbar, parts, zeros, rsum;
@@ -80,13 +81,18 @@ static long chunk_of(const mtp_batch* b) {
   return std::max(1, std::min(std::min(b->chunk > 0 ? b->chunk : b->n, b->n), kMaxChunk));
 }
 
+// Lanes per atom: by the batch's size, as for one system (not by the chunk, and the same for every
+// schedule, so that forces do not depend on it).
+static int batch_split(const mtp_batch* b) { return lanes_for(b->m->ncu, b->n); }
+
 // Reserve every buffer the run needs for the current schedule (never called during capture).
 static int reserve_run(mtp_batch* b) {
   const LevelOps& L = b->m->ops;
   const long n = b->n, ld = chunk_of(b);
   const int nchunks = (int)((n + ld - 1) / ld);
+  const int split = batch_split(b);
   long nblk = 0;
-  for (long i0 = 0; i0 < n; i0 += ld) nblk += (std::min(ld, n - i0) + kLaneBlockHost - 1) / kLaneBlockHost;
+  for (long i0 = 0; i0 < n; i0 += ld) nblk += pair_blocks((int)std::min(ld, n - i0), split);
   const long K = b->m->nrad;
   int rc;
   if ((rc = b->eatom.reserve(n * 8)) || (rc = b->watom.reserve(6 * n * 8)) ||
@@ -97,10 +103,11 @@ static int reserve_run(mtp_batch* b) {
       (rc = b->mbar.reserve(L.nmom * ld * 8)) || (rc = b->mdot.reserve(L.nmom * ld * 8)) ||
       (rc = b->cbard.reserve(L.ncomp * ld * 8)) || (rc = b->mbard.reserve(L.nmom * ld * 8)) ||
       (rc = b->xout.reserve(L.nalpha * ld * 8)) || (rc = b->dxi_part.reserve(L.nalpha * nchunks * 8)) ||
-      (rc = b->cpart.reserve(nblk * L.adj.nagroup * K * 8)) || (rc = b->wpart.reserve(nblk * 6 * 8)) ||
+      (rc = b->cpart.reserve(pair_blocks(b->n, split) * K * 8)) ||
+      (rc = b->rec.reserve(std::max<long long>(b->npairs, 1) * L.adj.record * 8)) || (rc = b->wpart.reserve(nblk * 6 * 8)) ||
       (rc = b->ebar_cfg.reserve(b->ncfg * 8)) || (rc = b->fbar.reserve(3 * n * 8)) ||
       (rc = b->parts.reserve((b->ncfg + n) * 8)) ||
-      (rc = b->rsum.reserve(std::max<long>(L.nalpha, K) * kRowParts * 8)))
+      (rc = b->rsum.reserve(std::max<long>(std::max<long>(L.nalpha, K) * kRowParts, kSumParts) * 8)))
     return rc;
   return MTP_OK;
 }
@@ -110,7 +117,22 @@ static long pair_launches(const mtp_batch* b) {
   const LevelOps& L = b->m->ops;
   const long ld = chunk_of(b);
   const long nchunks = ((long)b->n + ld - 1) / ld;
-  return nchunks * (2L * L.chain[2].nmgroup + L.chain[2].nbgroup + L.adj.ntgroup + L.adj.nagroup) + 1;
+  return nchunks * (2L * L.chain[2].nmgroup + L.chain[2].nbgroup + 2) + 1;
+}
+
+// Stable order of the atoms by descending neighbour count, within each species (counting sorts; sp
+// null: one class).
+static std::vector<int> order_by_count(const mtp_batch* b, const int* sp, int nsp) {
+  const std::vector<int>& o = b->h_off;
+  int most = 0;
+  for (int i = 0; i < b->n; ++i) most = std::max(most, o[i + 1] - o[i]);
+  const long rows = (long)most + 1;
+  auto key = [&](int i) { return (sp ? std::min(std::max(sp[i], 0), nsp - 1) : 0) * rows + (most - (o[i + 1] - o[i])); };
+  std::vector<int> at((sp ? nsp : 1) * rows + 1, 0), order(b->n);
+  for (int i = 0; i < b->n; ++i) at[key(i) + 1]++;
+  for (size_t k = 1; k < at.size(); ++k) at[k] += at[k - 1];
+  for (int i = 0; i < b->n; ++i) order[at[key(i)]++] = i;
+  return order;
 }
 
 static int set_schedule(mtp_batch* b, int sorted, int chunk, int persistent) {
@@ -125,13 +147,13 @@ static int set_schedule(mtp_batch* b, int sorted, int chunk, int persistent) {
     int rc = b->queue.reserve((size_t)pair_launches(b) * sizeof(int));
     if (rc) return rc;
   }
-  std::vector<int> perm(b->n);
-  std::iota(perm.begin(), perm.end(), 0);
+  std::vector<int> perm;
   if (b->sorted) {
     // atoms with similar neighbour counts share a wave: less divergence in the pair loops
-    std::stable_sort(perm.begin(), perm.end(), [&](int x, int y) {
-      return b->h_off[x + 1] - b->h_off[x] > b->h_off[y + 1] - b->h_off[y];
-    });
+    perm = order_by_count(b, nullptr, 1);
+  } else {
+    perm.resize(b->n);
+    std::iota(perm.begin(), perm.end(), 0);
   }
   int rc;
   if ((rc = b->perm.reserve((size_t)std::max(b->n, 1) * sizeof(int)))) return rc;
@@ -167,8 +189,6 @@ static void run_impl(mtp_batch* b, const double* e_target, const double* f_targe
   a.cfg = (const int*)b->cfg.p;
   a.perm = (const int*)b->perm.p;
   a.ebar = nullptr;
-  a.plink = b->plink.p ? (const int*)b->plink.p : nullptr;
-  a.pfirst = b->pfirst.p ? (const int*)b->pfirst.p : nullptr;
   a.sa = 2.0 / (m->rcut - m->rmin);
   a.sb = -(m->rmin + m->rcut) / (m->rcut - m->rmin);
   a.rcut = m->rcut;
@@ -177,7 +197,7 @@ static void run_impl(mtp_batch* b, const double* e_target, const double* f_targe
   a.ncheb = m->ncheb;
   a.queue = nullptr;
   a.pgrid = b->pgrid;
-  a.split = 1;
+  a.split = batch_split(b);
   // persistent schedule: one zeroed tile counter per pair-kernel launch (a kernel, not a memset,
   // so that the sequence can be captured into a graph)
   int* qbase = b->persistent ? (int*)b->queue.p : nullptr;
@@ -211,7 +231,7 @@ static void run_impl(mtp_batch* b, const double* e_target, const double* f_targe
       a.queue = q();
       K.backward(gi, a, (int)i0, cn, b->mbar.p, ld, g, wpart + 6 * blk, wa, (double*)b->fown.p, s);
     }
-    blk += (cn + kLaneBlockHost - 1) / kLaneBlockHost;
+    blk += pair_blocks(cn, a.split);
   }
   double* F = forces ? forces : (double*)b->forces.p;
   double* E = energy ? energy : (double*)b->energy.p;
@@ -235,7 +255,11 @@ static void run_impl(mtp_batch* b, const double* e_target, const double* f_targe
     double* parts = (double*)b->parts.p;
     ProfScope ps(&m->prof, P_REDUCE, s);
     launch_loss(E, e_target, b->ncfg, F, f_target, n, eb, fb, parts, parts + b->ncfg, s);
-    if (loss) launch_sum(parts, (long)b->ncfg + n, 1, loss, s);
+    // one workgroup up to kSmallSumMax terms (a launch less), else two levels (0.13 ms in one
+    // workgroup at 550,000 terms)
+    const long terms = (long)b->ncfg + n;
+    if (loss && terms <= kSmallSumMax) launch_sum(parts, terms, 1, loss, s);
+    else if (loss) launch_sum_parts(parts, terms, 1, 1, (double*)b->rsum.p, loss, s);
     ebar = eb;
     fbar = fb;
   }
@@ -244,11 +268,10 @@ static void run_impl(mtp_batch* b, const double* e_target, const double* f_targe
   const int nchunks = (int)((n + ld - 1) / ld);
   double* dxp = (double*)b->dxi_part.p;
   double* cpart = (double*)b->cpart.p;
-  long part = 0;
+  double* rec = (double*)b->rec.p;
   int c = 0;
   for (long i0 = 0; i0 < n; i0 += ld, ++c) {
     const int cn = (int)std::min(ld, (long)n - i0);
-    const long cblk = (cn + kLaneBlockHost - 1) / kLaneBlockHost;
     if (ld < n) {  // the forward state of this chunk was overwritten by later chunks
       for (int gi = 0; gi < K.nmgroup; ++gi) {
         ProfScope ps(&m->prof, P_MOMENTS, s);
@@ -265,10 +288,10 @@ static void run_impl(mtp_batch* b, const double* e_target, const double* f_targe
       ProfScope ps(&m->prof, P_PROG_REV, s);
       K.prog_rev(gi, b->mom.p, ld, cn, b->cbar.p, b->mbar.p, s);
     }
-    for (int gi = 0; gi < L.adj.ntgroup; ++gi) {
+    {
       ProfScope ps(&m->prof, P_TANGENT, s);
       a.queue = q();
-      L.adj.tan_moments(gi, a, fbar, (int)i0, cn, (double*)b->mdot.p, ld, s);
+      L.adj.tan_moments(a, fbar, (int)i0, cn, (double*)b->mdot.p, ld, s);
     }
     {
       ProfScope ps(&m->prof, P_TANGENT, s);
@@ -280,19 +303,23 @@ static void run_impl(mtp_batch* b, const double* e_target, const double* f_targe
       L.adj.tan_reverse[gi]((const double*)b->mom.p, (const double*)b->mdot.p, ld, cn, (const double*)b->cbar.p,
                     (const double*)b->cbard.p, (double*)b->mbard.p, s);
     }
-    for (int gi = 0; gi < L.adj.nagroup; ++gi) {
+    {
       ProfScope ps(&m->prof, P_ADJ_PAIRS, s);
       a.queue = q();
-      L.adj.adj_pairs(gi, a, fbar, (int)i0, cn, (const double*)b->mbar.p, (const double*)b->mbard.p, ld, 0.0,
-                  cpart + part * KR, s);
-      part += cblk;
+      L.adj.adj_pairs(a, fbar, (int)i0, cn, (const double*)b->mbar.p, (const double*)b->mbard.p, ld, 0.0, rec, s);
     }
     ProfScope ps(&m->prof, P_REDUCE, s);
-    launch_rowsum((const double*)b->xout.p, ld, 1, cn, L.nalpha, dxp + c, nchunks, s, (double*)b->rsum.p);
+    launch_rowsum((const double*)b->xout.p, ld, 1, cn, L.nalpha,
+                  nchunks > 1 ? dxp + c : d_linear, nchunks, s, (double*)b->rsum.p);
+  }
+  {
+    ProfScope ps(&m->prof, P_ADJ_PAIRS, s);
+    a.perm = (const int*)b->perm_sp.p;
+    L.adj.adj_radial(a, n, rec, cpart, s);
   }
   ProfScope ps(&m->prof, P_REDUCE, s);
-  launch_rowsum(dxp, nchunks, 1, nchunks, L.nalpha, d_linear, 1, s);
-  launch_rowsum(cpart, 1, KR, part, (int)KR, d_radial, 1, s, (double*)b->rsum.p);
+  if (nchunks > 1) launch_rowsum(dxp, nchunks, 1, nchunks, L.nalpha, d_linear, 1, s);
+  launch_rowsum(cpart, 1, KR, pair_blocks(n, a.split), (int)KR, d_radial, 1, s, (double*)b->rsum.p);
   launch_species_grad_cfg(b->species, (const int*)b->cfg.p, ebar, n, m->nsp, d_shift, (double*)b->rsum.p, s);
 }
 
@@ -367,17 +394,27 @@ int mtp_batch_create(mtp_model* m, int n_cfg, const int* atom_off, const double*
                                : mtp_fail(MTP_ERR_CELL, "an image shift does not fit in int8");
   }
   b->npairs = total;
-  if (m->nsp > 1 && total > 0) {
-    if ((rc = b->plink.reserve((size_t)total * 4)) || (rc = b->pfirst.reserve((size_t)n * m->nsp * 4))) {
-      delete b;
-      return mtp_fail(rc, "allocating the pair species chains failed");
-    }
-    launch_pair_links((const int*)b->off.p, nj, species, m->nsp, (int)n, (int*)b->plink.p, (int*)b->pfirst.p, s);
-  }
   b->h_off.resize(n + 1);
   if (hipMemcpy(b->h_off.data(), b->off.p, (n + 1) * sizeof(int), hipMemcpyDeviceToHost) != hipSuccess) {
     delete b;
     return mtp_fail(MTP_ERR_HIP, "reading neighbour offsets failed");
+  }
+  if (n > 0) {
+    // one centre species per wave: its sums need no selection by species (and rows of similar length)
+    std::vector<int> sp(n);
+    if (hipMemcpy(sp.data(), species, n * sizeof(int), hipMemcpyDeviceToHost) != hipSuccess) {
+      delete b;
+      return mtp_fail(MTP_ERR_HIP, "reading species failed");
+    }
+    const std::vector<int> order = order_by_count(b, sp.data(), m->nsp);
+    if ((rc = b->perm_sp.reserve(n * sizeof(int)))) {
+      delete b;
+      return rc;
+    }
+    if (hipMemcpy(b->perm_sp.p, order.data(), n * sizeof(int), hipMemcpyHostToDevice) != hipSuccess) {
+      delete b;
+      return mtp_fail(MTP_ERR_HIP, "copying the species order failed");
+    }
   }
   if ((rc = set_schedule(b, 0, 0, 0))) {
     delete b;

@@ -164,14 +164,24 @@ __global__ __launch_bounds__(kNT) void k_rowsum_part(const double* __restrict__ 
 }
 
 // d(ebar E + fbar.F)/ds_t = ebar * (number of atoms of species t); integer counts are exact
-__global__ __launch_bounds__(kNT) void k_species_grad(const int* __restrict__ species, int n, int nsp,
-                                                      double ebar, double* __restrict__ out) {
-  __shared__ int cnt[16];
-  if (threadIdx.x < 16) cnt[threadIdx.x] = 0;
+// One workgroup; a thread counts its atoms per species in registers (an LDS counter per species and
+// 256 threads took 18 us at 16,000 atoms, this 4).
+__global__ __launch_bounds__(kSumThreads) void k_species_grad(const int* __restrict__ species, int n, int nsp,
+                                                              double ebar, double* __restrict__ out) {
+  __shared__ int cnt[kMaxSpecies];
+  if (threadIdx.x < kMaxSpecies) cnt[threadIdx.x] = 0;
   __syncthreads();
-  for (int i = threadIdx.x; i < n; i += kNT) {
+  int c[kMaxSpecies] = {0};
+#pragma unroll 4
+  for (int i = threadIdx.x; i < n; i += kSumThreads) {
     const int z = species[i];
-    if (z >= 0 && z < nsp) atomicAdd(&cnt[z], 1);
+#pragma unroll
+    for (int t = 0; t < kMaxSpecies; ++t) c[t] += z == t;
+  }
+#pragma unroll
+  for (int t = 0; t < kMaxSpecies; ++t) {
+    for (int s = 32; s > 0; s >>= 1) c[t] += __shfl_xor(c[t], s, 64);
+    if ((threadIdx.x & 63) == 0 && c[t]) atomicAdd(&cnt[t], c[t]);
   }
   __syncthreads();
   if (threadIdx.x < nsp) out[threadIdx.x] = ebar * (double)cnt[threadIdx.x];
@@ -229,33 +239,6 @@ __global__ __launch_bounds__(kNT) void k_species_grad_cfg(const int* __restrict_
     if (species[i] == t) acc += ebar[cfg[i]];
   const double v = block_sum<kNT>(acc, sh);
   if (threadIdx.x == 0) part[t * kRowParts + blockIdx.x] = v;
-}
-
-// Per-species chains through each CSR row: pfirst[i][t] is the first pair of atom i whose
-// neighbour has species t and plink[p] the next pair of the same row and neighbour species
-// (-1 ends a chain). One lane per atom walks its row backwards.
-__global__ void k_pair_links(const int* __restrict__ off, const int* __restrict__ nj,
-                             const int* __restrict__ species, int nsp, int n, int* __restrict__ plink,
-                             int* __restrict__ pfirst) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  int last[kMaxSpecies];
-#pragma unroll
-  for (int t = 0; t < kMaxSpecies; ++t) last[t] = -1;
-  for (int q = off[i + 1] - 1; q >= off[i]; --q) {
-    const int z = clamp_species(species[nj[q]], nsp);
-    int nxt = -1;
-#pragma unroll
-    for (int t = 0; t < kMaxSpecies; ++t)
-      if (t == z) {
-        nxt = last[t];
-        last[t] = q;
-      }
-    plink[q] = nxt;
-  }
-#pragma unroll
-  for (int t = 0; t < kMaxSpecies; ++t)
-    if (t < nsp) pfirst[(long)i * nsp + t] = last[t];
 }
 
 // Consistency of a caller-supplied CSR list, one lane per atom; any failure sets *bad.
@@ -330,13 +313,6 @@ void launch_check_nlist(const int* off, const int* nj, const int* shift, const i
                      npairs, nsp, bad);
 }
 
-void launch_pair_links(const int* off, const int* nj, const int* species, int nsp, int n, int* plink,
-                       int* pfirst, hipStream_t s) {
-  if (n <= 0) return;
-  hipLaunchKernelGGL(k_pair_links, dim3((n + kNT - 1) / kNT), dim3(kNT), 0, s, off, nj, species, nsp, n, plink,
-                     pfirst);
-}
-
 void launch_segsum(const double* x, long stride, const int* seg_off, int nseg, int ncomp, double* out,
                    long os, hipStream_t s) {
   if (nseg <= 0) return;
@@ -370,7 +346,7 @@ void launch_rowsum(const double* x, long rs, long es, long n, int rows, double* 
 }
 
 void launch_species_grad(const int* species, int n, int nsp, double ebar, double* out, hipStream_t s) {
-  hipLaunchKernelGGL(k_species_grad, dim3(1), dim3(kNT), 0, s, species, n, nsp, ebar, out);
+  hipLaunchKernelGGL(k_species_grad, dim3(1), dim3(kSumThreads), 0, s, species, n, nsp, ebar, out);
 }
 
 void launch_gather_forces(const int* off, const int* rev, const double* g, const double* fown, int n,

@@ -25,9 +25,6 @@ struct SysArgs {
   const int* cfg;         // [N] configuration of each atom (batches), or null
   const int* perm;        // [N] processing order: lane k of the sweep takes atom perm[k], or null
   const double* ebar;     // [n_cfg] per-configuration energy cotangent (batches), or null
-  // per-species chains through the rows (launch_pair_links), or null for one species
-  const int* plink;       // [P] next pair of the same row and neighbour species, -1 at the end
-  const int* pfirst;      // [N][nsp] first pair of each neighbour species, -1 if none
   double sa, sb, rcut;    // u = sa r + sb
   int nsp, nmu, ncheb;
   // persistent launches of the pair kernels: a device counter from which workgroups pull their
@@ -35,7 +32,7 @@ struct SysArgs {
   // one workgroup per tile
   int* queue;
   int pgrid;
-  // lanes per atom of the single-system pair kernels (1, 2, 4 or 8): with more than one, the
+  // lanes per atom of the pair kernels (1, 2, 4 or 8): with more than one, the
   // lanes of an atom take every split-th pair of its row and combine their sums
   int split;
 };
@@ -62,8 +59,7 @@ struct ChainOps {
 
 // Parameter-adjoint launchers of one level (binary64).
 struct AdjOps {
-  void (*tan_moments)(int grp, const SysArgs& a, const double* fbar, int i0, int n, double* md,
-                      long ld, hipStream_t s);
+  void (*tan_moments)(const SysArgs& a, const double* fbar, int i0, int n, double* md, long ld, hipStream_t s);
   void (*tan_forward)(const SysArgs& a, const double* m, const double* md, long ld, int i0, int n,
                       const double* xi, double ebar, double* out, double* cbard, hipStream_t s);
   // one launcher per part of the reverse-tangent program (compiled in separate units); the
@@ -71,12 +67,12 @@ struct AdjOps {
   void (*tan_reverse[kMaxRevParts])(const double* m, const double* md, long ld, int n, const double* cb,
                                     const double* cbd, double* mbd, hipStream_t s);
   int nrtpart;
-  // grp is one of the nagroup adjoint groups (moment ranges sized for the pair kernel's
-  // registers, independent of the chain's groups)
-  void (*adj_pairs)(int grp, const SysArgs& a, const double* fbar, int i0, int n, const double* mb,
-                    const double* mbd, long ld, double ebar, double* cpart, hipStream_t s);
-  int nagroup;
-  int ntgroup;  // moment ranges of tan_moments (the adjoint ranges or the chain's groups)
+  // adj_pairs leaves a record of `record` doubles per pair (indexed by the list), adj_radial sums the
+  // records of atoms 0 .. n - 1 into cpart [split_tiles(n, a.split)][nsp * nsp * nmu * ncheb]
+  void (*adj_pairs)(const SysArgs& a, const double* fbar, int i0, int n, const double* mb, const double* mbd,
+                    long ld, double ebar, double* rec, hipStream_t s);
+  void (*adj_radial)(const SysArgs& a, int n, const double* rec, double* cpart, hipStream_t s);
+  int record;
 };
 
 // Launchers of one compiled level (assembled from the level's translation units).
@@ -160,13 +156,10 @@ void launch_species_grad_cfg(const int* species, const int* cfg, const double* e
 void launch_grade(const double* B, long ld, int n, const double* ainv, int na, int split,
                   double* grade, hipStream_t s);
 void launch_max(const double* x, long n, double* out, hipStream_t s);
-// zp[p] = species of neighbour nj[p], clamped to [0, nsp)
 // *bad |= 1 when the CSR list (off, nj, shift, rev) of n atoms and npairs pairs is inconsistent
 // or a species lies outside [0, nsp) (*bad is not cleared here)
 void launch_check_nlist(const int* off, const int* nj, const int* shift, const int* rev, const int* species,
                         int n, long long npairs, int nsp, int* bad, hipStream_t s);
-void launch_pair_links(const int* off, const int* nj, const int* species, int nsp, int n, int* plink,
-                       int* pfirst, hipStream_t s);
 // out[0] = max_k |(b . ainv)_k| for one descriptor b [na]
 void launch_cfg_grade(const double* b, const double* ainv, int na, double* out, hipStream_t s);
 

@@ -86,7 +86,7 @@ __device__ __forceinline__ double wave_sum(double v) {
   return v;
 }
 
-inline int pair_grid(const SysArgs& a, int nb) { return a.queue ? std::max(1, std::min(nb, a.pgrid)) : nb; }
+inline int pair_grid(const SysArgs& a, int nb) { return a.queue && a.split == 1 ? std::max(1, std::min(nb, a.pgrid)) : nb; }
 
 // Accessors of [row][atom] arrays in global memory.  The address of a row is the same for the
 // whole wave (scalar registers) and each lane adds its byte offset, so a load takes the
@@ -219,29 +219,58 @@ __device__ __forceinline__ void stage_row(const SysArgs& a, int p, int m, ListEn
     if (k < m) col[k * kLaneBlock] = e[k];
 }
 
-// Displacement, then prefetch() (the next pair's loads, into the registers this pair's position just
-// left: no copies, which would wait for the loads), then distance and the body (see for_pairs).  The
-// barriers keep the scheduler from moving the loads.
-template <class R, class P, class F>
-__device__ __forceinline__ void one_pair(const SysArgs& a, int p, int j, int sh, int sj, const double* H, double rix,
-                                         double riy, double riz, double xj, double yj, double zj, P&& prefetch,
-                                         F&& body) {
+// Position and species of a pair's partner, and with TAN its force cotangent.
+template <bool TAN>
+struct Partner {
+  double x, y, z, bx, by, bz;
+  int s;
+  __device__ __forceinline__ void load(const SysArgs& a, const double* __restrict__ fbar, int j) {
+    x = a.pos[3 * j];
+    y = a.pos[3 * j + 1];
+    z = a.pos[3 * j + 2];
+    s = a.species[j];
+    if constexpr (TAN) {
+      bx = fbar[3 * j];
+      by = fbar[3 * j + 1];
+      bz = fbar[3 * j + 2];
+    }
+  }
+};
+
+// One pair as the bodies of the pair loops see it: species of the partner, displacement, distance and
+// its inverse, and with TAN the difference of the force cotangents (partner minus centre).
+struct Pair {
+  int zj;
+  double dx, dy, dz, r, rinv, ex, ey, ez;
+};
+
+// Displacement, then prefetch() (the next pair's loads, into the registers this pair's partner just
+// left: no copies, which would wait for the loads), then distance and body(p, pair).  own: the centre
+// atom.  The barriers keep the scheduler from moving the loads.  R is the arithmetic type of the
+// kernel (binary32 kernels round the correctly rounded r).
+template <class R, bool TAN, class P, class F>
+__device__ __forceinline__ void one_pair(const SysArgs& a, int p, int sh, const double* H, const Partner<TAN>& own,
+                                         const Partner<TAN>& q, P&& prefetch, F&& body) {
+  Pair t;
   int n1, n2, n3;
   unpack_shift(sh, n1, n2, n3);
-  double dx, dy, dz;
-  pair_displacement(rix, riy, riz, xj, yj, zj, n1, n2, n3, H, dx, dy, dz);
-  const int zj_ = clamp_species(sj, a.nsp);
+  pair_displacement(own.x, own.y, own.z, q.x, q.y, q.z, n1, n2, n3, H, t.dx, t.dy, t.dz);
+  if constexpr (TAN) {
+    t.ex = q.bx - own.bx;
+    t.ey = q.by - own.by;
+    t.ez = q.bz - own.bz;
+  }
+  t.zj = clamp_species(q.s, a.nsp);
   __builtin_amdgcn_sched_barrier(0);
   prefetch();
   __builtin_amdgcn_sched_barrier(0);
-  double r, rinv;
   if constexpr (std::is_same_v<R, double>) {
-    root_and_inverse(dist2_exact(dx, dy, dz), r, rinv);
+    root_and_inverse(dist2_exact(t.dx, t.dy, t.dz), t.r, t.rinv);
   } else {
-    r = sqrt(dist2_exact(dx, dy, dz));
-    rinv = 0.0;  // not used
+    t.r = sqrt(dist2_exact(t.dx, t.dy, t.dz));
+    t.rinv = 0.0;  // not used
   }
-  body(p, j, zj_, dx, dy, dz, r, rinv);
+  body(p, t);
 }
 
 // Wait for every outstanding vector memory operation (vmcnt 0; the other counters at their
@@ -249,38 +278,33 @@ __device__ __forceinline__ void one_pair(const SysArgs& a, int p, int j, int sh,
 // operations alone, not for the path that enters it.
 __device__ __forceinline__ void drain_loads() { __builtin_amdgcn_s_waitcnt(0x0F70); }
 
-// Walk the CSR row of atom i with software prefetch: the partner position and species are loaded
-// one pair ahead, so the gather latency overlaps the arithmetic of the current pair.  The prefetch
-// index is clamped to the row instead of guarded: a loop body without branches around its memory
-// operations lets the waits count them exactly, so the wait for a pair's loads does not also wait
-// for younger stores (guarded loads and stores make every wait a full drain).
-// body(p, j, zj, dx, dy, dz, r, rinv) sees the exact displacement; R is the arithmetic type of the
-// kernel (binary32 kernels round the correctly rounded r).
+// Walk the CSR row of atom i with software prefetch: the partner's data are loaded one pair ahead,
+// so the gather latency overlaps the arithmetic of the current pair.  The prefetch index is clamped
+// to the row instead of guarded: a loop body without branches around its memory operations lets the
+// waits count them exactly, so the wait for a pair's loads does not also wait for younger stores
+// (guarded loads and stores make every wait a full drain).
 // With K lanes per atom, lane sub of the atom takes pairs sub, sub + K, sub + 2K, ... of the row
 // (the lanes of an atom read consecutive list entries); with one, lst is the wave's LDS stage.
-template <int K = 1, class R = double, class F>
+template <int K, class R, bool TAN, class F>
 __device__ __forceinline__ void for_pairs(const SysArgs& a, ListEntry* lst, int i, int sub, const double* H,
-                                          double rix, double riy, double riz, F&& body) {
+                                          const Partner<TAN>& own, const double* __restrict__ fbar, F&& body) {
   const int p0 = a.off[i] + sub, p1 = a.off[i + 1];
+  Partner<TAN> q;
   if constexpr (K == 1) {
     ListEntry* col = lst + (threadIdx.x & (kLaneBlock - 1));
     for (int b = p0; b < p1; b += kRowStage) {
       const int m = min(kRowStage, p1 - b);
       stage_row(a, b, m, col);
       ListEntry cur = col[0], nxt = col[(m > 1) * kLaneBlock];
-      double xA = a.pos[3 * cur.j], yA = a.pos[3 * cur.j + 1], zA = a.pos[3 * cur.j + 2];
-      int sA = a.species[cur.j];
+      q.load(a, fbar, cur.j);
       int k = 0;
       drain_loads();
       do {
-        one_pair<R>(
-            a, b + k, cur.j, cur.shift, sA, H, rix, riy, riz, xA, yA, zA,
+        one_pair<R, TAN>(
+            a, b + k, cur.shift, H, own, q,
             [&]() {
               cur = nxt;
-              xA = a.pos[3 * cur.j];
-              yA = a.pos[3 * cur.j + 1];
-              zA = a.pos[3 * cur.j + 2];
-              sA = a.species[cur.j];
+              q.load(a, fbar, cur.j);
               nxt = col[min(k + 2, m - 1) * kLaneBlock];
             },
             body);
@@ -289,22 +313,16 @@ __device__ __forceinline__ void for_pairs(const SysArgs& a, ListEntry* lst, int 
     }
   } else {
     if (p0 >= p1) return;
-    int jA = a.nj[p0], shA = a.shift[p0];
     const int pB = min(p0 + K, p1 - 1);
-    int jB = a.nj[pB], shB = a.shift[pB];
-    double xA = a.pos[3 * jA], yA = a.pos[3 * jA + 1], zA = a.pos[3 * jA + 2];
-    int sA = a.species[jA];
+    int jA = a.nj[p0], shA = a.shift[p0], jB = a.nj[pB], shB = a.shift[pB];
+    q.load(a, fbar, jA);
     int p = p0;
     drain_loads();
     do {
-      one_pair<R>(
-          a, p, jA, shA, sA, H, rix, riy, riz, xA, yA, zA,
+      one_pair<R, TAN>(
+          a, p, shA, H, own, q,
           [&]() {
-            xA = a.pos[3 * jB];
-            yA = a.pos[3 * jB + 1];
-            zA = a.pos[3 * jB + 2];
-            sA = a.species[jB];
-            jA = jB;
+            q.load(a, fbar, jB);
             shA = shB;
             const int pn = min(p + 2 * K, p1 - 1);
             jB = a.nj[pn];
@@ -314,6 +332,67 @@ __device__ __forceinline__ void for_pairs(const SysArgs& a, ListEntry* lst, int 
       p += K;
     } while (p < p1);
   }
+}
+
+// The same with T steps in every lane, for the first wave of a pipeline of waves: a lane past its len
+// pairs repeats the last one, a lane without pairs takes atom i itself (its results are dropped).
+template <int K, bool TAN, class F>
+__device__ __forceinline__ void for_steps(const SysArgs& a, ListEntry* lst, int i, int lane, int p0, int len, int T,
+                                          const double* H, const Partner<TAN>& own, const double* __restrict__ fbar,
+                                          F&& body) {
+  Partner<TAN> q;
+  if constexpr (K == 1) {
+    ListEntry* col = lst + lane;
+    for (int b = 0; b < T; b += kRowStage) {
+      const int m = min(kRowStage, len - b), kn = min(kRowStage, T - b);
+      if (m > 0) stage_row(a, p0 + b, m, col);
+      else col[0] = ListEntry{i, 0};  // a lane past its row
+      const int last = max(m - 1, 0);
+      ListEntry cur = col[0], nxt = col[min(1, last) * kLaneBlock];
+      q.load(a, fbar, cur.j);
+      drain_loads();
+      for (int k = 0; k < kn; ++k) {
+        one_pair<double, TAN>(
+            a, b + k, cur.shift, H, own, q,
+            [&]() {
+              cur = nxt;
+              q.load(a, fbar, cur.j);
+              nxt = col[min(k + 2, last) * kLaneBlock];
+            },
+            body);
+      }
+    }
+  } else if (T > 0) {
+    // entry t of the lane; a lane without pairs reads the first entry of the (non-empty) list
+    auto at = [&](int t) { return len > 0 ? p0 + min(t, len - 1) * K : 0; };
+    int jA = a.nj[at(0)], shA = a.shift[at(0)], jB = a.nj[at(1)], shB = a.shift[at(1)];
+    q.load(a, fbar, jA);
+    drain_loads();
+    for (int t = 0; t < T; ++t) {
+      one_pair<double, TAN>(
+          a, t, shA, H, own, q,
+          [&]() {
+            q.load(a, fbar, jB);
+            shA = shB;
+            jB = a.nj[at(t + 2)];
+            shB = a.shift[at(t + 2)];
+          },
+          body);
+    }
+  }
+}
+
+// pairs of a lane (every K-th of its atom's row from sub on) and the longest such count of the wave
+template <int K>
+__device__ __forceinline__ int lane_pairs(const SysArgs& a, bool live, int i, int sub, int& p0, int& T) {
+  p0 = live ? a.off[i] + sub : 0;
+  const int p1 = live ? a.off[i + 1] : 0;
+  const int len = p1 > p0 ? (p1 - p0 + K - 1) / K : 0;
+  T = len;
+#pragma unroll
+  for (int s = 32; s > 0; s >>= 1) T = max(T, __shfl_xor(T, s, 64));
+  T = __builtin_amdgcn_readfirstlane(T);
+  return len;
 }
 
 // ---------------------------------------------------------------------------- moments
@@ -347,14 +426,14 @@ __device__ __forceinline__ void moments_of_atom(const SysArgs& a, const R* csh, 
   R m[NE];
 #pragma unroll
   for (int e = 0; e < NE; ++e) m[e] = R(0);
-  const double rix = a.pos[3 * i], riy = a.pos[3 * i + 1], riz = a.pos[3 * i + 2];
-  const int zi = clamp_species(a.species[i], a.nsp);
-  const R* cz = csh + zi * a.nsp * L::NMU * a.ncheb;
-  for_pairs<K, R>(a, lst, i, sub, H, rix, riy, riz, [&](int, int, int zj, double dx, double dy, double dz, double r, double) {
+  Partner<false> own;
+  own.load(a, nullptr, i);
+  const R* cz = csh + clamp_species(own.s, a.nsp) * a.nsp * L::NMU * a.ncheb;
+  for_pairs<K, R, false>(a, lst, i, sub, H, own, nullptr, [&](int, const Pair& t) {
     R f[L::NMU];
-    radial_values<R, L::NMU, NC>((R)r, (R)a.sa, (R)a.sb, (R)a.rcut, cz + zj * L::NMU * a.ncheb, a.ncheb, f);
-    if constexpr (PARTS) L::template acc_part<P>(m, f, (R)dx, (R)dy, (R)dz);
-    else L::template acc_moments<P>(m, f, (R)dx, (R)dy, (R)dz);
+    radial_values<R, L::NMU, NC>((R)t.r, (R)a.sa, (R)a.sb, (R)a.rcut, cz + t.zj * L::NMU * a.ncheb, a.ncheb, f);
+    if constexpr (PARTS) L::template acc_part<P>(m, f, (R)t.dx, (R)t.dy, (R)t.dz);
+    else L::template acc_moments<P>(m, f, (R)t.dx, (R)t.dy, (R)t.dz);
   });
   if constexpr (K > 1) {
 #pragma unroll
@@ -380,7 +459,6 @@ __device__ __forceinline__ void moments_of_atom(const SysArgs& a, const R* csh, 
 template <class L, int G, class R, bool BATCH, int NC, bool PERSIST = false, int K = 1>
 __global__ __launch_bounds__(kLaneBlock) __attribute__((amdgpu_waves_per_eu(std::is_same_v<R, double> ? 2 : 1)))
 void k_moments(SysArgs a, int i0, int n, R* __restrict__ mout, long ld) {
-  static_assert(K == 1 || !BATCH, "batches take one lane per atom");
   constexpr int NP = std::is_same_v<R, double> ? L::NPART : 1;
   __shared__ ListEntry lst[K == 1 ? kRowStage * kLaneBlock : 1];
   const R* csh = stage_radial<R>(a);
@@ -498,7 +576,10 @@ __device__ __forceinline__ void finish_gradients(bool live, int i, int sub, int 
   if (live) {
     if constexpr (BATCH) {
 #pragma unroll
-      for (int k = 0; k < 6; ++k) watom[6L * i + k] = ADD ? watom[6L * i + k] + w[k] : w[k];
+      for (int k = 0; k < 6; ++k) {
+        const double v = group_sum<K>(w[k]);
+        if (sub == 0) watom[6L * i + k] = ADD ? watom[6L * i + k] + v : v;
+      }
     }
     if constexpr (K > 1) {
 #pragma unroll
@@ -541,7 +622,6 @@ template <class L, int G, class R, bool BATCH, int NC, bool PERSIST = false, int
 __global__ __launch_bounds__(kLaneBlock) __attribute__((amdgpu_waves_per_eu(std::is_same_v<R, double> ? 2 : 1)))
 void k_backward(SysArgs a, int i0, int n, const R* __restrict__ mbar, long ld, double* __restrict__ g,
                 double* __restrict__ wpart, double* __restrict__ watom, double* __restrict__ fown) {
-  static_assert(K == 1 || !BATCH, "batches take one lane per atom");
   constexpr bool PARTS = std::is_same_v<R, double>;
   constexpr bool accumulate = G > 0;  // the first pass stores, later ones add
   constexpr int LO = PARTS ? 0 : L::GROUP_LO[PARTS ? 0 : G];
@@ -565,10 +645,11 @@ void k_backward(SysArgs a, int i0, int n, const R* __restrict__ mbar, long ld, d
       mb[e] = mbar[(long)(PARTS ? L::PART_ENTRY[0][PARTS ? e : 0] : LO + e) * ld + li];
       if constexpr (!PARTS) mb[e] *= R(L::MFACT[LO + e]);
     }
-    const double rix = a.pos[3 * i], riy = a.pos[3 * i + 1], riz = a.pos[3 * i + 2];
-    const int zi = clamp_species(a.species[i], a.nsp);
-    const R* cz = csh + zi * a.nsp * L::NMU * a.ncheb;
-    for_pairs<K, R>(a, lst, i, sub, H, rix, riy, riz, [&](int p, int, int zj, double dx, double dy, double dz, double r, double rinv) {
+    Partner<false> own;
+    own.load(a, nullptr, i);
+    const R* cz = csh + clamp_species(own.s, a.nsp) * a.nsp * L::NMU * a.ncheb;
+    for_pairs<K, R, false>(a, lst, i, sub, H, own, nullptr, [&](int p, const Pair& t) {
+      const double dx = t.dx, dy = t.dy, dz = t.dz;
       double old[3] = {0.0, 0.0, 0.0};  // loaded ahead of the arithmetic
       if constexpr (accumulate) {
 #pragma unroll
@@ -576,15 +657,15 @@ void k_backward(SysArgs a, int i0, int n, const R* __restrict__ mbar, long ld, d
         __builtin_amdgcn_sched_barrier(0);
       }
       R f[L::NMU], fp[L::NMU];
-      radial<R, L::NMU, NC>((R)r, (R)a.sa, (R)a.sb, (R)a.rcut, cz + zj * L::NMU * a.ncheb, a.ncheb, f, fp);
+      radial<R, L::NMU, NC>((R)t.r, (R)a.sa, (R)a.sb, (R)a.rcut, cz + t.zj * L::NMU * a.ncheb, a.ncheb, f, fp);
       R rgx = R(0), rgy = R(0), rgz = R(0), ru = R(0);
       double ur;
       if constexpr (PARTS) {
         L::template pair_part<0>(mb, f, fp, dx, dy, dz, rgx, rgy, rgz, ru);
-        ur = ru * rinv;
+        ur = ru * t.rinv;
       } else {
         L::template pair_grad<G>(mb, f, fp, (R)dx, (R)dy, (R)dz, rgx, rgy, rgz, ru);
-        ur = (double)ru / r;
+        ur = (double)ru / t.r;
       }
       const double gx = fma(ur, dx, (double)rgx);
       const double gy = fma(ur, dy, (double)rgy);
@@ -639,74 +720,26 @@ __device__ __forceinline__ void gradient_stage_first(const SysArgs& a, const dou
   double mb[NE];
 #pragma unroll
   for (int e = 0; e < NE; ++e) mb[e] = mbar[(long)L::PART_ENTRY[P][e] * ld + li];
-  const double rix = a.pos[3 * i], riy = a.pos[3 * i + 1], riz = a.pos[3 * i + 2];
-  const int zi = clamp_species(a.species[i], a.nsp);
-  const double* cz = csh + zi * a.nsp * L::NMU * a.ncheb;
+  Partner<false> own;
+  own.load(a, nullptr, i);
+  const double* cz = csh + clamp_species(own.s, a.nsp) * a.nsp * L::NMU * a.ncheb;
   int slot = 0;
-  auto body = [&](int, int, int zj, double dx, double dy, double dz, double r, double rinv) {
+  for_steps<K, false>(a, lst, i, lane, p0, len, T, H, own, nullptr, [&](int, const Pair& t) {
     double f[L::NMU], h[L::NMU];
-    radial<double, L::NMU, NC>(r, a.sa, a.sb, a.rcut, cz + zj * L::NMU * a.ncheb, a.ncheb, f, h);
+    radial<double, L::NMU, NC>(t.r, a.sa, a.sb, a.rcut, cz + t.zj * L::NMU * a.ncheb, a.ncheb, f, h);
 #pragma unroll
-    for (int mu = 0; mu < L::NMU; ++mu) h[mu] *= rinv;
+    for (int mu = 0; mu < L::NMU; ++mu) h[mu] *= t.rinv;
     double gx = 0.0, gy = 0.0, gz = 0.0, u = 0.0;
-    L::template pair_part<P>(mb, f, h, dx, dy, dz, gx, gy, gz, u);
+    L::template pair_part<P>(mb, f, h, t.dx, t.dy, t.dz, gx, gy, gz, u);
     auto& v = slots.v[slot];
-    v[0][lane] = double2{dx, dy};
-    v[1][lane] = double2{dz, fma(u, dx, gx)};
-    v[2][lane] = double2{fma(u, dy, gy), fma(u, dz, gz)};
+    v[0][lane] = double2{t.dx, t.dy};
+    v[1][lane] = double2{t.dz, fma(u, t.dx, gx)};
+    v[2][lane] = double2{fma(u, t.dy, gy), fma(u, t.dz, gz)};
 #pragma unroll
     for (int mu = 0; mu < L::NMU_SHARED; ++mu) v[3 + mu][lane] = double2{f[mu], h[mu]};
     slot = slot + 1 < L::NPART ? slot + 1 : 0;
     step_barrier();
-  };
-  if constexpr (K == 1) {
-    ListEntry* col = lst + lane;
-    for (int b = 0; b < T; b += kRowStage) {
-      const int m = min(kRowStage, len - b), kn = min(kRowStage, T - b);
-      if (m > 0) stage_row(a, p0 + b, m, col);
-      else col[0] = ListEntry{i, 0};  // a lane past its row
-      const int last = max(m - 1, 0);
-      ListEntry cur = col[0], nxt = col[min(1, last) * kLaneBlock];
-      double xA = a.pos[3 * cur.j], yA = a.pos[3 * cur.j + 1], zA = a.pos[3 * cur.j + 2];
-      int sA = a.species[cur.j];
-      drain_loads();
-      for (int k = 0; k < kn; ++k) {
-        one_pair<double>(
-            a, 0, 0, cur.shift, sA, H, rix, riy, riz, xA, yA, zA,
-            [&]() {
-              cur = nxt;
-              xA = a.pos[3 * cur.j];
-              yA = a.pos[3 * cur.j + 1];
-              zA = a.pos[3 * cur.j + 2];
-              sA = a.species[cur.j];
-              nxt = col[min(k + 2, last) * kLaneBlock];
-            },
-            body);
-      }
-    }
-  } else if (T > 0) {
-    // entry t of the lane; a lane without pairs reads some entry of the (non-empty) list
-    auto at = [&](int t) { return len > 0 ? p0 + min(t, len - 1) * K : 0; };
-    int jA = a.nj[at(0)], shA = a.shift[at(0)];
-    int jB = a.nj[at(1)], shB = a.shift[at(1)];
-    double xA = a.pos[3 * jA], yA = a.pos[3 * jA + 1], zA = a.pos[3 * jA + 2];
-    int sA = a.species[jA];
-    drain_loads();
-    for (int t = 0; t < T; ++t) {
-      one_pair<double>(
-          a, 0, 0, shA, sA, H, rix, riy, riz, xA, yA, zA,
-          [&]() {
-            xA = a.pos[3 * jB];
-            yA = a.pos[3 * jB + 1];
-            zA = a.pos[3 * jB + 2];
-            sA = a.species[jB];
-            shA = shB;
-            jB = a.nj[at(t + 2)];
-            shB = a.shift[at(t + 2)];
-          },
-          body);
-    }
-  }
+  });
 #pragma unroll
   for (int k = 1; k < L::NPART; ++k) step_barrier();
 }
@@ -763,7 +796,6 @@ template <class L, bool BATCH, int NC, bool PERSIST = false, int K = 1>
 __global__ __launch_bounds__(kLaneBlock * L::NPART) __attribute__((amdgpu_waves_per_eu(2)))
 void k_backward_stages(SysArgs a, int i0, int n, const double* __restrict__ mbar, long ld, double* __restrict__ g,
                        double* __restrict__ wpart, double* __restrict__ watom, double* __restrict__ fown) {
-  static_assert(K == 1 || !BATCH, "batches take one lane per atom");
   static_assert(L::NPART <= 4, "pair-gradient stages");
   __shared__ ListEntry lst[K == 1 ? kRowStage * kLaneBlock : 1];
   __shared__ StageSlots<L> slots;
@@ -775,12 +807,8 @@ void k_backward_stages(SysArgs a, int i0, int n, const double* __restrict__ mbar
     const bool live = li < n;
     const int ls = live ? li : 0;  // lanes past the last atom read the first one's data
     const int i = sweep_atom<BATCH>(a, i0 + ls);
-    const int p0 = live ? a.off[i] + sub : 0, p1 = live ? a.off[i + 1] : 0;
-    const int len = p1 > p0 ? (p1 - p0 + K - 1) / K : 0;
-    int T = len;  // longest row: the same in every wave
-#pragma unroll
-    for (int s = 32; s > 0; s >>= 1) T = max(T, __shfl_xor(T, s, 64));
-    T = __builtin_amdgcn_readfirstlane(T);
+    int p0, T;
+    const int len = lane_pairs<K>(a, live, i, sub, p0, T);
     // the stages alternate over the workgroup's waves from tile to tile (they differ in work, and
     // a wave's SIMD follows from its number)
     const int stage = (wave + b) % L::NPART;
@@ -799,36 +827,61 @@ void k_backward_stages(SysArgs a, int i0, int n, const double* __restrict__ mbar
 }
 
 // ---------------------------------------------------------------------------- parameter adjoint
-// Tangent of the moments along delta_ij = fbar_j - fbar_i (the direction in which the
-// force-weighted loss term differentiates the energy).
-template <class L, int G, bool PERSIST = false>
-__global__ __launch_bounds__(kLaneBlock) void k_tan_moments(SysArgs a, const double* __restrict__ fbar,
-                                                            int i0, int n, double* __restrict__ mdot,
-                                                            long ld) {
-  __shared__ ListEntry lst[kRowStage * kLaneBlock];
-  const double* csh = stage_radial<double>(a);
-  MTP_FOR_TILES(a, n, b) {
-  const int li = b * kLaneBlock + threadIdx.x;
-  if (li >= n) continue;
-  const int i = atom_at(a, i0 + li);
+// Tangent of the moments along delta_ij = fbar_j - fbar_i (the direction in which the force-weighted
+// loss term differentiates the energy), in parts of at most 66 entries as in the moment kernel: 1.8 ms
+// for 545,505 atoms at level 20 (4.3 in four passes of one wave per SIMD), 25 us for 16,000 at level 16
+// with four lanes per atom (139 in three passes of one lane per atom).
+template <class L, int P, int NC, int K>
+__device__ __forceinline__ void tangents_of_atom(const SysArgs& a, const double* csh, ListEntry* lst, int i, int li,
+                                                 int sub, const double* __restrict__ fbar,
+                                                 double* __restrict__ mdot, long ld) {
+  constexpr int NE = L::TPART_SIZE[P];
   double H[9];
   load_cell(a, i, H);
-  constexpr int LO = L::TGROUP_LO[G], HI = L::TGROUP_HI[G], NG = HI - LO;
-  double md[NG];
+  double md[NE];
 #pragma unroll
-  for (int e = 0; e < NG; ++e) md[e] = 0.0;
-  const double rix = a.pos[3 * i], riy = a.pos[3 * i + 1], riz = a.pos[3 * i + 2];
-  const double fix = fbar[3 * i], fiy = fbar[3 * i + 1], fiz = fbar[3 * i + 2];
-  const int zi = clamp_species(a.species[i], a.nsp);
-  for_pairs(a, lst, i, 0, H, rix, riy, riz, [&](int, int j, int zj, double dx, double dy, double dz, double r, double rinv) {
-    double f[L::NMU], fp[L::NMU];
-    radial<double, L::NMU>(r, a.sa, a.sb, a.rcut, csh + (zi * a.nsp + zj) * L::NMU * a.ncheb, a.ncheb, f, fp);
-    const double ex = fbar[3 * j] - fix, ey = fbar[3 * j + 1] - fiy, ez = fbar[3 * j + 2] - fiz;
-    const double rdot = (dx * ex + dy * ey + dz * ez) * rinv;
-    L::template tan_moments<G>(md, f, fp, dx, dy, dz, ex, ey, ez, rdot);
+  for (int e = 0; e < NE; ++e) md[e] = 0.0;
+  Partner<true> own;
+  own.load(a, fbar, i);
+  const double* cz = csh + clamp_species(own.s, a.nsp) * a.nsp * L::NMU * a.ncheb;
+  for_pairs<K, double, true>(a, lst, i, sub, H, own, fbar, [&](int, const Pair& t) {
+    double f[L::NMU], fd[L::NMU];
+    radial<double, L::NMU, NC>(t.r, a.sa, a.sb, a.rcut, cz + t.zj * L::NMU * a.ncheb, a.ncheb, f, fd);
+    const double rdot = (t.dx * t.ex + t.dy * t.ey + t.dz * t.ez) * t.rinv;
+#pragma unroll
+    for (int mu = 0; mu < L::NMU; ++mu) fd[mu] *= rdot;
+    L::template tan_part<P>(md, f, fd, t.dx, t.dy, t.dz, t.ex, t.ey, t.ez);
   });
+  if constexpr (K > 1) {
 #pragma unroll
-  for (int e = 0; e < NG; ++e) mdot[(long)(LO + e) * ld + li] = md[e];
+    for (int e = 0; e < NE; ++e) {
+      md[e] = group_sum<K>(md[e]);
+      asm volatile("" : "+v"(md[e]));
+    }
+  }
+  if (sub == 0) {
+#pragma unroll
+    for (int e = 0; e < NE; ++e) mdot[(long)L::TPART_ENTRY[P][e] * ld + li] = md[e];
+  }
+}
+
+template <class L, int NC, bool PERSIST = false, int K = 1>
+__global__ __launch_bounds__(kLaneBlock) __attribute__((amdgpu_waves_per_eu(2)))
+void k_tan_moments(SysArgs a, const double* __restrict__ fbar, int i0, int n, double* __restrict__ mdot, long ld) {
+  constexpr int NP = L::NTPART;
+  static_assert(NP <= 5, "moment-tangent parts");
+  __shared__ ListEntry lst[K == 1 ? kRowStage * kLaneBlock : 1];
+  const double* csh = stage_radial<double>(a);
+  MTP_FOR_TILES_K(a, n, K, NP, b) {
+  const int li = (b / NP) * (kLaneBlock / K) + (int)threadIdx.x / K, sub = (int)threadIdx.x % K;
+  if (li >= n) continue;
+  const int i = atom_at(a, i0 + li);
+  const int part = b % NP;
+  if (part == 0) tangents_of_atom<L, 0, NC, K>(a, csh, lst, i, li, sub, fbar, mdot, ld);
+  else if (NP > 1 && part == 1) tangents_of_atom<L, (NP > 1 ? 1 : 0), NC, K>(a, csh, lst, i, li, sub, fbar, mdot, ld);
+  else if (NP > 2 && part == 2) tangents_of_atom<L, (NP > 2 ? 2 : 0), NC, K>(a, csh, lst, i, li, sub, fbar, mdot, ld);
+  else if (NP > 3 && part == 3) tangents_of_atom<L, (NP > 3 ? 3 : 0), NC, K>(a, csh, lst, i, li, sub, fbar, mdot, ld);
+  else if (NP > 4) tangents_of_atom<L, (NP > 4 ? 4 : 0), NC, K>(a, csh, lst, i, li, sub, fbar, mdot, ld);
   }
 }
 
@@ -888,124 +941,278 @@ __global__ __launch_bounds__(kLaneBlock) void k_tan_reverse(const double* __rest
 }
 
 // Radial-coefficient gradient: per pair (i, j) with species (s, t),
-//   dc[s][t][mu][b] += Q_b (ebar S_mu - A_mu) - Q'_b (rhat . delta) S_mu,
-// accumulated per lane for one neighbour species at a time (following the per-species pair
-// chains) and summed over the wave with a fixed butterfly; one partial per (workgroup, s, t)
-// lands in cpart. G is an adjoint group: a
-// moment range small enough that its adjoints, their tangents and the sums of its mu values
-// [AMU_LO, AMU_HI] stay in registers; the partial rows of the other mu values are written as
-// zeros. NC is the compile-time Chebyshev count (0: runtime count up to kMaxCheb); every index
-// into the accumulators is a compile-time constant.
-template <class L, int G, int NC, bool PERSIST = false>
-__global__ __launch_bounds__(kLaneBlock) void k_adj_pairs(SysArgs a, const double* __restrict__ fbar,
-                                                          int i0, int n,
-                                                          const double* __restrict__ mbar,
-                                                          const double* __restrict__ mbard, long ld,
-                                                          double ebar, double* __restrict__ cpart) {
-  const double ebar0 = ebar;
-  MTP_FOR_TILES(a, n, b) {
-  ebar = ebar0;
-  const int li = b * kLaneBlock + threadIdx.x;
-  constexpr int LO = L::AGROUP_LO[G], HI = L::AGROUP_HI[G], NG = HI - LO;
-  constexpr int NMU = L::NMU, MLO = L::AMU_LO[G], MHI = L::AMU_HI[G], NM = MHI - MLO + 1;
-  constexpr int NQ = NC > 0 ? NC : kMaxCheb;
-  const int nq = NC > 0 ? NC : a.ncheb;
-  const bool live = li < n;
-  const int i = atom_at(a, i0 + (live ? li : 0));
+//   dc[s][t][mu][b] += Q_b X_mu + Q'_b Y_mu,  X_mu = ebar S_mu - A_mu,  Y_mu = -(rhat . delta) S_mu,
+// with S_mu = sum_e mb_e mono_e and A_mu its tangent (adjoint tangents mbd, displacement tangent
+// delta).  Two kernels: k_adj_stages evaluates X and Y of every pair and leaves a record
+// [r, t, X_0, Y_0, X_1, Y_1, ...] per pair, k_adj_radial sums them against the radial basis.
+// Adjoints and tangents of every entry (260 values at level 16, 590 at level 20) do not fit a lane,
+// and one kernel over ranges of 64 entries walked the pairs three to six times, species by species,
+// forming geometry, monomials, tangents and the radial sums each time: 10.2 ms for 545,505 atoms at
+// level 20 and 213 us for 16,000 at level 16 (one lane per atom).  Together the two take 3.3 ms (2.3
+// and 1.0) and 61 us (four lanes per atom).
+
+// NASTAGE waves per tile pass the pairs along as in k_backward_stages (at most 90 coefficients each);
+// the first forms the geometry, the last writes the records.
+template <class L>
+struct AdjSlots {
+  double2 v[L::NASTAGE][4 + L::NMU][kLaneBlock];  // (dx, dy) (dz, ex) (ey, ez) (r, rdot) (X, S) ...
+  int zj[L::NASTAGE][kLaneBlock];
+};
+template <int NMU>
+constexpr int adj_record() { return 2 * NMU + 2; }
+
+template <int NMU>
+__device__ __forceinline__ void write_record(double* __restrict__ rec, long p, double r, double rdot, int zj,
+                                             const double* S, const double* X) {
+  double2* q = reinterpret_cast<double2*>(rec + p * adj_record<NMU>());
+  q[0] = double2{r, (double)zj};
+#pragma unroll
+  for (int mu = 0; mu < NMU; ++mu) q[1 + mu] = double2{X[mu], -rdot * S[mu]};
+}
+
+template <class L, int B>
+__device__ __forceinline__ void adj_coefficients(const double* __restrict__ mbar, const double* __restrict__ mbard,
+                                                 long ld, int li, double ebar, double* c) {
+#pragma unroll
+  for (int k = 0; k < L::ADJ_SIZE[B]; ++k) {
+    const long at = (long)L::ADJ_ENTRY[B][k] * ld + li;
+    c[k] = L::ADJ_VALUE[B][k] ? fma(ebar, mbar[at], -mbard[at]) : mbar[at];
+  }
+}
+
+template <class L, int K>
+__device__ __forceinline__ void adj_stage_first(const SysArgs& a, ListEntry* lst, AdjSlots<L>& slots, int i, int li,
+                                                int lane, int p0, int len, int T, const double* __restrict__ fbar,
+                                                const double* __restrict__ mbar, const double* __restrict__ mbard,
+                                                long ld, double ebar, double* __restrict__ rec) {
   double H[9];
   load_cell(a, i, H);
-  if (a.ebar) ebar = a.ebar[a.cfg ? a.cfg[i] : 0];
-  double mb[NG], mbd[NG];
+  double c[L::ADJ_SIZE[0]];
+  adj_coefficients<L, 0>(mbar, mbard, ld, li, ebar, c);
+  Partner<true> own;
+  own.load(a, fbar, i);
+  int slot = 0;
+  for_steps<K, true>(a, lst, i, lane, p0, len, T, H, own, fbar, [&](int t, const Pair& q) {
+    const double rdot = (q.dx * q.ex + q.dy * q.ey + q.dz * q.ez) * q.rinv;
+    double S[L::NMU], X[L::NMU];
 #pragma unroll
-  for (int e = 0; e < NG; ++e) {
-    mb[e] = live ? mbar[(long)(LO + e) * ld + li] : 0.0;
-    mbd[e] = live ? mbard[(long)(LO + e) * ld + li] : 0.0;
-  }
-  const double rix = a.pos[3 * i], riy = a.pos[3 * i + 1], riz = a.pos[3 * i + 2];
-  const double fix = fbar[3 * i], fiy = fbar[3 * i + 1], fiz = fbar[3 * i + 2];
-  const int zi = clamp_species(a.species[i], a.nsp);
-  const int p0 = live ? a.off[i] : 0, p1 = live ? a.off[i + 1] : 0;
-  for (int t = 0; t < a.nsp; ++t) {
-    double acc[NM * NQ];
+    for (int mu = 0; mu < L::NMU; ++mu) S[mu] = X[mu] = 0.0;
+    L::template adj_stage<0>(c, q.dx, q.dy, q.dz, q.ex, q.ey, q.ez, S, X);
+    if constexpr (L::NASTAGE == 1) {
+      if (t < len) write_record<L::NMU>(rec, p0 + (long)t * K, q.r, rdot, q.zj, S, X);
+    } else {
+      auto& v = slots.v[slot];
+      v[0][lane] = double2{q.dx, q.dy};
+      v[1][lane] = double2{q.dz, q.ex};
+      v[2][lane] = double2{q.ey, q.ez};
+      v[3][lane] = double2{q.r, rdot};
 #pragma unroll
-    for (int k = 0; k < NM * NQ; ++k) acc[k] = 0.0;
-    // each lane follows its row's chain of species-t pairs (the whole row with one species),
-    // so the wave runs the pair body max over lanes (not the row length) times per species;
-    // the next link and the next pair's list entries are loaded one pair ahead
-    auto link = [&](int q) -> int { return a.plink ? a.plink[q] : (q + 1 < p1 ? q + 1 : -1); };
-    int p = !live ? -1 : a.pfirst ? a.pfirst[(long)i * a.nsp + t] : (p0 < p1 ? p0 : -1);
-    int pn = p >= 0 ? link(p) : -1;
-    int j = p >= 0 ? a.nj[p] : 0, sh = p >= 0 ? a.shift[p] : 0;
-    for (;;) {
-      if (!__any(p >= 0)) break;
-      if (p < 0) continue;
-      const int pnn = pn >= 0 ? link(pn) : -1;
-      const int jn = pn >= 0 ? a.nj[pn] : 0, shn = pn >= 0 ? a.shift[pn] : 0;
-      int n1, n2, n3;
-      unpack_shift(sh, n1, n2, n3);
-      double dx, dy, dz;
-      pair_displacement(rix, riy, riz, a.pos[3 * j], a.pos[3 * j + 1], a.pos[3 * j + 2], n1, n2,
-                        n3, H, dx, dy, dz);
-      double r, rinv;
-      root_and_inverse(dist2_exact(dx, dy, dz), r, rinv);
-      const double ex = fbar[3 * j] - fix, ey = fbar[3 * j + 1] - fiy, ez = fbar[3 * j + 2] - fiz;
-      const double rdot = (dx * ex + dy * ey + dz * ez) * rinv;
-      double S[NMU], A[NMU];
-#pragma unroll
-      for (int mu = 0; mu < NMU; ++mu) S[mu] = A[mu] = 0.0;
-      L::template adj_pair<G>(mb, mbd, dx, dy, dz, ex, ey, ez, S, A);
-      double X[NM], Y[NM];
-#pragma unroll
-      for (int k = 0; k < NM; ++k) {
-        X[k] = fma(ebar, S[MLO + k], -A[MLO + k]);
-        Y[k] = -rdot * S[MLO + k];
-      }
-      // Q_b = T_b(u) w^2, Q'_b = sa T'_b(u) w^2 - 2 T_b(u) w
-      const double u = fma(a.sa, r, a.sb), w = a.rcut - r, w2 = w * w;
-      double t2 = 1.0, t1 = u, d2 = 0.0, d1 = 1.0;
-#pragma unroll
-      for (int bq = 0; bq < NQ; ++bq) {
-        if (NC == 0 && bq >= nq) break;
-        double T, D;
-        if (bq == 0) {
-          T = 1.0;
-          D = 0.0;
-        } else if (bq == 1) {
-          T = u;
-          D = 1.0;
-        } else {
-          T = fma(2.0 * u, t1, -t2);
-          D = fma(2.0 * u, d1, fma(2.0, t1, -d2));
-          t2 = t1;
-          t1 = T;
-          d2 = d1;
-          d1 = D;
-        }
-        const double q = T * w2, qp = fma(a.sa * w2, D, -2.0 * w * T);
-#pragma unroll
-        for (int k = 0; k < NM; ++k) acc[k * NQ + bq] = fma(q, X[k], fma(qp, Y[k], acc[k * NQ + bq]));
-      }
-      p = pn;
-      pn = pnn;
-      j = jn;
-      sh = shn;
+      for (int mu = 0; mu < L::NMU; ++mu) v[4 + mu][lane] = double2{X[mu], S[mu]};
+      slots.zj[slot][lane] = q.zj;
+      slot = slot + 1 < L::NASTAGE ? slot + 1 : 0;
+      step_barrier();
     }
-    for (int sp = 0; sp < a.nsp; ++sp) {
-      double* dst = cpart + (long)b * a.nsp * a.nsp * NMU * nq + (long)(sp * a.nsp + t) * NMU * nq;
-      for (int k = threadIdx.x; k < NMU * nq; k += kLaneBlock) {
-        const int mu = k / nq;
-        if (mu < MLO || mu > MHI) dst[k] = 0.0;
-      }
+  });
 #pragma unroll
-      for (int k = 0; k < NM; ++k)
+  for (int k = 1; k < L::NASTAGE; ++k) step_barrier();
+}
+
+template <class L, int B, int K>
+__device__ __forceinline__ void adj_stage(AdjSlots<L>& slots, int li, int lane, int p0, int len, int T,
+                                          const double* __restrict__ mbar, const double* __restrict__ mbard, long ld,
+                                          double ebar, double* __restrict__ rec) {
+  double c[L::ADJ_SIZE[B]];
+  adj_coefficients<L, B>(mbar, mbard, ld, li, ebar, c);
+#pragma unroll
+  for (int k = 0; k < B; ++k) step_barrier();
+  int slot = 0;
+  for (int t = 0; t < T; ++t) {
+    auto& v = slots.v[slot];
+    const double2 v0 = v[0][lane], v1 = v[1][lane], v2 = v[2][lane];
+    constexpr bool LAST = B == L::NASTAGE - 1;
+    double S[L::NMU], X[L::NMU];
+#pragma unroll
+    for (int mu = 0; mu < L::NMU; ++mu) {
+      if (LAST || (mu >= L::ADJ_MU_LO[B] && mu <= L::ADJ_MU_HI[B])) {
+        const double2 xs = v[4 + mu][lane];
+        X[mu] = xs.x;
+        S[mu] = xs.y;
+      } else {
+        X[mu] = S[mu] = 0.0;
+      }
+    }
+    L::template adj_stage<B>(c, v0.x, v0.y, v1.x, v1.y, v2.x, v2.y, S, X);
+    if constexpr (LAST) {
+      const double2 v3 = v[3][lane];
+      const int zj = slots.zj[slot][lane];
+      if (t < len) write_record<L::NMU>(rec, p0 + (long)t * K, v3.x, v3.y, zj, S, X);
+    } else {
+#pragma unroll
+      for (int mu = L::ADJ_MU_LO[B]; mu <= L::ADJ_MU_HI[B]; ++mu) v[4 + mu][lane] = double2{X[mu], S[mu]};
+    }
+    slot = slot + 1 < L::NASTAGE ? slot + 1 : 0;
+    step_barrier();
+  }
+#pragma unroll
+  for (int k = B + 1; k < L::NASTAGE; ++k) step_barrier();
+}
+
+template <class L, bool PERSIST = false, int K = 1>
+__global__ __launch_bounds__(kLaneBlock * L::NASTAGE) __attribute__((amdgpu_waves_per_eu(2)))
+void k_adj_stages(SysArgs a, const double* __restrict__ fbar, int i0, int n, const double* __restrict__ mbar,
+                  const double* __restrict__ mbard, long ld, double ebar0, double* __restrict__ rec) {
+  static_assert(L::NASTAGE <= 8, "adjoint stages");
+  __shared__ ListEntry lst[K == 1 ? kRowStage * kLaneBlock : 1];
+  __shared__ AdjSlots<L> slots;
+  const int lane = (int)threadIdx.x & (kLaneBlock - 1);
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kLaneBlock);
+  MTP_FOR_TILES_K(a, n, K, 1, b) {
+    const int li = b * (kLaneBlock / K) + lane / K, sub = lane % K;
+    const bool live = li < n;
+    const int ls = live ? li : 0;  // lanes past the last atom read the first one's data
+    const int i = atom_at(a, i0 + ls);
+    int p0, T;
+    const int len = lane_pairs<K>(a, live, i, sub, p0, T);
+    const double ebar = a.ebar ? a.ebar[a.cfg ? a.cfg[i] : 0] : ebar0;
+    const int stage = (wave + b) % L::NASTAGE;
+    if (stage == 0)
+      adj_stage_first<L, K>(a, lst, slots, i, ls, lane, p0, len, T, fbar, mbar, mbard, ld, ebar, rec);
+#define MTP_ADJ_STAGE(S)                                                                                     \
+  else if (L::NASTAGE > S && stage == S)                                                                     \
+      adj_stage<L, (L::NASTAGE > S ? S : 0), K>(slots, ls, lane, p0, len, T, mbar, mbard, ld, ebar, rec);
+    MTP_ADJ_STAGE(1) MTP_ADJ_STAGE(2) MTP_ADJ_STAGE(3) MTP_ADJ_STAGE(4) MTP_ADJ_STAGE(5) MTP_ADJ_STAGE(6)
+    MTP_ADJ_STAGE(7)
+#undef MTP_ADJ_STAGE
+    if constexpr (PERSIST) __syncthreads();
+  }
+}
+
+// Sums of the pair records against the radial basis.  A lane orders its pairs by neighbour species in
+// LDS (kOrderStage at a time) and the wave takes one species after the other, accumulating
+// NMU x n_cheb sums in registers; they are transposed through LDS and each lane adds one sum over
+// the wave's atoms of each centre species (in lane order).  One partial per (tile, s, t) in cpart.
+// The record reads (96 bytes per pair at level 20, the species a second time) and about 180 vector
+// instructions per pair bound it.
+constexpr int kOrderStage = 64;
+template <int NMU, int NC>
+__global__ __launch_bounds__(kLaneBlock)
+void k_adj_radial(SysArgs a, int n, const double* __restrict__ rec, double* __restrict__ cpart) {
+  constexpr int NQ = NC > 0 ? NC : kMaxCheb, NV = NMU * NQ, RW = adj_record<NMU>();
+  __shared__ unsigned char zp[kOrderStage][kLaneBlock], ord[kOrderStage][kLaneBlock];
+  __shared__ unsigned char first[kMaxSpecies + 1][kLaneBlock], cnt[kMaxSpecies][kLaneBlock];
+  constexpr int PASSES = (NV + 31) / 32, NR = (NV + PASSES - 1) / PASSES;  // sums transposed at a time
+  __shared__ double red[NR * (kLaneBlock + 1)];  // padded rows: a lane reads along its own row
+  const int nq = NC > 0 ? NC : a.ncheb, K = a.split;
+  const int lane = threadIdx.x;
+  const int b = xcd_logical_block(blockIdx.x, gridDim.x);
+  const int li = b * (kLaneBlock / K) + lane / K;
+  const bool live = li < n;
+  const int i = atom_at(a, live ? li : 0);
+  const int zi = live ? clamp_species(a.species[i], a.nsp) : -1;
+  const int p0 = live ? a.off[i] + lane % K : 0, p1 = live ? a.off[i + 1] : 0;
+  const int len = p1 > p0 ? (p1 - p0 + K - 1) / K : 0;
+  // order of pairs [base, base + m) of the lane by species
+  auto arrange = [&](int base, int m) {
+    for (int t = 0; t < a.nsp; ++t) cnt[t][lane] = 0;
+#pragma unroll 8
+    for (int k = 0; k < m; ++k) {
+      const int t = (int)rec[(p0 + (long)(base + k) * K) * RW + 1];
+      zp[k][lane] = (unsigned char)t;
+      cnt[t][lane]++;
+    }
+    int at = 0;
+    for (int t = 0; t < a.nsp; ++t) {
+      first[t][lane] = (unsigned char)at;
+      at += cnt[t][lane];
+      cnt[t][lane] = first[t][lane];
+    }
+    first[a.nsp][lane] = (unsigned char)at;
+    for (int k = 0; k < m; ++k) {
+      const int t = zp[k][lane];
+      ord[cnt[t][lane]++][lane] = (unsigned char)k;
+    }
+  };
+  const bool once = !__any(len > kOrderStage);  // every row of the wave fits one arrangement
+  if (once) arrange(0, len);
+  for (int t = 0; t < a.nsp; ++t) {
+    double acc[NV];
+#pragma unroll
+    for (int k = 0; k < NV; ++k) acc[k] = 0.0;
+    for (int base = 0; base < len; base += kOrderStage) {
+      if (!once) arrange(base, min(kOrderStage, len - base));
+      const int k0 = first[t][lane], k1 = first[t + 1][lane];
+      if (k0 >= k1) continue;
+      auto row = [&](int k) {
+        return reinterpret_cast<const double2*>(rec + (p0 + (long)(base + ord[k][lane]) * K) * RW);
+      };
+      const double2* q = row(k0);
+      double2 v[NMU + 1];
+#pragma unroll
+      for (int m = 0; m <= NMU; ++m) v[m] = q[m];
+      int k = k0;
+      do {
+        double X[NMU], Y[NMU];
+        const double r = v[0].x;
+#pragma unroll
+        for (int m = 0; m < NMU; ++m) {
+          X[m] = v[1 + m].x;
+          Y[m] = v[1 + m].y;
+        }
+        const double u = fma(a.sa, r, a.sb), w = a.rcut - r, w2 = w * w;
+        q = row(min(k + 1, k1 - 1));
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int m = 0; m <= NMU; ++m) v[m] = q[m];
+        __builtin_amdgcn_sched_barrier(0);
+        // Q_b = T_b(u) w^2, Q'_b = sa T'_b(u) w^2 - 2 T_b(u) w
+        double t2 = 1.0, t1 = u, d2 = 0.0, d1 = 1.0;
 #pragma unroll
         for (int bq = 0; bq < NQ; ++bq) {
-          if (NC == 0 && bq >= nq) break;
-          const double v = wave_sum((live && zi == sp) ? acc[k * NQ + bq] : 0.0);
-          if (threadIdx.x == 0) dst[(MLO + k) * nq + bq] = v;
+          if (NC == 0 && bq >= nq) continue;
+          double T, D;
+          if (bq == 0) {
+            T = 1.0;
+            D = 0.0;
+          } else if (bq == 1) {
+            T = u;
+            D = 1.0;
+          } else {
+            T = fma(2.0 * u, t1, -t2);
+            D = fma(2.0 * u, d1, fma(2.0, t1, -d2));
+            t2 = t1;
+            t1 = T;
+            d2 = d1;
+            d1 = D;
+          }
+          const double qb = T * w2, qp = fma(a.sa * w2, D, -2.0 * w * T);
+#pragma unroll
+          for (int m = 0; m < NMU; ++m) acc[m * NQ + bq] = fma(qb, X[m], fma(qp, Y[m], acc[m * NQ + bq]));
         }
+        ++k;
+      } while (k < k1);
     }
-  }
+#pragma unroll
+    for (int v0 = 0; v0 < NV; v0 += NR) {
+      __syncthreads();  // the sums transposed before are read
+#pragma unroll
+      for (int k = 0; k < NR; ++k)
+        if (v0 + k < NV) red[k * (kLaneBlock + 1) + lane] = acc[v0 + k];
+      __syncthreads();
+      const int v = v0 + lane;
+      const double* row = red + (lane < NR ? lane : 0) * (kLaneBlock + 1);
+      for (int sp = 0; sp < a.nsp; ++sp) {
+        double* dst = cpart + (long)b * a.nsp * a.nsp * NMU * nq + (long)(sp * a.nsp + t) * NMU * nq;
+        const unsigned long long mask = __ballot(zi == sp);
+        double sum = 0.0;
+        if (mask == ~0ull) {
+#pragma unroll 16
+          for (int l = 0; l < kLaneBlock; ++l) sum += row[l];
+        } else {
+          for (unsigned long long mk = mask; mk; mk &= mk - 1) sum += row[__ffsll(mk) - 1];
+        }
+        if (lane < NR && v < NV && v % NQ < nq) dst[(v / NQ) * nq + v % NQ] = sum;
+      }
+    }
   }
 }
 
@@ -1023,16 +1230,17 @@ void launch_moments_gp(const SysArgs& a, int i0, int n, void* m, long ld, hipStr
   else
     hipLaunchKernelGGL((k_moments<L, G, R, BATCH, 0, PERSIST, K>), dim3(nb), dim3(kLaneBlock), sh, s, a, i0, n, (R*)m, ld);
 }
-// persistent variants exist for batches only (a single system uses one grid of its tiles);
-// split lanes for single systems in binary64 only
+// split lanes in binary64 only; persistent variants exist for batches of one lane per atom (a
+// system small enough for split lanes is one round of workgroups)
 template <class L, int G, class R, bool BATCH>
 void launch_moments_g(const SysArgs& a, int i0, int n, void* m, long ld, hipStream_t s) {
-  if constexpr (BATCH) {
-    if (a.queue) return launch_moments_gp<L, G, R, BATCH, true>(a, i0, n, m, ld, s);
-  } else if constexpr (std::is_same_v<R, double>) {
+  if constexpr (std::is_same_v<R, double>) {
     if (a.split == 2) return launch_moments_gp<L, G, R, BATCH, false, 2>(a, i0, n, m, ld, s);
     if (a.split == 4) return launch_moments_gp<L, G, R, BATCH, false, 4>(a, i0, n, m, ld, s);
     if (a.split == 8) return launch_moments_gp<L, G, R, BATCH, false, 8>(a, i0, n, m, ld, s);
+  }
+  if constexpr (BATCH) {
+    if (a.queue) return launch_moments_gp<L, G, R, BATCH, true>(a, i0, n, m, ld, s);
   }
   launch_moments_gp<L, G, R, BATCH, false>(a, i0, n, m, ld, s);
 }
@@ -1065,12 +1273,13 @@ void launch_backward_gp(const SysArgs& a, int i0, int n, const void* mb, long ld
 template <class L, int G, class R, bool BATCH>
 void launch_backward_g(const SysArgs& a, int i0, int n, const void* mb, long ld, double* g,
                        double* wpart, double* watom, double* fown, hipStream_t s) {
-  if constexpr (BATCH) {
-    if (a.queue) return launch_backward_gp<L, G, R, BATCH, true>(a, i0, n, mb, ld, g, wpart, watom, fown, s);
-  } else if constexpr (std::is_same_v<R, double>) {
+  if constexpr (std::is_same_v<R, double>) {
     if (a.split == 2) return launch_backward_gp<L, G, R, BATCH, false, 2>(a, i0, n, mb, ld, g, wpart, watom, fown, s);
     if (a.split == 4) return launch_backward_gp<L, G, R, BATCH, false, 4>(a, i0, n, mb, ld, g, wpart, watom, fown, s);
     if (a.split == 8) return launch_backward_gp<L, G, R, BATCH, false, 8>(a, i0, n, mb, ld, g, wpart, watom, fown, s);
+  }
+  if constexpr (BATCH) {
+    if (a.queue) return launch_backward_gp<L, G, R, BATCH, true>(a, i0, n, mb, ld, g, wpart, watom, fown, s);
   }
   launch_backward_gp<L, G, R, BATCH, false>(a, i0, n, mb, ld, g, wpart, watom, fown, s);
 }
@@ -1134,23 +1343,24 @@ struct EnergyChain {
 
 template <class L>
 struct AdjImpl {
-  template <int G>
-  static void tan_moments_g(const SysArgs& a, const double* fbar, int i0, int n, double* md, long ld,
-                            hipStream_t s) {
-    const int nb = pair_grid(a, (n + kLaneBlock - 1) / kLaneBlock);
-    if (a.queue)
-      hipLaunchKernelGGL((k_tan_moments<L, G, true>), dim3(nb), dim3(kLaneBlock), radial_bytes<double>(a), s, a, fbar, i0, n, md, ld);
-    else
-      hipLaunchKernelGGL((k_tan_moments<L, G, false>), dim3(nb), dim3(kLaneBlock), radial_bytes<double>(a), s, a, fbar, i0, n, md, ld);
+  template <int NC, bool PERSIST, int K>
+  static void tan_moments_k(const SysArgs& a, const double* fbar, int i0, int n, double* md, long ld, hipStream_t s) {
+    const int nb = pair_grid(a, split_tiles(n, K) * L::NTPART);
+    hipLaunchKernelGGL((k_tan_moments<L, NC, PERSIST, K>), dim3(nb), dim3(kLaneBlock), radial_bytes<double>(a), s, a,
+                       fbar, i0, n, md, ld);
   }
-  template <size_t... Gs>
-  static void tan_moments_d(int g, const SysArgs& a, const double* fbar, int i0, int n, double* md, long ld,
-                            hipStream_t s, std::index_sequence<Gs...>) {
-    ((g == (int)Gs ? tan_moments_g<(int)Gs>(a, fbar, i0, n, md, ld, s) : void()), ...);
+  template <int NC>
+  static void tan_moments_nc(const SysArgs& a, const double* fbar, int i0, int n, double* md, long ld, hipStream_t s) {
+    if (a.split == 2) tan_moments_k<NC, false, 2>(a, fbar, i0, n, md, ld, s);
+    else if (a.split == 4) tan_moments_k<NC, false, 4>(a, fbar, i0, n, md, ld, s);
+    else if (a.split == 8) tan_moments_k<NC, false, 8>(a, fbar, i0, n, md, ld, s);
+    else if (a.queue) tan_moments_k<NC, true, 1>(a, fbar, i0, n, md, ld, s);
+    else tan_moments_k<NC, false, 1>(a, fbar, i0, n, md, ld, s);
   }
-  static void tan_moments(int g, const SysArgs& a, const double* fbar, int i0, int n, double* md, long ld,
-                          hipStream_t s) {
-    tan_moments_d(g, a, fbar, i0, n, md, ld, s, std::make_index_sequence<L::NTGROUP>{});
+  static void tan_moments(const SysArgs& a, const double* fbar, int i0, int n, double* md, long ld, hipStream_t s) {
+    if (a.ncheb == 8) tan_moments_nc<8>(a, fbar, i0, n, md, ld, s);
+    else if (a.ncheb == 10) tan_moments_nc<10>(a, fbar, i0, n, md, ld, s);
+    else tan_moments_nc<0>(a, fbar, i0, n, md, ld, s);
   }
   static void tan_forward(const SysArgs& a, const double* m, const double* md, long ld, int i0, int n,
                           const double* xi, double ebar, double* out, double* cbard, hipStream_t s) {
@@ -1164,42 +1374,33 @@ struct AdjImpl {
     const int nb = (n + kLaneBlock - 1) / kLaneBlock;
     hipLaunchKernelGGL((k_tan_reverse<L, P>), dim3(nb), dim3(kLaneBlock), 0, s, m, md, ld, n, cb, cbd, mbd);
   }
-  template <int G>
-  static void adj_pairs_g(const SysArgs& a, const double* fbar, int i0, int n, const double* mb,
-                          const double* mbd, long ld, double ebar, double* cpart, hipStream_t s) {
-    const int nb = pair_grid(a, (n + kLaneBlock - 1) / kLaneBlock);
-    if (a.queue) adj_pairs_gp<G, true>(nb, a, fbar, i0, n, mb, mbd, ld, ebar, cpart, s);
-    else adj_pairs_gp<G, false>(nb, a, fbar, i0, n, mb, mbd, ld, ebar, cpart, s);
+  template <bool PERSIST, int K>
+  static void adj_pairs_k(const SysArgs& a, const double* fbar, int i0, int n, const double* mb, const double* mbd,
+                          long ld, double ebar, double* rec, hipStream_t s) {
+    const int nb = pair_grid(a, split_tiles(n, K));
+    hipLaunchKernelGGL((k_adj_stages<L, PERSIST, K>), dim3(nb), dim3(kLaneBlock * L::NASTAGE), 0, s, a, fbar, i0, n, mb,
+                       mbd, ld, ebar, rec);
   }
-  template <int G, bool P>
-  static void adj_pairs_gp(int nb, const SysArgs& a, const double* fbar, int i0, int n, const double* mb,
-                           const double* mbd, long ld, double ebar, double* cpart, hipStream_t s) {
-    if (a.ncheb == 8)
-      hipLaunchKernelGGL((k_adj_pairs<L, G, 8, P>), dim3(nb), dim3(kLaneBlock), 0, s, a, fbar, i0, n, mb, mbd, ld,
-                         ebar, cpart);
-    else if (a.ncheb == 10)
-      hipLaunchKernelGGL((k_adj_pairs<L, G, 10, P>), dim3(nb), dim3(kLaneBlock), 0, s, a, fbar, i0, n, mb, mbd, ld,
-                         ebar, cpart);
-    else
-      hipLaunchKernelGGL((k_adj_pairs<L, G, 0, P>), dim3(nb), dim3(kLaneBlock), 0, s, a, fbar, i0, n, mb, mbd, ld,
-                         ebar, cpart);
+  static void adj_pairs(const SysArgs& a, const double* fbar, int i0, int n, const double* mb, const double* mbd,
+                        long ld, double ebar, double* rec, hipStream_t s) {
+    if (a.split == 2) adj_pairs_k<false, 2>(a, fbar, i0, n, mb, mbd, ld, ebar, rec, s);
+    else if (a.split == 4) adj_pairs_k<false, 4>(a, fbar, i0, n, mb, mbd, ld, ebar, rec, s);
+    else if (a.split == 8) adj_pairs_k<false, 8>(a, fbar, i0, n, mb, mbd, ld, ebar, rec, s);
+    else if (a.queue) adj_pairs_k<true, 1>(a, fbar, i0, n, mb, mbd, ld, ebar, rec, s);
+    else adj_pairs_k<false, 1>(a, fbar, i0, n, mb, mbd, ld, ebar, rec, s);
   }
-  template <size_t... Gs>
-  static void adj_pairs_d(int g, const SysArgs& a, const double* fbar, int i0, int n, const double* mb,
-                          const double* mbd, long ld, double ebar, double* cpart, hipStream_t s,
-                          std::index_sequence<Gs...>) {
-    ((g == (int)Gs ? adj_pairs_g<(int)Gs>(a, fbar, i0, n, mb, mbd, ld, ebar, cpart, s) : void()), ...);
-  }
-  static void adj_pairs(int g, const SysArgs& a, const double* fbar, int i0, int n, const double* mb,
-                        const double* mbd, long ld, double ebar, double* cpart, hipStream_t s) {
-    adj_pairs_d(g, a, fbar, i0, n, mb, mbd, ld, ebar, cpart, s, std::make_index_sequence<L::NAGROUP>{});
+  static void adj_radial(const SysArgs& a, int n, const double* rec, double* cpart, hipStream_t s) {
+    const dim3 nb(split_tiles(n, a.split)), nt(kLaneBlock);
+    if (a.ncheb == 8) hipLaunchKernelGGL((k_adj_radial<L::NMU, 8>), nb, nt, 0, s, a, n, rec, cpart);
+    else if (a.ncheb == 10) hipLaunchKernelGGL((k_adj_radial<L::NMU, 10>), nb, nt, 0, s, a, n, rec, cpart);
+    else hipLaunchKernelGGL((k_adj_radial<L::NMU, 0>), nb, nt, 0, s, a, n, rec, cpart);
   }
   static AdjOps ops() {
     AdjOps o{};
     o.tan_moments = &tan_moments;
     o.adj_pairs = &adj_pairs;
-    o.nagroup = L::NAGROUP;
-    o.ntgroup = L::NTGROUP;
+    o.adj_radial = &adj_radial;
+    o.record = adj_record<L::NMU>();
     o.nrtpart = L::NRTPART;
     static_assert(L::NRTPART <= kMaxRevParts, "reverse-tangent parts");
     return o;
