@@ -2,19 +2,22 @@
 // extrapolation grade; the iteration of Goreinov et al. 2010).
 //
 // One iteration on the device, candidates C [m][n], active set A [n][n], Ainv = A^-1:
-//   1. k_rowmax: for every candidate row i, the largest |(c_i Ainv)_k| and the first k reaching
-//      it, with the product on binary64 matrix cores (a wave takes 16 rows, column tiles of 16);
-//   2. k_argmax_part / k_argmax_final: the first row (row-major order) reaching the largest value;
-//   3. k_swap: g = (c_i Ainv)_k; row r = c_i Ainv is formed in LDS, Ainv is updated by
-//      Sherman-Morrison for replacing row k of A by c_i,
+//   1. k_best: every workgroup's first entry (row-major) of largest |(c_i Ainv)_k| over its tiles of 16
+//      candidate rows, the product on binary64 matrix cores;
+//   2. k_select: the first such entry over the workgroups; g = (c_i Ainv)_k, the row r = c_i Ainv - e_k
+//      and the column Ainv[:, k]; decides whether the iteration goes on and logs (i, k, g);
+//   3. k_update: Ainv is updated by Sherman-Morrison for replacing row k of A by c_i,
 //        Ainv' = Ainv - Ainv[:, k] (r - e_k) / g,
 //      and rows A[k] and C[i] are exchanged.
-// The host reads (i, k, g) once per iteration and stops when |g| <= 1 + tol.
+// The kernels of an iteration after the last one return at once, so the host enqueues several
+// iterations (twice as many each time) before it reads the log.  5000 candidates of 116 columns:
+// 152 us per iteration with one wave per 16 rows, the update in one workgroup and a synchronization
+// per iteration; 31 us now (k_best 16.5, k_select 8, k_update 3), bound by the latency of three
+// dependent kernels that each read what another chiplet's L2 just wrote.
 #include <hip/hip_runtime.h>
 #include <math.h>
 
-#include <cmath>
-
+#include <algorithm>
 #include <string>
 
 #include "mtp.h"
@@ -25,172 +28,202 @@
 namespace mtp {
 namespace {
 
-constexpr int kRowWaves = 4;
-constexpr int kNT = 256;
-constexpr int kArgParts = 256;
+constexpr int kRowWaves = 4;      // waves of a workgroup of k_best
+constexpr int kColTiles = 2;      // column tiles of 16 a wave accumulates at a time
+constexpr int kChunk = 128;       // columns of C staged in LDS at a time
+constexpr int kMaxParts = 2048;   // workgroups of k_best (more tiles: several per workgroup)
+constexpr int kSelThreads = 1024;
+constexpr int kSegments = 8;      // partial sums per entry of r
 
 typedef double v4d __attribute__((ext_vector_type(4)));
 
-// (value, index) pair kept by the larger value, then the smaller index
-__device__ __forceinline__ void keep_max(double& v, int& k, double v2, int k2) {
+// device words that steer the iterations of a call
+struct Control {
+  int done;       // 0: go on, 1: no entry above 1 + tol, 2: the selected entry is not finite
+  int swaps;      // swaps done
+  int i, k;       // selection of the current iteration
+  double g;
+};
+struct Log {
+  double i, k, g;
+};
+
+// (value, row-major index) pair kept by the larger value, then the smaller index
+__device__ __forceinline__ void keep_max(double& v, long& k, double v2, long k2) {
   if (v2 > v || (v2 == v && k2 < k)) {
     v = v2;
     k = k2;
   }
 }
+__device__ __forceinline__ void keep_max_across(double& v, long& k, int s) {
+  const double v2 = __shfl_xor(v, s, 64);
+  const long k2 = __shfl_xor(k, s, 64);
+  keep_max(v, k, v2, k2);
+}
 
 // V_MFMA_F64_16X16X4F64 layout (wave64): lane l supplies A[l % 16][l / 16] and B[l / 16][l % 16];
 // accumulator register r holds D[4 r + l / 16][l % 16].
-__global__ __launch_bounds__(64 * kRowWaves) void k_rowmax(const double* __restrict__ C, int m, int n,
-                                                           const double* __restrict__ ainv,
-                                                           double* __restrict__ rmax, int* __restrict__ rarg) {
-  const int lane = threadIdx.x & 63;
-  const int tile = blockIdx.x * kRowWaves + (threadIdx.x >> 6);
-  const int i0 = tile * 16;
-  if (i0 >= m) return;
+// A workgroup takes tiles of 16 rows; its waves share the columns, kColTiles tiles each at a time.
+// The rows are staged in LDS (padded by two doubles: the 16 rows of an operand read start in
+// different banks); Ainv comes from L2.
+__global__ __launch_bounds__(64 * kRowWaves) void k_best(const double* __restrict__ C, int m, int n,
+                                                         const double* __restrict__ ainv,
+                                                         const Control* __restrict__ ctl, double* __restrict__ pv,
+                                                         long* __restrict__ pi) {
+  if (ctl->done) return;
+  __shared__ double rows[16][kChunk + 2];
+  __shared__ double sv[kRowWaves];
+  __shared__ long si[kRowWaves];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int row = lane & 15, kq = lane >> 4;
-  const int ci = i0 + row;
-  double best[4];
-  int bk[4];
+  double best = -1.0;
+  long at = 0x7FFFFFFFFFFFFFFFL;
+  const int tiles = (m + 15) / 16;
+  for (int tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+    const int i0 = tile * 16;
+    for (int c0 = 0; c0 < n; c0 += 16 * kColTiles * kRowWaves) {
+      const int cw = c0 + 16 * kColTiles * wave;  // first column of this wave
+      v4d acc[kColTiles];
 #pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    best[r] = -1.0;
-    bk[r] = 0x7FFFFFFF;
+      for (int t = 0; t < kColTiles; ++t) acc[t] = v4d{0.0, 0.0, 0.0, 0.0};
+      for (int k0 = 0; k0 < n; k0 += kChunk) {
+        const int kc = min(kChunk, n - k0), kr = (kc + 3) & ~3;  // rounded up: zeros
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < 16 / kRowWaves; ++q) {
+          const int r = wave * (16 / kRowWaves) + q;
+#pragma unroll
+          for (int h = 0; h < kChunk / 64; ++h) {
+            const int c = h * 64 + lane;
+            if (c < kr) rows[r][c] = (i0 + r < m && c < kc) ? C[(long)(i0 + r) * n + k0 + c] : 0.0;
+          }
+        }
+        __syncthreads();
+        if (cw < n) {
+#pragma unroll 8
+          for (int k = 0; k < kr; k += 4) {
+            const double av = rows[row][k + kq];
+            const long kk = min(k0 + k + kq, n - 1);  // past n the operand from C is zero
+#pragma unroll
+            for (int t = 0; t < kColTiles; ++t) {
+              const double bv = ainv[kk * n + min(cw + 16 * t + row, n - 1)];
+              // (not a product of zero and a copy of the last row: that one may be infinite)
+              acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(av, k0 + k + kq < n ? bv : 0.0, acc[t], 0, 0, 0);
+            }
+          }
+        }
+      }
+#pragma unroll
+      for (int t = 0; t < kColTiles; ++t) {
+        const int col = cw + 16 * t + row;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int i = i0 + 4 * r + kq;
+          // a NaN product counts as the largest magnitude, so that it is selected and reported
+          const double v = fabs(acc[t][r]);
+          if (col < n && i < m) keep_max(best, at, isnan(v) ? INFINITY : v, (long)i * n + col);
+        }
+      }
+    }
   }
-  for (int c0 = 0; c0 < n; c0 += 16) {
-    v4d acc = v4d{0.0, 0.0, 0.0, 0.0};
-    const int col = c0 + row;
-    for (int k0 = 0; k0 < n; k0 += 4) {
-      const int k = k0 + kq;
-      const double a = (ci < m && k < n) ? C[(long)ci * n + k] : 0.0;
-      const double b = (k < n && col < n) ? ainv[(long)k * n + col] : 0.0;
-      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc, 0, 0, 0);
-    }
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      // a NaN product counts as the largest magnitude, so that it is selected and reported
-      const double v = fabs(acc[r]);
-      if (col < n) keep_max(best[r], bk[r], isnan(v) ? INFINITY : v, col);
-    }
+  for (int s = 32; s > 0; s >>= 1) keep_max_across(best, at, s);
+  if (lane == 0) {
+    sv[wave] = best;
+    si[wave] = at;
   }
-  // rows 4 r + kq: reduce over the 16 lanes that share kq (the columns)
-#pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    double v = best[r];
-    int k = bk[r];
-#pragma unroll
-    for (int s = 8; s > 0; s >>= 1) {
-      const double v2 = __shfl_xor(v, s, 64);
-      const int k2 = __shfl_xor(k, s, 64);
-      keep_max(v, k, v2, k2);
-    }
-    const int out = i0 + 4 * r + kq;
-    if (row == 0 && out < m) {
-      rmax[out] = v;
-      rarg[out] = k;
-    }
-  }
-}
-
-// first row reaching the largest row maximum: per-part (value, row), then one workgroup
-__global__ __launch_bounds__(kNT) void k_argmax_part(const double* __restrict__ rmax, int m,
-                                                     double* __restrict__ pv, int* __restrict__ pi) {
-  __shared__ double sv[kNT];
-  __shared__ int si[kNT];
-  const long per = (m + kArgParts - 1) / kArgParts;
-  const long lo = (long)blockIdx.x * per, hi = min((long)m, lo + per);
-  double v = -1.0;
-  int id = 0x7FFFFFFF;
-  for (long i = lo + threadIdx.x; i < hi; i += kNT) keep_max(v, id, rmax[i], (int)i);
-  sv[threadIdx.x] = v;
-  si[threadIdx.x] = id;
   __syncthreads();
-  for (int s = kNT / 2; s > 0; s >>= 1) {
-    if (threadIdx.x < s) {
-      double a = sv[threadIdx.x];
-      int b = si[threadIdx.x];
-      keep_max(a, b, sv[threadIdx.x + s], si[threadIdx.x + s]);
-      sv[threadIdx.x] = a;
-      si[threadIdx.x] = b;
-    }
-    __syncthreads();
-  }
   if (threadIdx.x == 0) {
-    pv[blockIdx.x] = sv[0];
-    pi[blockIdx.x] = si[0];
+    for (int w = 1; w < kRowWaves; ++w) keep_max(best, at, sv[w], si[w]);
+    pv[blockIdx.x] = best;
+    pi[blockIdx.x] = at;
   }
 }
 
-// out: [0] = row i, [1] = column k (as doubles), [2] = g = (c_i Ainv)_k (signed).  Every row
-// holds a column in [0, n) (column 0 always competes), so i and k are in range; they are still
-// clamped, with g set to NaN, should that ever fail.
-__global__ __launch_bounds__(kNT) void k_argmax_final(const double* __restrict__ pv, const int* __restrict__ pi,
-                                                      const int* __restrict__ rarg, const double* __restrict__ C,
-                                                      int m, int n, const double* __restrict__ ainv,
-                                                      double* __restrict__ out) {
-  __shared__ double sv[kNT];
-  __shared__ int si[kNT];
-  __shared__ double sg[kNT];
+// One workgroup: the first largest entry over the parts, r = c_i Ainv - e_k (kSegments partial sums per
+// entry, added in order), the column Ainv[:, k], and the decision.  The selected index is in range
+// (entry (0, 0) always competes); it is still clamped, with g set to NaN, should that ever fail.
+__global__ __launch_bounds__(kSelThreads) void k_select(const double* __restrict__ pv, const long* __restrict__ pi,
+                                                        int parts, const double* __restrict__ C, int m, int n,
+                                                        const double* __restrict__ ainv, double limit,
+                                                        Control* __restrict__ ctl, Log* __restrict__ log,
+                                                        double* __restrict__ r, double* __restrict__ colk) {
+  if (ctl->done) return;
+  constexpr int W = kSelThreads / 64, COLS = kSelThreads / kSegments;
+  __shared__ double sv[W];
+  __shared__ long si[W];
+  __shared__ double seg[kSegments][COLS];
+  __shared__ double sg;
   double v = -1.0;
-  int id = 0x7FFFFFFF;
-  for (int t = threadIdx.x; t < kArgParts; t += kNT) keep_max(v, id, pv[t], pi[t]);
-  sv[threadIdx.x] = v;
-  si[threadIdx.x] = id;
+  long id = 0x7FFFFFFFFFFFFFFFL;
+  for (int t = threadIdx.x; t < parts; t += kSelThreads) keep_max(v, id, pv[t], pi[t]);
+#pragma unroll
+  for (int s = 32; s > 0; s >>= 1) keep_max_across(v, id, s);
+  if ((threadIdx.x & 63) == 0) {
+    sv[threadIdx.x >> 6] = v;
+    si[threadIdx.x >> 6] = id;
+  }
   __syncthreads();
-  for (int s = kNT / 2; s > 0; s >>= 1) {
-    if (threadIdx.x < s) {
-      double a = sv[threadIdx.x];
-      int b = si[threadIdx.x];
-      keep_max(a, b, sv[threadIdx.x + s], si[threadIdx.x + s]);
-      sv[threadIdx.x] = a;
-      si[threadIdx.x] = b;
-    }
-    __syncthreads();
-  }
-  const bool i_ok = si[0] >= 0 && si[0] < m;
-  const int i = i_ok ? si[0] : 0;
-  const bool k_ok = i_ok && rarg[i] >= 0 && rarg[i] < n;
-  const int k = k_ok ? rarg[i] : 0;
-  // signed g = sum_t C[i][t] Ainv[t][k], fixed-order tree over the threads
-  double part = 0.0;
-  for (int t = threadIdx.x; t < n; t += kNT) part = fma(C[(long)i * n + t], ainv[(long)t * n + k], part);
-  const double gs = block_sum<kNT>(part, sg);
-  const double g = k_ok ? gs : NAN;
-  if (threadIdx.x == 0) {
-    out[0] = (double)i;
-    out[1] = (double)k;
-    out[2] = g;
-  }
-}
-
-// r = c_i Ainv in LDS; Ainv -= Ainv[:, k] (r - e_k) / g; exchange rows A[k] and C[i].
-// One workgroup; the update of Ainv reads column k, which it also writes: the column is staged
-// in LDS first.
-__global__ __launch_bounds__(1024) void k_swap(double* __restrict__ C, double* __restrict__ A,
-                                               double* __restrict__ ainv, int n, const double* __restrict__ sel) {
-  extern __shared__ double sm[];  // r [n], column k of Ainv [n]
-  double* r = sm;
-  double* colk = sm + n;
-  const int i = (int)sel[0], k = (int)sel[1];
-  const double g = sel[2];
-  for (int j = threadIdx.x; j < n; j += blockDim.x) {
+  v = sv[0];
+  id = si[0];
+  for (int w = 1; w < W; ++w) keep_max(v, id, sv[w], si[w]);
+  const bool ok = id >= 0 && id < (long)m * n;
+  const int i = ok ? (int)(id / n) : 0, k = ok ? (int)(id % n) : 0;
+  const int part = threadIdx.x / COLS, col = threadIdx.x % COLS;
+  const int per = (n + kSegments - 1) / kSegments, lo = min(part * per, n), hi = min(lo + per, n);
+  for (int j0 = 0; j0 < n; j0 += COLS) {
+    const int j = j0 + col;
     double s = 0.0;
-    for (int t = 0; t < n; ++t) s = fma(C[(long)i * n + t], ainv[(long)t * n + j], s);
-    r[j] = s - (j == k ? 1.0 : 0.0);
-    colk[j] = ainv[(long)j * n + k];
+    if (j < n) {
+#pragma unroll 8
+      for (int t = lo; t < hi; ++t) s = fma(C[(long)i * n + t], ainv[(long)t * n + j], s);
+    }
+    seg[part][col] = s;
+    __syncthreads();
+    if (part == 0 && j < n) {
+      double sum = seg[0][col];
+      for (int q = 1; q < kSegments; ++q) sum += seg[q][col];
+      if (j == k) sg = sum;
+      r[j] = sum - (j == k ? 1.0 : 0.0);
+    }
+    __syncthreads();
   }
-  __syncthreads();
-  const double inv_g = 1.0 / g;
-  for (long idx = threadIdx.x; idx < (long)n * n; idx += blockDim.x) {
-    const int a = (int)(idx / n), b = (int)(idx % n);
-    ainv[idx] = ainv[idx] - colk[a] * (r[b] * inv_g);
-  }
-  for (int t = threadIdx.x; t < n; t += blockDim.x) {
-    const double x = A[(long)k * n + t];
-    A[(long)k * n + t] = C[(long)i * n + t];
-    C[(long)i * n + t] = x;
+  for (int j = threadIdx.x; j < n; j += kSelThreads) colk[j] = ainv[(long)j * n + k];
+  if (threadIdx.x == 0) {
+    const double g = ok ? sg : NAN;
+    ctl->i = i;
+    ctl->k = k;
+    ctl->g = g;
+    if (!isfinite(g)) {
+      ctl->done = 2;
+    } else if (!(fabs(g) > limit)) {
+      ctl->done = 1;
+    } else {
+      *log = Log{(double)i, (double)k, g};
+      ctl->swaps += 1;
+    }
   }
 }
+
+// Ainv -= Ainv[:, k] (r - e_k) / g, one workgroup per row; the first one exchanges rows A[k] and C[i].
+__global__ __launch_bounds__(128) void k_update(double* __restrict__ C, double* __restrict__ A,
+                                                double* __restrict__ ainv, int n, const Control* __restrict__ ctl,
+                                                const double* __restrict__ r, const double* __restrict__ colk) {
+  if (ctl->done) return;
+  const int a = blockIdx.x;
+  const double inv_g = 1.0 / ctl->g, f = colk[a];
+  for (int b = threadIdx.x; b < n; b += 128) ainv[(long)a * n + b] -= f * (r[b] * inv_g);
+  if (a == 0) {
+    const int i = ctl->i, k = ctl->k;
+    for (int t = threadIdx.x; t < n; t += 128) {
+      const double x = A[(long)k * n + t];
+      A[(long)k * n + t] = C[(long)i * n + t];
+      C[(long)i * n + t] = x;
+    }
+  }
+}
+
+__global__ void k_start(Control* ctl) { *ctl = Control{0, 0, 0, 0, 0.0}; }
 
 }  // namespace
 }  // namespace mtp
@@ -206,36 +239,49 @@ extern "C" int mtp_maxvol(mtp_model* m, double* cand, int n_cand, int n, double*
   if (!active || !ainv || (n_cand > 0 && !cand)) return mtp_fail(MTP_ERR_ARG, "null matrix");
   if (n_cand == 0 || max_swaps == 0) return MTP_OK;
   hipStream_t s = (hipStream_t)stream;
+  const int tiles = (int)(((long)n_cand + 15) / 16), parts = std::min(tiles, kMaxParts);
+  constexpr int kMostAhead = 32;  // iterations enqueued between two reads of the log
   int rc;
-  if ((rc = m->scratch.reserve((size_t)n_cand * 8 + (size_t)n_cand * 4 + kArgParts * 12 + 64))) return rc;
-  double* rmax = (double*)m->scratch.p;
-  int* rarg = (int*)(rmax + n_cand);
-  double* pv = (double*)((char*)m->scratch.p + (((size_t)n_cand * 12 + 15) & ~(size_t)15));
-  int* pi = (int*)(pv + kArgParts);
-  double* sel = (double*)(pi + kArgParts + (kArgParts & 1));
-  double host[3];
-  const int tiles = (n_cand + 15) / 16;
-  const int threads = n < 1024 ? ((n + 63) / 64) * 64 : 1024;
-  for (int it = 0; it < max_swaps; ++it) {
-    hipLaunchKernelGGL(k_rowmax, dim3((tiles + kRowWaves - 1) / kRowWaves), dim3(64 * kRowWaves), 0, s, cand,
-                       n_cand, n, ainv, rmax, rarg);
-    hipLaunchKernelGGL(k_argmax_part, dim3(kArgParts), dim3(kNT), 0, s, rmax, n_cand, pv, pi);
-    hipLaunchKernelGGL(k_argmax_final, dim3(1), dim3(kNT), 0, s, pv, pi, rarg, cand, n_cand, n, ainv, sel);
+  if ((rc = m->scratch.reserve((size_t)parts * 16 + (size_t)n * 16 + kMostAhead * sizeof(Log) + sizeof(Control))))
+    return rc;
+  double* pv = (double*)m->scratch.p;
+  long* pi = (long*)(pv + parts);
+  double* r = (double*)(pi + parts);
+  double* colk = r + n;
+  Log* log = (Log*)(colk + n);
+  Control* ctl = (Control*)(log + kMostAhead);
+  struct {
+    Log log[kMostAhead];
+    Control ctl;
+  } host;  // as laid out on the device
+  static_assert(sizeof(host) == kMostAhead * sizeof(Log) + sizeof(Control), "log and control are contiguous");
+  hipLaunchKernelGGL(k_start, dim3(1), dim3(1), 0, s, ctl);
+  int ahead = 4;
+  for (int it = 0; it < max_swaps;) {
+    const int batch = std::min(ahead, max_swaps - it);
+    for (int q = 0; q < batch; ++q) {
+      hipLaunchKernelGGL(k_best, dim3(parts), dim3(64 * kRowWaves), 0, s, cand, n_cand, n, ainv, ctl, pv, pi);
+      hipLaunchKernelGGL(k_select, dim3(1), dim3(kSelThreads), 0, s, pv, pi, parts, cand, n_cand, n, ainv, 1.0 + tol,
+                         ctl, log + q, r, colk);
+      hipLaunchKernelGGL(k_update, dim3(n), dim3(128), 0, s, cand, active, ainv, n, ctl, r, colk);
+    }
     if (hipGetLastError() != hipSuccess) return mtp_fail(MTP_ERR_HIP, "mtp_maxvol: launch failed");
-    if (hipMemcpyAsync(host, sel, sizeof(host), hipMemcpyDeviceToHost, s) != hipSuccess ||
+    if (hipMemcpyAsync(&host, log, sizeof(host), hipMemcpyDeviceToHost, s) != hipSuccess ||
         hipStreamSynchronize(s) != hipSuccess)
       return mtp_fail(MTP_ERR_HIP, "mtp_maxvol: reading the selection failed");
-    if (!std::isfinite(host[2]))
-      return mtp_fail(MTP_ERR_ARG, "mtp_maxvol: non-finite grade (candidates or inverse not finite)");
-    if (!(fabs(host[2]) > 1.0 + tol)) break;
-    hipLaunchKernelGGL(k_swap, dim3(1), dim3(threads), 2 * n * sizeof(double), s, cand, active, ainv, n, sel);
-    if (hipGetLastError() != hipSuccess) return mtp_fail(MTP_ERR_HIP, "mtp_maxvol: launch failed");
-    if (swaps) {
-      swaps[2 * it] = (int)host[0];
-      swaps[2 * it + 1] = (int)host[1];
+    for (int q = 0; it + q < host.ctl.swaps; ++q) {
+      if (swaps) {
+        swaps[2 * (it + q)] = (int)host.log[q].i;
+        swaps[2 * (it + q) + 1] = (int)host.log[q].k;
+      }
+      if (grades) grades[it + q] = host.log[q].g;
     }
-    if (grades) grades[it] = host[2];
-    *n_swaps = it + 1;
+    *n_swaps = host.ctl.swaps;
+    if (host.ctl.done == 2)
+      return mtp_fail(MTP_ERR_ARG, "mtp_maxvol: non-finite grade (candidates or inverse not finite)");
+    if (host.ctl.done) break;
+    it += batch;
+    ahead = std::min(2 * ahead, kMostAhead);
   }
   return MTP_OK;
 }

@@ -85,3 +85,16 @@ def test_maxvol_rejects_non_finite_candidates():
             pot.maxvol(C, A, Ai, tol=1e-3, max_swaps=10)
         torch.cuda.synchronize()
         np.testing.assert_array_equal(A.cpu().numpy(), active)
+
+
+@pytest.mark.parametrize("n,m,swaps", [(4, 40000, 60), (127, 33, 12), (128, 400, 3), (131, 17, 40), (260, 50, 9)])
+def test_maxvol_sizes_at_tile_edges(n, m, swaps):
+    """Column counts around the 128 staged at a time and the 128 a workgroup covers, rows not a
+    multiple of 16, more row tiles than workgroups, and swap limits inside and at the end of the
+    batches of iterations enqueued together."""
+    s, p = small_lattice(95, (2, 2, 2), 3.16, 0.05, 6, 1)
+    rng = np.random.default_rng(n + m)
+    active = np.eye(n) + 0.3 * rng.normal(size=(n, n)) / np.sqrt(n)
+    cand = rng.normal(size=(m, n))
+    got = _run(_pot(p), active, cand, 1e-3, swaps, f"edges n{n} m{m}")
+    assert 0 < len(got) <= swaps
