@@ -60,7 +60,11 @@ def _ngroups(lv):
 
 
 def _nrtparts(lv):
-    """Number of reverse-tangent parts of a generated level (read from its program header)."""
+    """Number of reverse-tangent kernels of a generated level: one where several waves share a tile,
+    else the parts of the one-lane program (read from its header)."""
+    from .codegen.waves import WAVES
+    if lv in WAVES:
+        return 1
     with open(os.path.join(GEN, f"mtp_L{lv}.inc")) as fh:
         for line in fh:
             if "static constexpr int NRTPART" in line:
@@ -80,7 +84,7 @@ def _assembly(lv):
                  "double, double*, double*, hipStream_t);")
     for g in range(_nrtparts(lv)):
         lines.append(f"void adj_rev_{lv}_{g}(const double*, const double*, long, int, const double*, "
-                     "const double*, double*, hipStream_t);")
+                     "const double*, const double*, double*, hipStream_t);")
     lines += [f"LevelOps level_ops_{lv}() {{", "  LevelOps o{};", f"  using L = Lv{lv};",
               "  o.level = L::LEVEL; o.nmom = L::NMOM; o.ncomp = L::NCOMP; o.nalpha = L::NALPHA;",
               "  o.nmu = L::NMU; o.maxnu = L::MAXNU; o.ngroup = L::NGROUP; o.triples = L::TRIPLES;",

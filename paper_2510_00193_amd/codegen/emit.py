@@ -25,6 +25,7 @@ from collections import defaultdict
 from fractions import Fraction
 
 from .program import Program, build_program
+from .waves import emit_waves
 
 
 def _lit(w) -> str:
@@ -549,7 +550,7 @@ def _emit_components_reverse(w: _W, prog: Program, groups):
             _emit_block_forward(w, blk, with_output=False)
             for k in range(blk.n_temp):
                 w(f"R tb{k} = R(0);")
-            _emit_block_reverse(w, blk, lo, hi)
+            _emit_block_reverse(w, blk, lambda ref: _adj(ref, lo, hi))
             w.pop()
             w("}")
         w.pop()
@@ -565,7 +566,8 @@ def _adj(ref, lo, hi):
     return "cb"
 
 
-def _emit_block_reverse(w: _W, blk, lo, hi):
+def _emit_block_reverse(w: _W, blk, adj):
+    """The block read backwards; adj names the adjoint of a reference (None: not accumulated)."""
     # walk steps backwards: ops were appended step by step
     rev_ops = list(reversed(blk.ops))
     # group by (dst, x) for x-adjoints and by (dst, y) for y-adjoints, in reverse step order
@@ -577,10 +579,10 @@ def _emit_block_reverse(w: _W, blk, lo, hi):
         by_dst[dst].append((x, y, wgt))
     for dst in seen_dst:
         lst = by_dst[dst]
-        db = _adj(dst, lo, hi)
+        db = adj(dst)
         if lst[0][1] is None:
             (x, _, _), = lst
-            tgt = _adj(x, lo, hi)
+            tgt = adj(x)
             if tgt:
                 w(f"{tgt} += {db};")
             continue
@@ -590,13 +592,13 @@ def _emit_block_reverse(w: _W, blk, lo, hi):
             xs.setdefault(x, []).append((y, wgt))
             ys.setdefault(y, []).append((x, wgt))
         for x, l2 in xs.items():
-            tgt = _adj(x, lo, hi)
+            tgt = adj(x)
             if not tgt:
                 continue
             _emit_inner(w, l2, "s")
             w(f"{tgt} = fma({db}, s, {tgt}); }}")
         for y, l2 in ys.items():
-            tgt = _adj(y, lo, hi)
+            tgt = adj(y)
             if not tgt:
                 continue
             _emit_inner(w, l2, "s")
@@ -707,6 +709,7 @@ def emit_level(level: int, n_groups: int = 1, rtan_budget: int = RTAN_REG_BUDGET
     _emit_products(w, prog)
     _emit_dispatchers(w, len(groups))
     emit_tangent_parts(w, prog, rparts)
+    emit_waves(w, prog)
     w.pop()
     w("};")
     return w.text()

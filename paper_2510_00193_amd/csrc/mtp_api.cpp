@@ -461,8 +461,8 @@ int run_energy_chain(mtp_model* m, const mtp_system* sys, const mtp_nlist& nl, d
       // energies and moment adjoints in one kernel
       {
         ProfScope ps(&m->prof, P_PROGRAM, s);
-        K.program(mom, ld, i0, cn, sys->species, (const double*)m->linear.p, (const double*)m->shift.p, m->nsp,
-                  e_atom, mbar, s);
+        K.program(mom, ld, i0, cn, nullptr, sys->species, (const double*)m->linear.p, (const double*)m->shift.p,
+                  m->nsp, e_atom, nullptr, mbar, s);
       }
       for (int g = 0; g < K.nbgroup; ++g) {
         ProfScope ps(&m->prof, P_BACKWARD, s);
@@ -478,9 +478,9 @@ int run_energy_chain(mtp_model* m, const mtp_system* sys, const mtp_nlist& nl, d
     }
     if (after_forward) after_forward(i0, cn);
     if (backward) {
-      for (int g = 0; g < L.ngroup; ++g) {
+      for (int g = 0; g < K.nrgroup; ++g) {
         ProfScope ps(&m->prof, P_PROG_REV, s);
-        K.prog_rev(g, mom, ld, cn, cbar, mbar, s);
+        K.prog_rev(g, mom, ld, cn, (const double*)m->linear.p, cbar, mbar, s);
       }
       for (int g = 0; g < K.nbgroup; ++g) {
         ProfScope ps(&m->prof, P_BACKWARD, s);
@@ -690,14 +690,22 @@ extern "C" int mtp_param_grad(mtp_model* m, const mtp_system* sys, const mtp_nli
       ProfScope ps(&m->prof, P_MOMENTS, s);
       L.chain[0].moments(g, a, i0, cn, mom, ld, s);
     }
-    {
-      ProfScope ps(&m->prof, P_PROG_FWD, s);
-      L.chain[0].prog_fwd(mom, ld, i0, cn, nullptr, sys->species, (const double*)m->linear.p,
-                          (const double*)m->shift.p, m->nsp, (double*)m->eatom.p, cbar, nullptr, s);
-    }
-    for (int g = 0; g < L.ngroup; ++g) {
-      ProfScope ps(&m->prof, P_PROG_REV, s);
-      L.chain[0].prog_rev(g, mom, ld, cn, cbar, mbar, s);
+    const ChainOps& C = L.chain[0];
+    const double* xi = (const double*)m->linear.p;
+    if (C.program && C.program_full) {
+      ProfScope ps(&m->prof, P_PROGRAM, s);
+      C.program(mom, ld, i0, cn, nullptr, sys->species, xi, (const double*)m->shift.p, m->nsp, (double*)m->eatom.p,
+                cbar, mbar, s);
+    } else {
+      {
+        ProfScope ps(&m->prof, P_PROG_FWD, s);
+        C.prog_fwd(mom, ld, i0, cn, nullptr, sys->species, xi, (const double*)m->shift.p, m->nsp,
+                   (double*)m->eatom.p, cbar, nullptr, s);
+      }
+      for (int g = 0; g < C.nrgroup; ++g) {
+        ProfScope ps(&m->prof, P_PROG_REV, s);
+        C.prog_rev(g, mom, ld, cn, xi, cbar, mbar, s);
+      }
     }
     {
       ProfScope ps(&m->prof, P_TANGENT, s);
@@ -709,7 +717,7 @@ extern "C" int mtp_param_grad(mtp_model* m, const mtp_system* sys, const mtp_nli
     }
     for (int g = 0; g < L.adj.nrtpart; ++g) {
       ProfScope ps(&m->prof, P_TANGENT, s);
-      L.adj.tan_reverse[g](mom, mdot, ld, cn, cbar, cbard, mbard, s);
+      L.adj.tan_reverse[g](mom, mdot, ld, cn, xi, cbar, cbard, mbard, s);
     }
     {
       ProfScope ps(&m->prof, P_ADJ_PAIRS, s);

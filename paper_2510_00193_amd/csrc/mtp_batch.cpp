@@ -208,6 +208,25 @@ static void run_impl(mtp_batch* b, const double* e_target, const double* f_targe
   double* wa = (double*)b->watom.p;
   double* g = (double*)b->g.p;
   double* wpart = (double*)b->wpart.p;
+  const double* xi = (const double*)m->linear.p;
+  // site energies, contraction and moment adjoints of a chunk
+  auto program = [&](int i0, int cn) {
+    if (K.program && K.program_full) {
+      ProfScope ps(&m->prof, P_PROGRAM, s);
+      K.program(b->mom.p, ld, i0, cn, a.perm, b->species, xi, (const double*)m->shift.p, m->nsp, ea, b->cbar.p, b->mbar.p,
+                s);
+      return;
+    }
+    {
+      ProfScope ps(&m->prof, P_PROG_FWD, s);
+      K.prog_fwd(b->mom.p, ld, i0, cn, a.perm, b->species, xi, (const double*)m->shift.p, m->nsp, ea, b->cbar.p, nullptr,
+                 s);
+    }
+    for (int gi = 0; gi < K.nrgroup; ++gi) {
+      ProfScope ps(&m->prof, P_PROG_REV, s);
+      K.prog_rev(gi, b->mom.p, ld, cn, xi, b->cbar.p, b->mbar.p, s);
+    }
+  };
   long blk = 0;
   // ---- forward: energies, pair gradients, per-atom virials
   for (long i0 = 0; i0 < n; i0 += ld) {
@@ -217,15 +236,7 @@ static void run_impl(mtp_batch* b, const double* e_target, const double* f_targe
       a.queue = q();
       K.moments(gi, a, (int)i0, cn, b->mom.p, ld, s);
     }
-    {
-      ProfScope ps(&m->prof, P_PROG_FWD, s);
-      K.prog_fwd(b->mom.p, ld, (int)i0, cn, a.perm, b->species, (const double*)m->linear.p,
-                 (const double*)m->shift.p, m->nsp, ea, b->cbar.p, nullptr, s);
-    }
-    for (int gi = 0; gi < L.ngroup; ++gi) {
-      ProfScope ps(&m->prof, P_PROG_REV, s);
-      K.prog_rev(gi, b->mom.p, ld, cn, b->cbar.p, b->mbar.p, s);
-    }
+    program((int)i0, cn);
     for (int gi = 0; gi < K.nbgroup; ++gi) {
       ProfScope ps(&m->prof, P_BACKWARD, s);
       a.queue = q();
@@ -278,15 +289,7 @@ static void run_impl(mtp_batch* b, const double* e_target, const double* f_targe
         a.queue = q();
         K.moments(gi, a, (int)i0, cn, b->mom.p, ld, s);
       }
-      {
-        ProfScope ps(&m->prof, P_PROG_FWD, s);
-        K.prog_fwd(b->mom.p, ld, (int)i0, cn, a.perm, b->species, (const double*)m->linear.p,
-                   (const double*)m->shift.p, m->nsp, ea, b->cbar.p, nullptr, s);
-      }
-    }
-    for (int gi = 0; ld < n && gi < L.ngroup; ++gi) {
-      ProfScope ps(&m->prof, P_PROG_REV, s);
-      K.prog_rev(gi, b->mom.p, ld, cn, b->cbar.p, b->mbar.p, s);
+      program((int)i0, cn);
     }
     {
       ProfScope ps(&m->prof, P_TANGENT, s);
@@ -296,11 +299,11 @@ static void run_impl(mtp_batch* b, const double* e_target, const double* f_targe
     {
       ProfScope ps(&m->prof, P_TANGENT, s);
       L.adj.tan_forward(a, (const double*)b->mom.p, (const double*)b->mdot.p, ld, (int)i0, cn,
-                    (const double*)m->linear.p, 0.0, (double*)b->xout.p, (double*)b->cbard.p, s);
+                    xi, 0.0, (double*)b->xout.p, (double*)b->cbard.p, s);
     }
     for (int gi = 0; gi < L.adj.nrtpart; ++gi) {
       ProfScope ps(&m->prof, P_TANGENT, s);
-      L.adj.tan_reverse[gi]((const double*)b->mom.p, (const double*)b->mdot.p, ld, cn, (const double*)b->cbar.p,
+      L.adj.tan_reverse[gi]((const double*)b->mom.p, (const double*)b->mdot.p, ld, cn, xi, (const double*)b->cbar.p,
                     (const double*)b->cbard.p, (double*)b->mbard.p, s);
     }
     {

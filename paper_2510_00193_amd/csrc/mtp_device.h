@@ -7,6 +7,15 @@
 // programs: it keeps the moment loads of a block from being hoisted above earlier blocks,
 // which would otherwise make every moment live at once and spill registers.
 #define MTP_BLOCK_FENCE() __builtin_amdgcn_sched_barrier(0)
+// also ends the life of values read from LDS before it: they are read again rather than kept (in
+// registers, then in scratch) for a later block
+#define MTP_TILE_FENCE()                  \
+  do {                                    \
+    asm volatile("" ::: "memory");        \
+    __builtin_amdgcn_sched_barrier(0);    \
+  } while (0)
+// a value the compiler may not recognise as the one it was (an expression of it is formed again)
+#define MTP_PIN(x) asm volatile("" : "+v"(x))
 
 namespace mtp {
 

@@ -44,17 +44,21 @@ struct ChainOps {
   void (*prog_fwd)(const void* m, long ld, int i0, int n, const int* perm, const int* species,
                    const double* xi, const double* shift, int nsp, double* e_atom, void* cbar,
                    double* bout, hipStream_t s);
-  void (*prog_rev)(int g, const void* m, long ld, int n, const void* cb, void* mb, hipStream_t s);
+  // cb: what prog_fwd or program left (rows of the components, or of those whose adjoints do not follow
+  // from xi alone)
+  void (*prog_rev)(int g, const void* m, long ld, int n, const double* xi, const void* cb, void* mb, hipStream_t s);
   // passes grp = 0 (stores), 1, ... (add) over the pairs, in order on one stream
   // fown (optional, [atom][3]): (+)= the atom's own pair-gradient sum, for launch_gather_forces
   void (*backward)(int grp, const SysArgs& a, int i0, int n, const void* mb, long ld, double* g,
                    double* wpart, double* watom, double* fown, hipStream_t s);
-  // forward + products + reverse in one kernel (single-group levels, one system; else null):
-  // writes e_atom[i0 + k] and the moment adjoints
-  void (*program)(const void* m, long ld, int i0, int n, const int* species, const double* xi,
-                  const double* shift, int nsp, double* e_atom, void* mb, hipStream_t s);
+  // forward + products + reverse in one kernel (else null): writes e_atom of the chunk's atoms and the
+  // moment adjoints; with program_full also for a permuted order (perm, or null), and cbar when not null
+  void (*program)(const void* m, long ld, int i0, int n, const int* perm, const int* species, const double* xi,
+                  const double* shift, int nsp, double* e_atom, void* cbar, void* mb, hipStream_t s);
+  bool program_full;
   int nmgroup;  // launches of moments (g < nmgroup)
   int nbgroup;  // passes of backward (grp < nbgroup), each over a range of the moment adjoints
+  int nrgroup;  // launches of prog_rev (g < nrgroup)
 };
 
 // Parameter-adjoint launchers of one level (binary64).
@@ -64,8 +68,8 @@ struct AdjOps {
                       const double* xi, double ebar, double* out, double* cbard, hipStream_t s);
   // one launcher per part of the reverse-tangent program (compiled in separate units); the
   // parts store or add their entries of mbd and run in order 0 .. nrtpart - 1 on one stream
-  void (*tan_reverse[kMaxRevParts])(const double* m, const double* md, long ld, int n, const double* cb,
-                                    const double* cbd, double* mbd, hipStream_t s);
+  void (*tan_reverse[kMaxRevParts])(const double* m, const double* md, long ld, int n, const double* xi,
+                                    const double* cb, const double* cbd, double* mbd, hipStream_t s);
   int nrtpart;
   // adj_pairs leaves a record of `record` doubles per pair (indexed by the list), adj_radial sums the
   // records of atoms 0 .. n - 1 into cpart [split_tiles(n, a.split)][nsp * nsp * nmu * ncheb]

@@ -566,6 +566,242 @@ __global__ __launch_bounds__(kLaneBlock) void k_program(const R* __restrict__ mo
   for (int e = 0; e < L::NMOM; ++e) mbar[(long)e * ld + li] = mb[e];
 }
 
+// ---------------------------------------------------------------------------- wave programs
+// Levels from 12 on in binary64: a workgroup runs the contraction program of one tile of 64 atoms on
+// several waves, each a part of the contraction blocks.  The moments that two blocks or more read are
+// staged in LDS once ([row][atom]).  With one lane running the whole program the re-reads of shared
+// moments missed L2 (twice the moments fetched at level 16, 5 times at level 20) and the single wave
+// of a SIMD stood waiting for them four fifths of its time at level 20, where the contraction values
+// and adjoints of 160 components also went to scratch (up to 8.9 KB per lane).  Now the arithmetic is
+// half to three quarters of a tile's time, waits for LDS most of the rest.  Measured before -> after, us:
+//   level 16: 1008 atoms 20 -> 12.9 (both programs); 1,024,000 atoms 742 -> 693
+//   level 20: 31,416 atoms 385 -> 130 (forward 42, reverse 88)
+//   level 20, 540,480 atoms in a batch: forward 2200 -> 650, reverse 2460 -> 1500, tangent of the forward
+//   6200 -> 1510, of the reverse 8100 -> 4870
+// Two waves (level 12) and four (14, 16) keep two workgroups or more on a compute unit; at level 20 the
+// rows fill its LDS, so eight waves run the forward programs, and four of 512 registers the reverse ones,
+// whose accumulators eight of 256 would spill.
+
+// Moment of the lane's atom: LDS row or, for a moment that one block reads, memory.
+template <class L, bool TANGENT>
+struct TileMoments {
+  const double* lds;  // row 0 of the lane
+  const double* __restrict__ base;
+  long ld;
+  unsigned off;
+  __device__ __forceinline__ double operator()(int e) const {
+    const int row = TANGENT ? L::THOT_ROW[e] : L::HOT_ROW[e];
+    if (row >= 0) return lds[row * kLaneBlock];
+    return *reinterpret_cast<const double*>(reinterpret_cast<const char*>(base + (long)e * ld) + off);
+  }
+};
+// Row e of a [row][atom] array: stores, loads.
+struct RowStore {
+  double* __restrict__ base;
+  long ld;
+  unsigned off;
+  __device__ __forceinline__ void operator()(int e, double v) const {
+    *reinterpret_cast<double*>(reinterpret_cast<char*>(base + (long)e * ld) + off) = v;
+  }
+};
+struct RowLoad {
+  const double* __restrict__ base;
+  long ld;
+  unsigned off;
+  __device__ __forceinline__ double operator()(int e) const {
+    return *reinterpret_cast<const double*>(reinterpret_cast<const char*>(base + (long)e * ld) + off);
+  }
+};
+struct LdsRows {
+  double* p;
+  __device__ __forceinline__ double operator()(int g) const { return p[g * kLaneBlock]; }
+  __device__ __forceinline__ void operator()(int g, double v) const { p[g * kLaneBlock] = v; }
+};
+// both an LDS row (for the reverse program of the same launch) and a row in memory (for the adjoint)
+struct LdsAndRow {
+  LdsRows lds;
+  RowStore row;
+  bool keep;
+  __device__ __forceinline__ void operator()(int g, double v) const {
+    lds(g, v);
+    if (keep) row(g, v);
+  }
+};
+
+// Tile of the workgroup; lane: bytes of the lane's atom in a row, of LDS as of an array from the tile's
+// first atom on (one register for both).  Lanes past the last atom repeat it: they read, compute and
+// store what its own lane does.
+struct Tile {
+  int wave, first;
+  unsigned lane;
+};
+__device__ __forceinline__ Tile tile_of(int n) {
+  Tile t;
+  t.wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kLaneBlock);
+  t.first = xcd_logical_block(blockIdx.x, gridDim.x) * kLaneBlock;
+  t.lane = lane_bytes(min((int)threadIdx.x & (kLaneBlock - 1), n - 1 - t.first), sizeof(double));
+  return t;
+}
+__device__ __forceinline__ double* lane_ptr(double* p, unsigned lane) {
+  return reinterpret_cast<double*>(reinterpret_cast<char*>(p) + lane);
+}
+
+// f(constant<W>, LDS pointer of the lane, lane) for the wave's number.  The lane's offset is made anew
+// for each part: known from before it, its 64-bit form was what the register allocator kept, spilled and read
+// back for every row (reverse tangent of level 20, 540480 atoms: 8.9 -> 4.9 ms, with its loads one
+// block ahead instead of at the start).
+template <int N, int W = 0, class F>
+__device__ __forceinline__ void for_wave(const Tile& t, double* sm, F&& f) {
+  if constexpr (W < N) {
+    if (t.wave == W) {
+      unsigned lane = t.lane;
+      MTP_PIN(lane);
+      f(std::integral_constant<int, W>{}, lane_ptr(sm, lane), lane);
+    } else {
+      for_wave<N, W + 1>(t, sm, f);
+    }
+  }
+}
+
+// rows [entry[0..count)] of src for the lane's atom to LDS rows 0, 1, ... (the waves share the rows)
+template <int COUNT, int NW>
+__device__ __forceinline__ void stage_moments(const int (&entry)[COUNT], int wave, const double* __restrict__ src,
+                                              long ld, unsigned off, double* lds) {
+#pragma unroll 8
+  for (int r = wave; r < COUNT; r += NW)
+    lds[r * kLaneBlock] =
+        *reinterpret_cast<const double*>(reinterpret_cast<const char*>(src + (long)entry[r] * ld) + off);
+}
+
+// between two phases of a tile (the waves of a workgroup exchange data through LDS only)
+__device__ __forceinline__ void step_barrier() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt 0; vector memory operations stay in flight
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
+// Reverse phase: the blocks of the wave, then the entries that several waves touch added in wave order
+// through the LDS rows the moments no longer need.
+template <class L, int W, class MA, class CB>
+__device__ __forceinline__ void reverse_wave(const MA& M, const CB& cb, const double* __restrict__ xi, double* lds,
+                                             const RowStore& out) {
+  double mbs[L::SHARED[W] > 0 ? L::SHARED[W] : 1];
+  L::template rev_wave<W>(M, cb, xi, mbs, out);
+  step_barrier();
+#pragma unroll
+  for (int k = 0; k < W; ++k) step_barrier();
+  L::template rev_combine<W>(mbs, lds, out);
+#pragma unroll
+  for (int k = W + 1; k < L::NRWAVE; ++k) step_barrier();
+}
+
+// Four waves hold the accumulators of level 20 in 512 registers each; otherwise two waves per SIMD.
+template <class L>
+constexpr int wave_occupancy(int waves) { return waves == 4 && L::NMOM > 200 ? 1 : 2; }
+
+template <class L, bool WB>
+__global__ __launch_bounds__(kLaneBlock * L::NFWAVE) __attribute__((amdgpu_waves_per_eu(2)))
+void k_wave_forward(const double* __restrict__ mom, long ld, int i0, int n, const int* __restrict__ perm,
+                    const int* __restrict__ species, const double* __restrict__ xi, const double* __restrict__ shift,
+                    int nsp, double* __restrict__ e_atom, double* __restrict__ cbar, double* __restrict__ bout) {
+  constexpr int NW = L::NFWAVE, CROW = L::NHOT, PROW = CROW + L::NGEN;
+  __shared__ double sm[(PROW + 2 * NW) * kLaneBlock];
+  const Tile t = tile_of(n);
+  double* lds = lane_ptr(sm, t.lane);
+  stage_moments<L::NHOT, NW>(L::HOT_ENTRY, t.wave, mom + t.first, ld, t.lane, lds);
+  double e = 0.0, c0b = 0.0;
+  step_barrier();
+  for_wave<NW>(t, sm, [&](auto w, double* p, unsigned lane) {
+    L::template fwd_wave<decltype(w)::value, WB>(TileMoments<L, false>{p, mom + t.first, ld, lane}, xi,
+                                                 p + CROW * kLaneBlock, WB ? lane_ptr(bout + t.first, lane) : nullptr,
+                                                 ld, e, c0b);
+  });
+  step_barrier();
+  for_wave<NW>(t, sm, [&](auto w, double* p, unsigned lane) {
+    L::template core_wave<decltype(w)::value, WB>(TileMoments<L, false>{p, mom + t.first, ld, lane}, xi,
+                                                  p + CROW * kLaneBlock, RowStore{cbar + t.first, ld, lane},
+                                                  WB ? lane_ptr(bout + t.first, lane) : nullptr, ld, e, c0b);
+  });
+  lds[(PROW + t.wave) * kLaneBlock] = e;
+  lds[(PROW + NW + t.wave) * kLaneBlock] = c0b;
+  step_barrier();
+  if (t.wave == 0) {
+#pragma unroll
+    for (int k = 1; k < NW; ++k) {
+      e += lds[(PROW + k) * kLaneBlock];
+      c0b += lds[(PROW + NW + k) * kLaneBlock];
+    }
+    const int li = t.first + (int)(t.lane / sizeof(double)), i = perm ? perm[i0 + li] : i0 + li;
+    e_atom[i] = e + shift[clamp_species(species[i], nsp)];
+    RowStore{cbar + t.first, ld, t.lane}(L::GEN0, c0b);
+  }
+}
+
+template <class L>
+__global__ __launch_bounds__(kLaneBlock * L::NRWAVE)
+__attribute__((amdgpu_waves_per_eu(wave_occupancy<L>(L::NRWAVE))))
+void k_wave_reverse(const double* __restrict__ mom, long ld, int n, const double* __restrict__ xi,
+                    const double* __restrict__ cbar, double* __restrict__ mbar) {
+  constexpr int ROWS = L::NHOT > L::SHARED_ROWS ? L::NHOT : L::SHARED_ROWS;
+  __shared__ double sm[ROWS * kLaneBlock];
+  const Tile t = tile_of(n);
+  double* lds = lane_ptr(sm, t.lane);
+  stage_moments<L::NHOT, L::NRWAVE>(L::HOT_ENTRY, t.wave, mom + t.first, ld, t.lane, lds);
+  step_barrier();
+  for_wave<L::NRWAVE>(t, sm, [&](auto w, double* p, unsigned lane) {
+    reverse_wave<L, decltype(w)::value>(TileMoments<L, false>{p, mom + t.first, ld, lane},
+                                        RowLoad{cbar + t.first, ld, lane}, xi, p, RowStore{mbar + t.first, ld, lane});
+  });
+}
+
+// Forward and reverse of a tile in one launch (levels whose forward and reverse programs take the same
+// number of waves): the moments stay in LDS between the two, and so do the general contractions'
+// adjoints (also stored to cbar when given).
+template <class L>
+__global__ __launch_bounds__(kLaneBlock * L::NFWAVE) __attribute__((amdgpu_waves_per_eu(2)))
+void k_wave_program(const double* __restrict__ mom, long ld, int i0, int n, const int* __restrict__ perm,
+                    const int* __restrict__ species, const double* __restrict__ xi, const double* __restrict__ shift,
+                    int nsp, double* __restrict__ e_atom, double* __restrict__ cbar, double* __restrict__ mbar) {
+  constexpr int NW = L::NFWAVE, CROW = L::NHOT, BROW = CROW + L::NGEN, PROW = BROW + L::NGEN;
+  static_assert(L::NFWAVE == L::NRWAVE && L::SHARED_ROWS <= PROW, "one launch for both programs");
+  __shared__ double sm[(PROW + 2 * NW) * kLaneBlock];
+  const Tile t = tile_of(n);
+  double* lds = lane_ptr(sm, t.lane);
+  stage_moments<L::NHOT, NW>(L::HOT_ENTRY, t.wave, mom + t.first, ld, t.lane, lds);
+  const long first = cbar ? t.first : 0;  // no offset to a null pointer
+  double e = 0.0, c0b = 0.0;
+  step_barrier();
+  for_wave<NW>(t, sm, [&](auto w, double* p, unsigned lane) {
+    L::template fwd_wave<decltype(w)::value, false>(TileMoments<L, false>{p, mom + t.first, ld, lane}, xi,
+                                                    p + CROW * kLaneBlock, nullptr, ld, e, c0b);
+  });
+  step_barrier();
+  for_wave<NW>(t, sm, [&](auto w, double* p, unsigned lane) {
+    const LdsAndRow cb{LdsRows{p + BROW * kLaneBlock}, RowStore{cbar + first, ld, lane}, cbar != nullptr};
+    L::template core_wave<decltype(w)::value, false>(TileMoments<L, false>{p, mom + t.first, ld, lane}, xi,
+                                                     p + CROW * kLaneBlock, cb, nullptr, ld, e, c0b);
+  });
+  lds[(PROW + t.wave) * kLaneBlock] = e;
+  lds[(PROW + NW + t.wave) * kLaneBlock] = c0b;
+  step_barrier();
+  if (t.wave == 0) {
+#pragma unroll
+    for (int k = 1; k < NW; ++k) {
+      e += lds[(PROW + k) * kLaneBlock];
+      c0b += lds[(PROW + NW + k) * kLaneBlock];
+    }
+    const int li = t.first + (int)(t.lane / sizeof(double)), i = perm ? perm[i0 + li] : i0 + li;
+    e_atom[i] = e + shift[clamp_species(species[i], nsp)];
+    LdsAndRow{LdsRows{lds + BROW * kLaneBlock}, RowStore{cbar + first, ld, t.lane}, cbar != nullptr}(L::GEN0, c0b);
+  }
+  step_barrier();
+  for_wave<NW>(t, sm, [&](auto w, double* p, unsigned lane) {
+    reverse_wave<L, decltype(w)::value>(TileMoments<L, false>{p, mom + t.first, ld, lane}, LdsRows{p + BROW * kLaneBlock},
+                                        xi, p, RowStore{mbar + t.first, ld, lane});
+  });
+}
+
 // ---------------------------------------------------------------------------- backward pairs
 // The end of a pair-gradient tile: per-atom virials (batches), the atoms' own gradient sums and the
 // workgroup's virial partial.  With ADD (a later pass over the pairs) everything is added to.
@@ -700,14 +936,6 @@ struct StageSlots {
   static constexpr int WIDTH = 3 + L::NMU_SHARED;  // 16-byte fields: (dx, dy) (dz, gx) (gy, gz) (f, h) ...
   double2 v[L::NPART][WIDTH][kLaneBlock];
 };
-
-// between two steps: this wave's LDS writes are done, then every wave of the workgroup arrives
-__device__ __forceinline__ void step_barrier() {
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt 0; vector memory operations stay in flight
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");
-}
 
 // First stage (part NPART - 1): T steps.
 template <class L, bool BATCH, int NC, int K>
@@ -938,6 +1166,87 @@ __global__ __launch_bounds__(kLaneBlock) void k_tan_reverse(const double* __rest
     }
     L::template rev_tan<P, double>(M, Md, Cb, Cbd, LaneRows<double>{mbard, lo}, ld);
   }
+}
+
+// The same by several waves per tile (see the wave programs above): moments and tangents of the entries
+// most blocks read in LDS.  out[alpha] = ebar B_alpha - dB_alpha; cbard: rows of the general
+// contractions.
+template <class L>
+__global__ __launch_bounds__(kLaneBlock * L::NTFWAVE) __attribute__((amdgpu_waves_per_eu(2)))
+void k_wave_tan_forward(const double* __restrict__ mom, const double* __restrict__ mdot, long ld, int i0, int n,
+                        const int* __restrict__ perm, const int* __restrict__ cfg,
+                        const double* __restrict__ ebar_cfg, const double* __restrict__ xi, double ebar,
+                        double* __restrict__ out, double* __restrict__ cbard) {
+  constexpr int NW = L::NTFWAVE, DROW = L::NTHOT, CROW = 2 * L::NTHOT, PROW = CROW + 2 * L::NGEN;
+  __shared__ double sm[(PROW + NW) * kLaneBlock];
+  const Tile t = tile_of(n);
+  double* lds = lane_ptr(sm, t.lane);
+  stage_moments<L::NTHOT, NW>(L::THOT_ENTRY, t.wave, mom + t.first, ld, t.lane, lds);
+  stage_moments<L::NTHOT, NW>(L::THOT_ENTRY, t.wave, mdot + t.first, ld, t.lane, lds + DROW * kLaneBlock);
+  if (ebar_cfg) {
+    const int li = t.first + (int)(t.lane / sizeof(double)), i = perm ? perm[i0 + li] : i0 + li;
+    ebar = ebar_cfg[cfg ? cfg[i] : 0];
+  }
+  double c0bd = 0.0;
+  step_barrier();
+  for_wave<NW>(t, sm, [&](auto w, double* p, unsigned lane) {
+    double* crow = p + CROW * kLaneBlock;
+    L::template tfwd_wave<decltype(w)::value>(
+        TileMoments<L, true>{p, mom + t.first, ld, lane},
+        TileMoments<L, true>{p + DROW * kLaneBlock, mdot + t.first, ld, lane}, xi, ebar, crow,
+        crow + L::NGEN * kLaneBlock, LaneRows<double>{out + t.first, lane}, ld, c0bd);
+  });
+  step_barrier();
+  for_wave<NW>(t, sm, [&](auto w, double* p, unsigned lane) {
+    double* crow = p + CROW * kLaneBlock;
+    L::template tcore_wave<decltype(w)::value>(
+        TileMoments<L, true>{p, mom + t.first, ld, lane},
+        TileMoments<L, true>{p + DROW * kLaneBlock, mdot + t.first, ld, lane}, xi, ebar, crow,
+        crow + L::NGEN * kLaneBlock, RowStore{cbard + t.first, ld, lane}, LaneRows<double>{out + t.first, lane}, ld,
+        c0bd);
+  });
+  lds[(PROW + t.wave) * kLaneBlock] = c0bd;
+  step_barrier();
+  if (t.wave == 0) {
+#pragma unroll
+    for (int k = 1; k < NW; ++k) c0bd += lds[(PROW + k) * kLaneBlock];
+    RowStore{cbard + t.first, ld, t.lane}(L::GEN0, c0bd);
+  }
+}
+
+template <class L, int W, class MA>
+__device__ __forceinline__ void tangent_reverse_wave(const MA& M, const MA& Md, const RowLoad& cb, const RowLoad& cbd,
+                                                     const double* __restrict__ xi, double* lds, const RowStore& out) {
+  double mbs[L::TSHARED[W] > 0 ? L::TSHARED[W] : 1];
+  L::template trev_wave<W>(M, Md, cb, cbd, xi, mbs, out);
+  step_barrier();
+#pragma unroll
+  for (int k = 0; k < W; ++k) step_barrier();
+  L::template trev_combine<W>(mbs, lds, out);
+#pragma unroll
+  for (int k = W + 1; k < L::NTRWAVE; ++k) step_barrier();
+}
+
+template <class L>
+__global__ __launch_bounds__(kLaneBlock * L::NTRWAVE)
+__attribute__((amdgpu_waves_per_eu(wave_occupancy<L>(L::NTRWAVE))))
+void k_wave_tan_reverse(const double* __restrict__ mom, const double* __restrict__ mdot, long ld, int n,
+                        const double* __restrict__ xi, const double* __restrict__ cbar,
+                        const double* __restrict__ cbard, double* __restrict__ mbard) {
+  constexpr int NW = L::NTRWAVE, DROW = L::NTHOT;
+  constexpr int ROWS = 2 * L::NTHOT > L::TSHARED_ROWS ? 2 * L::NTHOT : L::TSHARED_ROWS;
+  __shared__ double sm[ROWS * kLaneBlock];
+  const Tile t = tile_of(n);
+  double* lds = lane_ptr(sm, t.lane);
+  stage_moments<L::NTHOT, NW>(L::THOT_ENTRY, t.wave, mom + t.first, ld, t.lane, lds);
+  stage_moments<L::NTHOT, NW>(L::THOT_ENTRY, t.wave, mdot + t.first, ld, t.lane, lds + DROW * kLaneBlock);
+  step_barrier();
+  for_wave<NW>(t, sm, [&](auto w, double* p, unsigned lane) {
+    tangent_reverse_wave<L, decltype(w)::value>(TileMoments<L, true>{p, mom + t.first, ld, lane},
+                                                TileMoments<L, true>{p + DROW * kLaneBlock, mdot + t.first, ld, lane},
+                                                RowLoad{cbar + t.first, ld, lane}, RowLoad{cbard + t.first, ld, lane},
+                                                xi, p, RowStore{mbard + t.first, ld, lane});
+  });
 }
 
 // Radial-coefficient gradient: per pair (i, j) with species (s, t),
@@ -1308,15 +1617,31 @@ struct EnergyChain {
   static void moments(int g, const SysArgs& a, int i0, int n, void* m, long ld, hipStream_t s) {
     dispatch_moments<L, R, BATCH>(g, a, i0, n, m, ld, s, std::make_index_sequence<nmgroup()>{});
   }
+  static constexpr bool waves() { return std::is_same_v<R, double> && L::WAVES; }
+  static constexpr bool one_launch() { return waves() ? L::NFWAVE == L::NRWAVE : L::NGROUP == 1 && !BATCH; }
   static void prog_fwd(const void* m, long ld, int i0, int n, const int* perm, const int* species,
                        const double* xi, const double* shift, int nsp, double* e_atom, void* cbar,
                        double* bout, hipStream_t s) {
     const int nb = (n + kLaneBlock - 1) / kLaneBlock;
-    hipLaunchKernelGGL((k_program_fwd<L, R>), dim3(nb), dim3(kLaneBlock), 0, s, (const R*)m, ld, i0, n,
-                       perm, species, xi, shift, nsp, e_atom, (R*)cbar, bout);
+    if constexpr (waves()) {
+      const dim3 nt(kLaneBlock * L::NFWAVE);
+      if (bout)
+        hipLaunchKernelGGL((k_wave_forward<L, true>), dim3(nb), nt, 0, s, (const double*)m, ld, i0, n, perm, species, xi,
+                           shift, nsp, e_atom, (double*)cbar, bout);
+      else
+        hipLaunchKernelGGL((k_wave_forward<L, false>), dim3(nb), nt, 0, s, (const double*)m, ld, i0, n, perm, species, xi,
+                           shift, nsp, e_atom, (double*)cbar, bout);
+    } else {
+      hipLaunchKernelGGL((k_program_fwd<L, R>), dim3(nb), dim3(kLaneBlock), 0, s, (const R*)m, ld, i0, n,
+                         perm, species, xi, shift, nsp, e_atom, (R*)cbar, bout);
+    }
   }
-  static void prog_rev(int g, const void* m, long ld, int n, const void* cb, void* mb, hipStream_t s) {
-    dispatch_rev<L, R>(g, m, ld, n, cb, mb, s, std::make_index_sequence<L::NGROUP>{});
+  static void prog_rev(int g, const void* m, long ld, int n, const double* xi, const void* cb, void* mb, hipStream_t s) {
+    if constexpr (waves())
+      hipLaunchKernelGGL((k_wave_reverse<L>), dim3((n + kLaneBlock - 1) / kLaneBlock), dim3(kLaneBlock * L::NRWAVE), 0, s,
+                         (const double*)m, ld, n, xi, (const double*)cb, (double*)mb);
+    else
+      dispatch_rev<L, R>(g, m, ld, n, cb, mb, s, std::make_index_sequence<L::NGROUP>{});
   }
   static void backward(int grp, const SysArgs& a, int i0, int n, const void* mb, long ld, double* gout,
                        double* wpart, double* watom, double* fown, hipStream_t s) {
@@ -1327,17 +1652,19 @@ struct EnergyChain {
   static constexpr int nmgroup() { return std::is_same_v<R, double> ? 1 : L::NGROUP; }
   // passes of the pair-gradient kernel over the pairs
   static constexpr int nbgroup() { return std::is_same_v<R, double> ? 1 : L::NGROUP; }
-  static void program(const void* m, long ld, int i0, int n, const int* species, const double* xi,
-                      const double* shift, int nsp, double* e_atom, void* mb, hipStream_t s) {
-    if constexpr (L::NGROUP == 1) {
-      const int nb = (n + kLaneBlock - 1) / kLaneBlock;
+  static void program(const void* m, long ld, int i0, int n, const int* perm, const int* species, const double* xi,
+                      const double* shift, int nsp, double* e_atom, void* cbar, void* mb, hipStream_t s) {
+    const int nb = (n + kLaneBlock - 1) / kLaneBlock;
+    if constexpr (one_launch() && waves())
+      hipLaunchKernelGGL((k_wave_program<L>), dim3(nb), dim3(kLaneBlock * L::NFWAVE), 0, s, (const double*)m, ld, i0, n,
+                         perm, species, xi, shift, nsp, e_atom, (double*)cbar, (double*)mb);
+    else if constexpr (one_launch())
       hipLaunchKernelGGL((k_program<L, R>), dim3(nb), dim3(kLaneBlock), 0, s, (const R*)m, ld, i0, n, species, xi,
                          shift, nsp, e_atom, (R*)mb);
-    }
   }
   static ChainOps ops() {
-    return ChainOps{&moments, &prog_fwd, &prog_rev, &backward, L::NGROUP == 1 && !BATCH ? &program : nullptr,
-                    nmgroup(), nbgroup()};
+    return ChainOps{&moments, &prog_fwd, &prog_rev, &backward, one_launch() ? &program : nullptr, waves(), nmgroup(),
+                    nbgroup(), waves() ? 1 : L::NGROUP};
   }
 };
 
@@ -1365,14 +1692,22 @@ struct AdjImpl {
   static void tan_forward(const SysArgs& a, const double* m, const double* md, long ld, int i0, int n,
                           const double* xi, double ebar, double* out, double* cbard, hipStream_t s) {
     const int nb = (n + kLaneBlock - 1) / kLaneBlock;
-    hipLaunchKernelGGL((k_tan_forward<L>), dim3(nb), dim3(kLaneBlock), 0, s, m, md, ld, i0, n, a.perm, a.cfg,
-                       a.ebar, xi, ebar, out, cbard);
+    if constexpr (L::WAVES)
+      hipLaunchKernelGGL((k_wave_tan_forward<L>), dim3(nb), dim3(kLaneBlock * L::NTFWAVE), 0, s, m, md, ld, i0, n, a.perm,
+                         a.cfg, a.ebar, xi, ebar, out, cbard);
+    else
+      hipLaunchKernelGGL((k_tan_forward<L>), dim3(nb), dim3(kLaneBlock), 0, s, m, md, ld, i0, n, a.perm, a.cfg,
+                         a.ebar, xi, ebar, out, cbard);
   }
   template <int P>
-  static void tan_reverse_g(const double* m, const double* md, long ld, int n, const double* cb,
+  static void tan_reverse_g(const double* m, const double* md, long ld, int n, const double* xi, const double* cb,
                             const double* cbd, double* mbd, hipStream_t s) {
     const int nb = (n + kLaneBlock - 1) / kLaneBlock;
-    hipLaunchKernelGGL((k_tan_reverse<L, P>), dim3(nb), dim3(kLaneBlock), 0, s, m, md, ld, n, cb, cbd, mbd);
+    if constexpr (L::WAVES)
+      hipLaunchKernelGGL((k_wave_tan_reverse<L>), dim3(nb), dim3(kLaneBlock * L::NTRWAVE), 0, s, m, md, ld, n, xi, cb, cbd,
+                         mbd);
+    else
+      hipLaunchKernelGGL((k_tan_reverse<L, P>), dim3(nb), dim3(kLaneBlock), 0, s, m, md, ld, n, cb, cbd, mbd);
   }
   template <bool PERSIST, int K>
   static void adj_pairs_k(const SysArgs& a, const double* fbar, int i0, int n, const double* mb, const double* mbd,
@@ -1401,8 +1736,8 @@ struct AdjImpl {
     o.adj_pairs = &adj_pairs;
     o.adj_radial = &adj_radial;
     o.record = adj_record<L::NMU>();
-    o.nrtpart = L::NRTPART;
-    static_assert(L::NRTPART <= kMaxRevParts, "reverse-tangent parts");
+    o.nrtpart = L::WAVES ? 1 : L::NRTPART;
+    static_assert(L::WAVES || L::NRTPART <= kMaxRevParts, "reverse-tangent parts");
     return o;
   }
 };
@@ -1428,8 +1763,8 @@ struct AdjImpl {
   }
 #define MTP_DEFINE_ADJ_REV(LV, NUM, G) \
   namespace mtp {                      \
-  void adj_rev_##NUM##_##G(const double* m, const double* md, long ld, int n, const double* cb, \
-                           const double* cbd, double* mbd, hipStream_t s) {                     \
-    AdjImpl<LV>::tan_reverse_g<G>(m, md, ld, n, cb, cbd, mbd, s);                             \
+  void adj_rev_##NUM##_##G(const double* m, const double* md, long ld, int n, const double* xi, \
+                           const double* cb, const double* cbd, double* mbd, hipStream_t s) {   \
+    AdjImpl<LV>::tan_reverse_g<G>(m, md, ld, n, xi, cb, cbd, mbd, s);                         \
   }                                                                                          \
   }
