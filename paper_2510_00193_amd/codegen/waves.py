@@ -81,7 +81,11 @@ class Layout:
         assert all(q in self.grow for c in self.cores for q in c)
         use = Counter(e for b in prog.blocks for e in b.entries)
         order = sorted((e for e in range(prog.n_mom) if use[e] > 1), key=lambda e: (-use[e], e))
-        self.hot = order
+        self.hot = order  # most used first: the first 128 rows are in reach of an instruction's offset
+        # all the moments where two workgroups still share a compute unit (a moment of one block would be
+        # read by the forward and by the reverse program, each time with the wave waiting)
+        if prog.n_mom + 2 * len(self.general) + 2 * max(waves) <= LDS_ROWS // 2:
+            self.hot = list(range(prog.n_mom))
         assert len(self.hot) + 2 * len(self.general) + 2 * max(waves) <= LDS_ROWS
         # the tangents hold two rows per entry; two workgroups share a compute unit if that leaves out
         # a tenth of the entries at most (level 16)

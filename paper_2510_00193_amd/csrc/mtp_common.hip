@@ -423,9 +423,4 @@ void launch_sum(const double* x, long n, long stride, double* out, hipStream_t s
   hipLaunchKernelGGL(k_sum, dim3(1), dim3(kSumThreads), 0, s, x, n, stride, out);
 }
 
-void launch_sum_virial(const double* wpart, long nblocks, double* out, hipStream_t s) {
-  for (int k = 0; k < 6; ++k)
-    hipLaunchKernelGGL(k_sum, dim3(1), dim3(kSumThreads), 0, s, wpart + k, nblocks, 6L, out + k);
-}
-
 }  // namespace mtp

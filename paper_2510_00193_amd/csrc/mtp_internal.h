@@ -138,7 +138,6 @@ void launch_sum_parts2(const double* x1, long n1, long st1, int nc1, double* out
                        long st2, int nc2, double* out2, double* part, hipStream_t s);
 void launch_sum_parts(const double* x, long n, long stride, int ncomp, double* part, double* out,
                       hipStream_t s);
-void launch_sum_virial(const double* wpart, long nblocks, double* out, hipStream_t s);
 
 // out[r * os] = sum_{k < n} x[r * rs + k * es], r < rows (deterministic: the order depends on n
 // and on whether tmp is given).  tmp (optional, rows * kRowParts doubles) lets rows of at least

@@ -568,13 +568,13 @@ __global__ __launch_bounds__(kLaneBlock) void k_program(const R* __restrict__ mo
 
 // ---------------------------------------------------------------------------- wave programs
 // Levels from 12 on in binary64: a workgroup runs the contraction program of one tile of 64 atoms on
-// several waves, each a part of the contraction blocks.  The moments that two blocks or more read are
-// staged in LDS once ([row][atom]).  With one lane running the whole program the re-reads of shared
+// several waves, each a part of the contraction blocks.  The moments (at level 20 those that two blocks
+// or more read) are staged in LDS once ([row][atom]).  With one lane running the whole program the re-reads of shared
 // moments missed L2 (twice the moments fetched at level 16, 5 times at level 20) and the single wave
 // of a SIMD stood waiting for them four fifths of its time at level 20, where the contraction values
 // and adjoints of 160 components also went to scratch (up to 8.9 KB per lane).  Now the arithmetic is
 // half to three quarters of a tile's time, waits for LDS most of the rest.  Measured before -> after, us:
-//   level 16: 1008 atoms 20 -> 12.9 (both programs); 1,024,000 atoms 742 -> 693
+//   level 16: 1008 atoms 20 -> 12.9 (both programs); 1,024,000 atoms 742 -> 588 (2.1 GB moved: 3.6 TB/s)
 //   level 20: 31,416 atoms 385 -> 130 (forward 42, reverse 88)
 //   level 20, 540,480 atoms in a batch: forward 2200 -> 650, reverse 2460 -> 1500, tangent of the forward
 //   6200 -> 1510, of the reverse 8100 -> 4870
@@ -663,14 +663,26 @@ __device__ __forceinline__ void for_wave(const Tile& t, double* sm, F&& f) {
   }
 }
 
-// rows [entry[0..count)] of src for the lane's atom to LDS rows 0, 1, ... (the waves share the rows)
-template <int COUNT, int NW>
-__device__ __forceinline__ void stage_moments(const int (&entry)[COUNT], int wave, const double* __restrict__ src,
-                                              long ld, unsigned off, double* lds) {
+// Rows entry[0..COUNT) of src for the lane's atom to LDS rows 0, 1, ..., the waves in turn.  Where that is
+// every row (ALL: levels up to 16) the addresses follow from one another and all loads of a wave are in
+// flight at once: 1,024,000 atoms at level 16 693 -> 588 us, with the moments of one contraction staged
+// too.  Rows from the table go eight at a time.
+template <int COUNT, int NW, bool ALL>
+__device__ __forceinline__ void stage_moments(const int (&entry)[COUNT], const Tile& t, const double* __restrict__ src,
+                                              long ld, double* lds) {
+  const RowLoad rows{src + t.first, ld, t.lane};
+  if constexpr (ALL) {
+    constexpr int N = COUNT / NW, REST = COUNT % NW;
+    double v[N];
+#pragma unroll
+    for (int k = 0; k < N; ++k) v[k] = rows(t.wave + k * NW);
+    if (t.wave < REST) lds[(N * NW + t.wave) * kLaneBlock] = rows(N * NW + t.wave);
+#pragma unroll
+    for (int k = 0; k < N; ++k) lds[(t.wave + k * NW) * kLaneBlock] = v[k];
+  } else {
 #pragma unroll 8
-  for (int r = wave; r < COUNT; r += NW)
-    lds[r * kLaneBlock] =
-        *reinterpret_cast<const double*>(reinterpret_cast<const char*>(src + (long)entry[r] * ld) + off);
+    for (int r = t.wave; r < COUNT; r += NW) lds[r * kLaneBlock] = rows(entry[r]);
+  }
 }
 
 // between two phases of a tile (the waves of a workgroup exchange data through LDS only)
@@ -709,7 +721,7 @@ void k_wave_forward(const double* __restrict__ mom, long ld, int i0, int n, cons
   __shared__ double sm[(PROW + 2 * NW) * kLaneBlock];
   const Tile t = tile_of(n);
   double* lds = lane_ptr(sm, t.lane);
-  stage_moments<L::NHOT, NW>(L::HOT_ENTRY, t.wave, mom + t.first, ld, t.lane, lds);
+  stage_moments<L::NHOT, NW, L::NHOT == L::NMOM>(L::HOT_ENTRY, t, mom, ld, lds);
   double e = 0.0, c0b = 0.0;
   step_barrier();
   for_wave<NW>(t, sm, [&](auto w, double* p, unsigned lane) {
@@ -747,7 +759,7 @@ void k_wave_reverse(const double* __restrict__ mom, long ld, int n, const double
   __shared__ double sm[ROWS * kLaneBlock];
   const Tile t = tile_of(n);
   double* lds = lane_ptr(sm, t.lane);
-  stage_moments<L::NHOT, L::NRWAVE>(L::HOT_ENTRY, t.wave, mom + t.first, ld, t.lane, lds);
+  stage_moments<L::NHOT, L::NRWAVE, L::NHOT == L::NMOM>(L::HOT_ENTRY, t, mom, ld, lds);
   step_barrier();
   for_wave<L::NRWAVE>(t, sm, [&](auto w, double* p, unsigned lane) {
     reverse_wave<L, decltype(w)::value>(TileMoments<L, false>{p, mom + t.first, ld, lane},
@@ -768,7 +780,7 @@ void k_wave_program(const double* __restrict__ mom, long ld, int i0, int n, cons
   __shared__ double sm[(PROW + 2 * NW) * kLaneBlock];
   const Tile t = tile_of(n);
   double* lds = lane_ptr(sm, t.lane);
-  stage_moments<L::NHOT, NW>(L::HOT_ENTRY, t.wave, mom + t.first, ld, t.lane, lds);
+  stage_moments<L::NHOT, NW, L::NHOT == L::NMOM>(L::HOT_ENTRY, t, mom, ld, lds);
   const long first = cbar ? t.first : 0;  // no offset to a null pointer
   double e = 0.0, c0b = 0.0;
   step_barrier();
@@ -1181,8 +1193,8 @@ void k_wave_tan_forward(const double* __restrict__ mom, const double* __restrict
   __shared__ double sm[(PROW + NW) * kLaneBlock];
   const Tile t = tile_of(n);
   double* lds = lane_ptr(sm, t.lane);
-  stage_moments<L::NTHOT, NW>(L::THOT_ENTRY, t.wave, mom + t.first, ld, t.lane, lds);
-  stage_moments<L::NTHOT, NW>(L::THOT_ENTRY, t.wave, mdot + t.first, ld, t.lane, lds + DROW * kLaneBlock);
+  stage_moments<L::NTHOT, NW, L::NTHOT == L::NMOM>(L::THOT_ENTRY, t, mom, ld, lds);
+  stage_moments<L::NTHOT, NW, L::NTHOT == L::NMOM>(L::THOT_ENTRY, t, mdot, ld, lds + DROW * kLaneBlock);
   if (ebar_cfg) {
     const int li = t.first + (int)(t.lane / sizeof(double)), i = perm ? perm[i0 + li] : i0 + li;
     ebar = ebar_cfg[cfg ? cfg[i] : 0];
@@ -1238,8 +1250,8 @@ void k_wave_tan_reverse(const double* __restrict__ mom, const double* __restrict
   __shared__ double sm[ROWS * kLaneBlock];
   const Tile t = tile_of(n);
   double* lds = lane_ptr(sm, t.lane);
-  stage_moments<L::NTHOT, NW>(L::THOT_ENTRY, t.wave, mom + t.first, ld, t.lane, lds);
-  stage_moments<L::NTHOT, NW>(L::THOT_ENTRY, t.wave, mdot + t.first, ld, t.lane, lds + DROW * kLaneBlock);
+  stage_moments<L::NTHOT, NW, L::NTHOT == L::NMOM>(L::THOT_ENTRY, t, mom, ld, lds);
+  stage_moments<L::NTHOT, NW, L::NTHOT == L::NMOM>(L::THOT_ENTRY, t, mdot, ld, lds + DROW * kLaneBlock);
   step_barrier();
   for_wave<NW>(t, sm, [&](auto w, double* p, unsigned lane) {
     tangent_reverse_wave<L, decltype(w)::value>(TileMoments<L, true>{p, mom + t.first, ld, lane},
