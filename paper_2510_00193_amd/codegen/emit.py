@@ -680,6 +680,10 @@ def emit_level(level: int, n_groups: int = 1, rtan_budget: int = RTAN_REG_BUDGET
     w = _W()
     w(f"// Generated MTP level-{level} program.  Do not edit; produced by codegen/emit.py.")
     w("#pragma once")
+    w("#ifndef MTP_TILE_FENCE  // compiled for the host, where the order of the code is the compiler's")
+    w("#define MTP_TILE_FENCE()")
+    w("#define MTP_PIN(x)")
+    w("#endif")
     w(f"struct Lv{level} {{")
     w.push()
     w(f"static constexpr int LEVEL = {level};")
