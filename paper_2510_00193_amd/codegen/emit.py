@@ -481,7 +481,9 @@ TAN_PREFETCH_DEPTH = int(os.environ.get("MTP_TAN_PREFETCH_DEPTH", "24"))
 # prefetched loads.  A part of the reverse-tangent program adds the accumulators live at each of
 # its blocks (two VGPRs each); parts are cut so that this stays within RTAN_REG_BUDGET (the 512
 # VGPR + AGPR of one wave per SIMD).  The estimate is rough (some parts spill, some blocks over
-# it do not); at level 20 budgets of 430, 512 and 545 measured 8.9, 8.1 and 8.05 ms.
+# it do not).  On the device one lane runs it up to level 10, in a single part; levels from 12 on run by
+# several waves per tile (at level 20 4.9 ms, where the parts took 8.1) and keep these parts for the
+# host's tests.
 RTAN_REG_BUDGET = int(os.environ.get("MTP_RTAN_BUDGET", "512"))
 # blocks tried for each addition to a part (those adding the fewest new entries)
 RTAN_CANDIDATES = 12
