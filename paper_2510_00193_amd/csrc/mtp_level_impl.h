@@ -861,13 +861,20 @@ __device__ __forceinline__ void add_gradient(double dx, double dy, double dz, do
   w[5] -= dy * gz;
 }
 
+// Waves per SIMD of the binary64 kernel of one part: two up to 64 entries (46 at level 12 take 198 to 250
+// registers).  The 81 of level 14, next to six own sums and a pair's values, spill 40 to 180 bytes per lane
+// in the 256 registers of two waves and take 266 to 278 of one: 1.47 -> 0.72 ms at 998,560 atoms, 99 -> 55 us
+// at 63,488.
+constexpr int gradient_occupancy(int entries) { return entries > 64 ? 1 : 2; }
+
 // g[p] (+)= dE_i/dd_ij restricted to the entries of group G (binary32; binary64 levels of one part
 // take the whole adjoint by pair_part); per-workgroup virial partials;
 // fown[i] (+)= sum of the atom's own g over its row (the first half of its force), when given.
 // K lanes per atom (single systems): each takes every K-th pair of the row; the own sums are
 // combined over the atom's lanes, the virial partial over the workgroup as before.
 template <class L, int G, class R, bool BATCH, int NC, bool PERSIST = false, int K = 1>
-__global__ __launch_bounds__(kLaneBlock) __attribute__((amdgpu_waves_per_eu(std::is_same_v<R, double> ? 2 : 1)))
+__global__ __launch_bounds__(kLaneBlock)
+__attribute__((amdgpu_waves_per_eu(std::is_same_v<R, double> ? gradient_occupancy(L::NMOM) : 1)))
 void k_backward(SysArgs a, int i0, int n, const R* __restrict__ mbar, long ld, double* __restrict__ g,
                 double* __restrict__ wpart, double* __restrict__ watom, double* __restrict__ fown) {
   constexpr bool PARTS = std::is_same_v<R, double>;
