@@ -173,50 +173,47 @@ inline unsigned radial_bytes(const SysArgs& a) {
 // of a list array touches 64 cache lines, and the lines of the four waves of a CU do not stay in
 // its 32 KB L1 until the next pair; the refills bounded the pair loops (the loads issued a whole
 // pair ahead were still waited for: with the instructions cut by a quarter the pair-gradient kernel
-// stayed at 1.14 ms at a million atoms, staged rows took it to 0.95).  So a lane copies its row, kRowStage pairs at a time with
-// 16-byte reads, to a column of its own in LDS (16 KB per wave) and reads the pairs from there.
+// stayed at 1.14 ms at a million atoms, staged rows took it to 0.95).  So a lane copies its row,
+// kRowStage pairs at a time with 16-byte reads, to a column of its own in LDS (16 KB per wave) and reads
+// the pairs from there.  A read of four may pass the end of its row, but not of the list: the waves of
+// the last rows read entry by entry, which one test per wave decides.  A stage takes about 130
+// instructions; with selects in every read and single entries written it took 740, and the wave's first
+// pair waits for it.  Evaluations in binary32, unstaged / that way / now: 33,600 atoms of 42 pairs at
+// level 12 122 / 128 / 122 us, 63,488 of 27 at level 16 142 / 148 / 142.
 constexpr int kRowStage = 32;
-struct alignas(8) ListEntry {
+constexpr int kStageInts = 2 * kRowStage * kLaneBlock;  // partners, then shifts: [pair][lane] each
+struct ListEntry {
   int j, shift;
 };
-
-// The four list entries from pair p on.  Entries past the end of the list repeat its last one;
-// entries past the row's end belong to other rows and are not used.
-__device__ __forceinline__ void load_entries(const SysArgs& a, int p, ListEntry* e) {
-  typedef int v4i __attribute__((ext_vector_type(4), aligned(4)));
-  const int last = a.npairs - 4;
-  if (last < 0) {  // the whole list holds fewer than four pairs
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const int q = min(p + k, a.npairs - 1);
-      e[k] = ListEntry{a.nj[q], a.shift[q]};
-    }
-    return;
-  }
-  const int b = min(p, last), d = min(p - b, 3);
-  v4i j = *reinterpret_cast<const v4i*>(a.nj + b);
-  v4i s = *reinterpret_cast<const v4i*>(a.shift + b);
-  if (d & 1) {  // the end of the list: entry k is element k + d of what was read
-    j = v4i{j[1], j[2], j[3], j[3]};
-    s = v4i{s[1], s[2], s[3], s[3]};
-  }
-  if (d & 2) {
-    j = v4i{j[2], j[3], j[3], j[3]};
-    s = v4i{s[2], s[3], s[3], s[3]};
-  }
-#pragma unroll
-  for (int k = 0; k < 4; ++k) e[k] = ListEntry{j[k], s[k]};
+__device__ __forceinline__ ListEntry staged(const int* col, int k) {
+  return ListEntry{col[k * kLaneBlock], col[(kRowStage + k) * kLaneBlock]};
+}
+__device__ __forceinline__ void stage_entry(int* col, int k, ListEntry e) {
+  col[k * kLaneBlock] = e.j;
+  col[(kRowStage + k) * kLaneBlock] = e.shift;
 }
 
-// Copy pairs [p, p + m) of a row to the lane's LDS column (stride kLaneBlock); m <= kRowStage.
-__device__ __forceinline__ void stage_row(const SysArgs& a, int p, int m, ListEntry* __restrict__ col) {
-  ListEntry e[kRowStage];
+// Copy pairs [p, p + m) of a row to the lane's LDS column; 1 <= m <= kRowStage.  Up to three entries past
+// m are written with them (pairs of other rows, not used).
+__device__ __forceinline__ void stage_row(const SysArgs& a, int p, int m, int* __restrict__ col) {
+  typedef int v4i __attribute__((ext_vector_type(4), aligned(4)));
+  if (__any(p > a.npairs - kRowStage)) {
+    for (int k = 0; k < m; ++k) stage_entry(col, k, ListEntry{a.nj[p + k], a.shift[p + k]});
+    return;
+  }
+  v4i j[kRowStage / 4], s[kRowStage / 4];
 #pragma unroll
-  for (int k = 0; k < kRowStage; k += 4)
-    if (k < m) load_entries(a, p + k, e + k);
+  for (int k = 0; k < kRowStage / 4; ++k)
+    if (4 * k < m) {
+      j[k] = *reinterpret_cast<const v4i*>(a.nj + p + 4 * k);
+      s[k] = *reinterpret_cast<const v4i*>(a.shift + p + 4 * k);
+    }
 #pragma unroll
-  for (int k = 0; k < kRowStage; ++k)
-    if (k < m) col[k * kLaneBlock] = e[k];
+  for (int k = 0; k < kRowStage / 4; ++k)
+    if (4 * k < m) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) stage_entry(col, 4 * k + q, ListEntry{j[k][q], s[k][q]});
+    }
 }
 
 // Position and species of a pair's partner, and with TAN its force cotangent.
@@ -286,16 +283,16 @@ __device__ __forceinline__ void drain_loads() { __builtin_amdgcn_s_waitcnt(0x0F7
 // With K lanes per atom, lane sub of the atom takes pairs sub, sub + K, sub + 2K, ... of the row
 // (the lanes of an atom read consecutive list entries); with one, lst is the wave's LDS stage.
 template <int K, class R, bool TAN, class F>
-__device__ __forceinline__ void for_pairs(const SysArgs& a, ListEntry* lst, int i, int sub, const double* H,
+__device__ __forceinline__ void for_pairs(const SysArgs& a, int* lst, int i, int sub, const double* H,
                                           const Partner<TAN>& own, const double* __restrict__ fbar, F&& body) {
   const int p0 = a.off[i] + sub, p1 = a.off[i + 1];
   Partner<TAN> q;
   if constexpr (K == 1) {
-    ListEntry* col = lst + (threadIdx.x & (kLaneBlock - 1));
+    int* col = lst + (threadIdx.x & (kLaneBlock - 1));
     for (int b = p0; b < p1; b += kRowStage) {
       const int m = min(kRowStage, p1 - b);
       stage_row(a, b, m, col);
-      ListEntry cur = col[0], nxt = col[(m > 1) * kLaneBlock];
+      ListEntry cur = staged(col, 0), nxt = staged(col, m > 1);
       q.load(a, fbar, cur.j);
       int k = 0;
       drain_loads();
@@ -305,7 +302,7 @@ __device__ __forceinline__ void for_pairs(const SysArgs& a, ListEntry* lst, int 
             [&]() {
               cur = nxt;
               q.load(a, fbar, cur.j);
-              nxt = col[min(k + 2, m - 1) * kLaneBlock];
+              nxt = staged(col, min(k + 2, m - 1));
             },
             body);
         ++k;
@@ -337,18 +334,18 @@ __device__ __forceinline__ void for_pairs(const SysArgs& a, ListEntry* lst, int 
 // The same with T steps in every lane, for the first wave of a pipeline of waves: a lane past its len
 // pairs repeats the last one, a lane without pairs takes atom i itself (its results are dropped).
 template <int K, bool TAN, class F>
-__device__ __forceinline__ void for_steps(const SysArgs& a, ListEntry* lst, int i, int lane, int p0, int len, int T,
+__device__ __forceinline__ void for_steps(const SysArgs& a, int* lst, int i, int lane, int p0, int len, int T,
                                           const double* H, const Partner<TAN>& own, const double* __restrict__ fbar,
                                           F&& body) {
   Partner<TAN> q;
   if constexpr (K == 1) {
-    ListEntry* col = lst + lane;
+    int* col = lst + lane;
     for (int b = 0; b < T; b += kRowStage) {
       const int m = min(kRowStage, len - b), kn = min(kRowStage, T - b);
       if (m > 0) stage_row(a, p0 + b, m, col);
-      else col[0] = ListEntry{i, 0};  // a lane past its row
+      else stage_entry(col, 0, ListEntry{i, 0});  // a lane past its row
       const int last = max(m - 1, 0);
-      ListEntry cur = col[0], nxt = col[min(1, last) * kLaneBlock];
+      ListEntry cur = staged(col, 0), nxt = staged(col, min(1, last));
       q.load(a, fbar, cur.j);
       drain_loads();
       for (int k = 0; k < kn; ++k) {
@@ -357,7 +354,7 @@ __device__ __forceinline__ void for_steps(const SysArgs& a, ListEntry* lst, int 
             [&]() {
               cur = nxt;
               q.load(a, fbar, cur.j);
-              nxt = col[min(k + 2, last) * kLaneBlock];
+              nxt = staged(col, min(k + 2, last));
             },
             body);
       }
@@ -416,7 +413,7 @@ __device__ __forceinline__ void cell_of(const SysArgs& a, int i, double* H) {
 // per atom (single systems) each accumulate every K-th pair of the row, the partial moments are
 // summed over the atom's lanes and its first lane writes them.
 template <class L, int P, class R, bool BATCH, int NC, int K>
-__device__ __forceinline__ void moments_of_atom(const SysArgs& a, const R* csh, ListEntry* lst, int i, int li, int sub,
+__device__ __forceinline__ void moments_of_atom(const SysArgs& a, const R* csh, int* lst, int i, int li, int sub,
                                                 R* __restrict__ mout, long ld) {
   constexpr bool PARTS = std::is_same_v<R, double>;
   constexpr int LO = PARTS ? 0 : L::GROUP_LO[PARTS ? 0 : P];
@@ -460,7 +457,7 @@ template <class L, int G, class R, bool BATCH, int NC, bool PERSIST = false, int
 __global__ __launch_bounds__(kLaneBlock) __attribute__((amdgpu_waves_per_eu(std::is_same_v<R, double> ? 2 : 1)))
 void k_moments(SysArgs a, int i0, int n, R* __restrict__ mout, long ld) {
   constexpr int NP = std::is_same_v<R, double> ? L::NPART : 1;
-  __shared__ ListEntry lst[K == 1 ? kRowStage * kLaneBlock : 1];
+  __shared__ int lst[K == 1 ? kStageInts : 1];
   const R* csh = stage_radial<R>(a);
   MTP_FOR_TILES_K(a, n, K, NP, b) {
   // parts of a tile in consecutive workgroups: they read the same rows
@@ -882,7 +879,7 @@ void k_backward(SysArgs a, int i0, int n, const R* __restrict__ mbar, long ld, d
   constexpr int LO = PARTS ? 0 : L::GROUP_LO[PARTS ? 0 : G];
   constexpr int NG = PARTS ? L::NMOM : L::GROUP_HI[PARTS ? 0 : G] - LO;
   static_assert(!PARTS || L::NPART == 1, "levels of several parts take k_backward_stages");
-  __shared__ ListEntry lst[K == 1 ? kRowStage * kLaneBlock : 1];
+  __shared__ int lst[K == 1 ? kStageInts : 1];
   const R* csh = stage_radial<R>(a);
   MTP_FOR_TILES_K(a, n, K, 1, b) {
   const int li = b * (kLaneBlock / K) + (int)threadIdx.x / K, sub = (int)threadIdx.x % K;
@@ -958,7 +955,7 @@ struct StageSlots {
 
 // First stage (part NPART - 1): T steps.
 template <class L, bool BATCH, int NC, int K>
-__device__ __forceinline__ void gradient_stage_first(const SysArgs& a, const double* csh, ListEntry* lst,
+__device__ __forceinline__ void gradient_stage_first(const SysArgs& a, const double* csh, int* lst,
                                                      StageSlots<L>& slots, int i, int li, int sub, int lane, int p0,
                                                      int len, int T, const double* __restrict__ mbar, long ld) {
   constexpr int P = L::NPART - 1, NE = L::PART_SIZE[P];
@@ -1044,7 +1041,7 @@ __global__ __launch_bounds__(kLaneBlock * L::NPART) __attribute__((amdgpu_waves_
 void k_backward_stages(SysArgs a, int i0, int n, const double* __restrict__ mbar, long ld, double* __restrict__ g,
                        double* __restrict__ wpart, double* __restrict__ watom, double* __restrict__ fown) {
   static_assert(L::NPART <= 4, "pair-gradient stages");
-  __shared__ ListEntry lst[K == 1 ? kRowStage * kLaneBlock : 1];
+  __shared__ int lst[K == 1 ? kStageInts : 1];
   __shared__ StageSlots<L> slots;
   const double* csh = stage_radial<double>(a);
   const int lane = (int)threadIdx.x & (kLaneBlock - 1);
@@ -1079,7 +1076,7 @@ void k_backward_stages(SysArgs a, int i0, int n, const double* __restrict__ mbar
 // for 545,505 atoms at level 20 (4.3 in four passes of one wave per SIMD), 25 us for 16,000 at level 16
 // with four lanes per atom (139 in three passes of one lane per atom).
 template <class L, int P, int NC, int K>
-__device__ __forceinline__ void tangents_of_atom(const SysArgs& a, const double* csh, ListEntry* lst, int i, int li,
+__device__ __forceinline__ void tangents_of_atom(const SysArgs& a, const double* csh, int* lst, int i, int li,
                                                  int sub, const double* __restrict__ fbar,
                                                  double* __restrict__ mdot, long ld) {
   constexpr int NE = L::TPART_SIZE[P];
@@ -1117,7 +1114,7 @@ __global__ __launch_bounds__(kLaneBlock) __attribute__((amdgpu_waves_per_eu(2)))
 void k_tan_moments(SysArgs a, const double* __restrict__ fbar, int i0, int n, double* __restrict__ mdot, long ld) {
   constexpr int NP = L::NTPART;
   static_assert(NP <= 5, "moment-tangent parts");
-  __shared__ ListEntry lst[K == 1 ? kRowStage * kLaneBlock : 1];
+  __shared__ int lst[K == 1 ? kStageInts : 1];
   const double* csh = stage_radial<double>(a);
   MTP_FOR_TILES_K(a, n, K, NP, b) {
   const int li = (b / NP) * (kLaneBlock / K) + (int)threadIdx.x / K, sub = (int)threadIdx.x % K;
@@ -1309,7 +1306,7 @@ __device__ __forceinline__ void adj_coefficients(const double* __restrict__ mbar
 }
 
 template <class L, int K>
-__device__ __forceinline__ void adj_stage_first(const SysArgs& a, ListEntry* lst, AdjSlots<L>& slots, int i, int li,
+__device__ __forceinline__ void adj_stage_first(const SysArgs& a, int* lst, AdjSlots<L>& slots, int i, int li,
                                                 int lane, int p0, int len, int T, const double* __restrict__ fbar,
                                                 const double* __restrict__ mbar, const double* __restrict__ mbard,
                                                 long ld, double ebar, double* __restrict__ rec) {
@@ -1390,7 +1387,7 @@ __global__ __launch_bounds__(kLaneBlock * L::NASTAGE) __attribute__((amdgpu_wave
 void k_adj_stages(SysArgs a, const double* __restrict__ fbar, int i0, int n, const double* __restrict__ mbar,
                   const double* __restrict__ mbard, long ld, double ebar0, double* __restrict__ rec) {
   static_assert(L::NASTAGE <= 8, "adjoint stages");
-  __shared__ ListEntry lst[K == 1 ? kRowStage * kLaneBlock : 1];
+  __shared__ int lst[K == 1 ? kStageInts : 1];
   __shared__ AdjSlots<L> slots;
   const int lane = (int)threadIdx.x & (kLaneBlock - 1);
   const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kLaneBlock);

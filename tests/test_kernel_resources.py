@@ -1,5 +1,5 @@
-"""Register allocation of device kernels that fit the registers only at the occupancy they are compiled
-for: compiled for gfx950 (no GPU needed), they must not use scratch memory."""
+"""Device kernels compiled for gfx950 (no GPU needed): those that fit the registers only at the occupancy
+they are compiled for must not use scratch memory, and the copy of list rows to LDS must stay short."""
 import re
 import subprocess
 
@@ -9,19 +9,31 @@ from paper_2510_00193_amd import build
 from paper_2510_00193_amd.codegen.emit import write_level
 
 
-@pytest.mark.parametrize("level", [12, 14])
-def test_pair_gradients_of_one_part_stay_in_registers(level, tmp_path):
+def _compile(tmp_path, level, kernels, *options):
+    """stderr and output of the device compilation of explicit kernel instantiations."""
     write_level(level, str(tmp_path))
-    unit = tmp_path / "unit.hip"
+    unit, out = tmp_path / "unit.hip", tmp_path / "unit.out"
     lines = ['#include "mtp_device.h"', f'#include "mtp_L{level}.inc"', '#include "mtp_level_impl.h"']
-    for ncheb in (0, 8):
-        for lanes in (1, 2):
-            lines.append(f"template __global__ void mtp::k_backward<Lv{level}, 0, double, false, {ncheb}, false, {lanes}>("
-                         "mtp::SysArgs, int, int, const double*, long, double*, double*, double*, double*);")
-    unit.write_text("\n".join(lines) + "\n")
-    cmd = [build.HIPCC, *build.FLAGS, f"-I{tmp_path}", "--offload-device-only", "-Rpass-analysis=kernel-resource-usage",
-           "-c", str(unit), "-o", str(tmp_path / "unit.o")]
+    unit.write_text("\n".join(lines + [f"template __global__ void mtp::{k};" for k in kernels]) + "\n")
+    cmd = [build.HIPCC, *build.FLAGS, f"-I{tmp_path}", "--offload-device-only", *options, str(unit), "-o", str(out)]
     res = subprocess.run(cmd, capture_output=True, text=True)
     assert res.returncode == 0, res.stderr[-2000:]
-    scratch = [int(x) for x in re.findall(r"ScratchSize \[bytes/lane\]: (\d+)", res.stderr)]
-    assert scratch == [0] * 4
+    return res.stderr, out
+
+
+@pytest.mark.parametrize("level", [12, 14])
+def test_pair_gradients_of_one_part_stay_in_registers(level, tmp_path):
+    args = "mtp::SysArgs, int, int, const double*, long, double*, double*, double*, double*"
+    kernels = [f"k_backward<Lv{level}, 0, double, false, {ncheb}, false, {lanes}>({args})"
+               for ncheb in (0, 8) for lanes in (1, 2)]
+    log, _ = _compile(tmp_path, level, kernels, "-Rpass-analysis=kernel-resource-usage", "-c")
+    scratch = [int(x) for x in re.findall(r"ScratchSize \[bytes/lane\]: (\d+)", log)]
+    assert scratch == [0] * len(kernels)
+
+
+def test_row_stage_selects_nothing_per_entry(tmp_path):
+    """Whether a read might pass the end of the list is one test per wave: the smallest binary32 moment
+    kernel, whose code is mostly the stage, holds few selects (5 when written, 102 with a test per read)."""
+    _, asm = _compile(tmp_path, 2, ["k_moments<Lv2, 0, float, false, 8, false, 1>(mtp::SysArgs, int, int, float*, long)"],
+                      "-S")
+    assert asm.read_text().count("v_cndmask_b32") < 32
