@@ -32,6 +32,7 @@ struct SysArgs {
   // one workgroup per tile
   int* queue;
   int pgrid;
+  int simds;  // SIMDs of the device (single systems)
   // lanes per atom of the pair kernels (1, 2, 4 or 8): with more than one, the
   // lanes of an atom take every split-th pair of its row and combine their sums
   int split;

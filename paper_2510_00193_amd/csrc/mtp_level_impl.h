@@ -18,6 +18,7 @@
 namespace mtp {
 
 constexpr int kLaneBlock = 64;   // one wave per workgroup for the lane-per-atom kernels
+constexpr int kMaxWaves = 8;     // waves a SIMD can hold
 
 // Tiles of kLaneBlock atoms a workgroup of a pair kernel processes: its own block of the grid
 // (PERSIST false: the loop body runs once), or, for a persistent launch, tiles pulled from the
@@ -453,8 +454,10 @@ __device__ __forceinline__ void moments_of_atom(const SysArgs& a, const R* csh, 
 // 0.73 -> 0.59 ms at 1,024,000 atoms of level 16 (the vector unit is busy three quarters of it),
 // 1.93 -> 1.17 ms at level 20 (545,505 atoms; it took three passes before).
 // Binary32: group G of the layout.
-template <class L, int G, class R, bool BATCH, int NC, bool PERSIST = false, int K = 1>
-__global__ __launch_bounds__(kLaneBlock) __attribute__((amdgpu_waves_per_eu(std::is_same_v<R, double> ? 2 : 1)))
+// ALONE: one wave per SIMD (launch_moments_g).
+template <class L, int G, class R, bool BATCH, int NC, bool PERSIST = false, int K = 1, bool ALONE = false>
+__global__ __launch_bounds__(kLaneBlock)
+__attribute__((amdgpu_waves_per_eu(std::is_same_v<R, double> && !ALONE ? 2 : 1, ALONE ? 1 : kMaxWaves)))
 void k_moments(SysArgs a, int i0, int n, R* __restrict__ mout, long ld) {
   constexpr int NP = std::is_same_v<R, double> ? L::NPART : 1;
   __shared__ int lst[K == 1 ? kStageInts : 1];
@@ -869,9 +872,10 @@ constexpr int gradient_occupancy(int entries) { return entries > 64 ? 1 : 2; }
 // fown[i] (+)= sum of the atom's own g over its row (the first half of its force), when given.
 // K lanes per atom (single systems): each takes every K-th pair of the row; the own sums are
 // combined over the atom's lanes, the virial partial over the workgroup as before.
-template <class L, int G, class R, bool BATCH, int NC, bool PERSIST = false, int K = 1>
+template <class L, int G, class R, bool BATCH, int NC, bool PERSIST = false, int K = 1, bool ALONE = false>
 __global__ __launch_bounds__(kLaneBlock)
-__attribute__((amdgpu_waves_per_eu(std::is_same_v<R, double> ? gradient_occupancy(L::NMOM) : 1)))
+__attribute__((amdgpu_waves_per_eu(std::is_same_v<R, double> && !ALONE ? gradient_occupancy(L::NMOM) : 1,
+                                   ALONE ? 1 : kMaxWaves)))
 void k_backward(SysArgs a, int i0, int n, const R* __restrict__ mbar, long ld, double* __restrict__ g,
                 double* __restrict__ wpart, double* __restrict__ watom, double* __restrict__ fown) {
   constexpr bool PARTS = std::is_same_v<R, double>;
@@ -1544,16 +1548,31 @@ void k_adj_radial(SysArgs a, int n, const double* __restrict__ rec, double* __re
 // ---------------------------------------------------------------------------- launchers
 // The pair kernels come in Chebyshev-count specialisations for the common sizes 8 and 10 and a
 // runtime-count form for the rest.
+template <class L, int G, class R, bool BATCH, bool PERSIST, int K, bool ALONE>
+void launch_moments_nc(const SysArgs& a, int nb, int i0, int n, void* m, long ld, hipStream_t s) {
+  const unsigned sh = radial_bytes<R>(a);
+  if (a.ncheb == 8)
+    hipLaunchKernelGGL((k_moments<L, G, R, BATCH, 8, PERSIST, K, ALONE>), dim3(nb), dim3(kLaneBlock), sh, s, a, i0, n, (R*)m, ld);
+  else if (a.ncheb == 10)
+    hipLaunchKernelGGL((k_moments<L, G, R, BATCH, 10, PERSIST, K, ALONE>), dim3(nb), dim3(kLaneBlock), sh, s, a, i0, n, (R*)m, ld);
+  else
+    hipLaunchKernelGGL((k_moments<L, G, R, BATCH, 0, PERSIST, K, ALONE>), dim3(nb), dim3(kLaneBlock), sh, s, a, i0, n, (R*)m, ld);
+}
+// Single systems, levels of one part: while there is a SIMD for every wave of a launch, the form that
+// takes a SIMD's registers whole, so that no two waves share one with others idle.  The hardware deals
+// single waves so in some sequences of launches and not in others: moments of 35,280 atoms at level 12 44
+// or 57 us (after a force reduction, after a grade) where two fit a SIMD, 42 always with this form.
+// Levels of several parts have two waves per SIMD to deal out from half that size on.
+template <class L, class R, bool BATCH>
+constexpr bool may_run_alone() { return std::is_same_v<R, double> && !BATCH && L::NPART == 1; }
+
 template <class L, int G, class R, bool BATCH, bool PERSIST, int K = 1>
 void launch_moments_gp(const SysArgs& a, int i0, int n, void* m, long ld, hipStream_t s) {
   const int nb = pair_grid(a, split_tiles(n, K) * (std::is_same_v<R, double> ? L::NPART : 1));
-  const unsigned sh = radial_bytes<R>(a);
-  if (a.ncheb == 8)
-    hipLaunchKernelGGL((k_moments<L, G, R, BATCH, 8, PERSIST, K>), dim3(nb), dim3(kLaneBlock), sh, s, a, i0, n, (R*)m, ld);
-  else if (a.ncheb == 10)
-    hipLaunchKernelGGL((k_moments<L, G, R, BATCH, 10, PERSIST, K>), dim3(nb), dim3(kLaneBlock), sh, s, a, i0, n, (R*)m, ld);
-  else
-    hipLaunchKernelGGL((k_moments<L, G, R, BATCH, 0, PERSIST, K>), dim3(nb), dim3(kLaneBlock), sh, s, a, i0, n, (R*)m, ld);
+  if constexpr (may_run_alone<L, R, BATCH>()) {
+    if (nb <= a.simds) return launch_moments_nc<L, G, R, BATCH, PERSIST, K, true>(a, nb, i0, n, m, ld, s);
+  }
+  launch_moments_nc<L, G, R, BATCH, PERSIST, K, false>(a, nb, i0, n, m, ld, s);
 }
 // split lanes in binary64 only; persistent variants exist for batches of one lane per atom (a
 // system small enough for split lanes is one round of workgroups)
@@ -1580,12 +1599,19 @@ void launch_backward_nc(const SysArgs& a, int i0, int n, const void* mb, long ld
                         double* watom, double* fown, hipStream_t s) {
   const int nb = pair_grid(a, split_tiles(n, K));
   const unsigned sh = radial_bytes<R>(a);
-  if constexpr (std::is_same_v<R, double> && L::NPART > 1)
+  if constexpr (std::is_same_v<R, double> && L::NPART > 1) {
     hipLaunchKernelGGL((k_backward_stages<L, BATCH, NC, PERSIST, K>), dim3(nb), dim3(kLaneBlock * L::NPART), sh, s, a,
                        i0, n, (const double*)mb, ld, g, wpart, watom, fown);
-  else
-    hipLaunchKernelGGL((k_backward<L, G, R, BATCH, NC, PERSIST, K>), dim3(nb), dim3(kLaneBlock), sh, s, a, i0, n,
-                       (const R*)mb, ld, g, wpart, watom, fown);
+  } else {
+    // as for the moments (a kernel for one wave per SIMD runs so by itself)
+    constexpr bool ALONE = may_run_alone<L, R, BATCH>() && gradient_occupancy(L::NMOM) > 1;
+    if (ALONE && nb <= a.simds)
+      hipLaunchKernelGGL((k_backward<L, G, R, BATCH, NC, PERSIST, K, ALONE>), dim3(nb), dim3(kLaneBlock), sh, s, a, i0, n,
+                         (const R*)mb, ld, g, wpart, watom, fown);
+    else
+      hipLaunchKernelGGL((k_backward<L, G, R, BATCH, NC, PERSIST, K, false>), dim3(nb), dim3(kLaneBlock), sh, s, a, i0, n,
+                         (const R*)mb, ld, g, wpart, watom, fown);
+  }
 }
 template <class L, int G, class R, bool BATCH, bool PERSIST, int K = 1>
 void launch_backward_gp(const SysArgs& a, int i0, int n, const void* mb, long ld, double* g, double* wpart,

@@ -37,3 +37,15 @@ def test_row_stage_selects_nothing_per_entry(tmp_path):
     _, asm = _compile(tmp_path, 2, ["k_moments<Lv2, 0, float, false, 8, false, 1>(mtp::SysArgs, int, int, float*, long)"],
                       "-S")
     assert asm.read_text().count("v_cndmask_b32") < 32
+
+
+def test_waves_of_small_launches_take_a_simd_each(tmp_path):
+    """The forms for launches of at most one wave per SIMD hold all its registers (more than 256), so that
+    no second wave is placed beside one while other SIMDs idle; the other forms leave room for two."""
+    moments, gradients = "(mtp::SysArgs, int, int, double*, long)", "(mtp::SysArgs, int, int, const double*, long, " \
+        "double*, double*, double*, double*)"
+    kernels = [f"{name}<Lv12, 0, double, false, 7, false, 1, {alone}>{args}"
+               for name, args in (("k_moments", moments), ("k_backward", gradients)) for alone in ("true", "false")]
+    _, asm = _compile(tmp_path, 12, kernels, "-S")
+    vgprs = [int(x) for x in re.findall(r"\.amdhsa_next_free_vgpr (\d+)", asm.read_text())]
+    assert [v > 256 for v in vgprs] == [True, False] * 2, vgprs
