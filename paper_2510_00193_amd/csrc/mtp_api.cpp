@@ -392,23 +392,32 @@ SysArgs make_sys_args(const mtp_model* m, const mtp_system* sys, const mtp_nlist
   return a;
 }
 
-// Small systems leave SIMDs idle with one lane per atom (a wave per 64 atoms, one wave per
-// SIMD at these register counts): the lanes per atom double while the waves still fit on the
-// SIMDs (4 per compute unit) at once.
+// Small systems leave SIMDs idle with one lane per atom (a wave per 64 atoms): the lanes per atom double
+// while the waves of one part still find a SIMD (4 per compute unit) each.
 int lanes_for(int ncu, int n) {
   int k = 1;
   while (k < 8 && (long)n * 2 * k <= (long)kLaneBlockHost * 4 * ncu) k *= 2;
   return k;
 }
 
+// A SIMD holds two waves of the pair kernels: a system that would run one lane per atom in at most one
+// wave per SIMD (levels of one part, 32,769 to 65,536 atoms on 256 compute units) takes two lanes, whose
+// waves need no row stage.  One -> two lanes, level 12, us: grade of 33,800 atoms 46.9 -> 43.9, of 63,488
+// 63.6 -> 61.5; evaluation 72.8 -> 63.6, 88.8 -> 87.1.  Beyond, evaluations with two lanes gain and lose
+// (101,000 atoms of 42 pairs, level 10: 190 us with one, 197 with two; of 27 pairs 113 and 112).
 int pair_split(const mtp_model* m, int n) {
   if (m->precision != MTP_FP64) return 1;
-  return m->split > 0 ? m->split : lanes_for(m->ncu, n);
+  if (m->split > 0) return m->split;
+  const int k = lanes_for(m->ncu, n);
+  const bool one_wave = (long)n * m->ops.chain[0].nparts <= (long)kLaneBlockHost * 4 * m->ncu;
+  return k == 1 && one_wave ? 2 : k;
 }
 
 long pair_blocks(int n, int split) { return ((long)n * split + kLaneBlockHost - 1) / kLaneBlockHost; }
 
 long chain_wpart_blocks(int n, int chunk, int split) {
+  // chunks of whole workgroups of atoms end with a workgroup
+  if (chunk >= n || chunk % kLaneBlockHost == 0) return pair_blocks(n, split);
   return pair_blocks(n, split) + (n / std::max(chunk, 1) + 1);
 }
 

@@ -60,6 +60,7 @@ struct ChainOps {
   int nmgroup;  // launches of moments (g < nmgroup)
   int nbgroup;  // passes of backward (grp < nbgroup), each over a range of the moment adjoints
   int nrgroup;  // launches of prog_rev (g < nrgroup)
+  int nparts;   // waves that share a tile's moment entries
 };
 
 // Parameter-adjoint launchers of one level (binary64).

@@ -1706,7 +1706,7 @@ struct EnergyChain {
   }
   static ChainOps ops() {
     return ChainOps{&moments, &prog_fwd, &prog_rev, &backward, one_launch() ? &program : nullptr, waves(), nmgroup(),
-                    nbgroup(), waves() ? 1 : L::NGROUP};
+                    nbgroup(), waves() ? 1 : L::NGROUP, std::is_same_v<R, double> ? L::NPART : 1};
   }
 };
 
