@@ -72,8 +72,9 @@ typedef struct {
   int precision;         /* MTP_FP64 or MTP_FP32_MOMENTS */
   int chunk_atoms;       /* atoms evaluated per chunk (bounds workspace, cf. the paper's
                             chunksize, Section 2.3); 0 = library default (1,048,576 atoms,
-                            about 2 KB of workspace per atom at level 16); at most 2^28,
-                            else MTP_ERR_ARG */
+                            about 2 KB of workspace per atom at level 16; in mtp_param_grad
+                            about 6 KB and a record of 16 (n_mu + 1) bytes for each of its
+                            pairs); at most 2^28, else MTP_ERR_ARG */
   double grade_select;   /* grade_max above this returns MTP_GRADE_SELECT; <= 0 disables */
   double grade_break;    /* grade_max above this returns MTP_GRADE_BREAK; <= 0 disables */
   int lanes_per_atom;    /* lanes that share one atom's neighbour loop in the binary64 pair
@@ -213,7 +214,10 @@ int mtp_maxvol(mtp_model* m, double* cand, int n_cand, int n, double* active, do
  * needs, computed on the device:
  *   d_linear [n_alpha], d_radial [n_species^2 n_mu n_cheb], d_shift [n_species] (device) =
  *   ebar dE/dtheta + sum_k fbar_k . dF_k/dtheta,  fbar device [N][3].
- * For the loss (E - E0)^2 + sum |F - F0|^2 pass ebar = 2 (E - E0), fbar = 2 (F - F0). */
+ * For the loss (E - E0)^2 + sum |F - F0|^2 pass ebar = 2 (E - E0), fbar = 2 (F - F0).
+ * With more than one chunk of atoms it synchronizes once (the pairs of each chunk are read from the
+ * list; not under stream capture, where a call with the workspace of an earlier one goes through
+ * windows of as many pairs). */
 int mtp_param_grad(mtp_model* m, const mtp_system* sys, const mtp_nlist* nl, double ebar,
                    const double* fbar, double* d_linear, double* d_radial, double* d_shift,
                    void* stream);
@@ -226,7 +230,8 @@ int mtp_param_grad(mtp_model* m, const mtp_system* sys, const mtp_nlist* nl, dou
  *   (host int array, atom_off[0] = 0, non-decreasing); pos (device [N][3]) and species
  *   (device [N]) are referenced, not copied, and must stay valid for the batch's lifetime;
  *   cells (host [n_cfg][9], rows = lattice vectors) are copied.  Builds every
- *   configuration's canonical neighbour list once (synchronizes) and reserves all workspace.
+ *   configuration's canonical neighbour list once (synchronizes) and reserves all workspace,
+ *   that of the loss gradient included (16 (n_mu + 1) bytes per pair beside the per-atom buffers).
  * mtp_batch_run: energies [n_cfg], forces [N][3], virials [n_cfg][6] (device, any may be
  *   NULL) of every configuration; with targets e_target [n_cfg] and f_target [N][3] also the
  *   loss L = sum_c (E_c - E0_c)^2 + sum_i |F_i - F0_i|^2 (loss [1], may be NULL) and its

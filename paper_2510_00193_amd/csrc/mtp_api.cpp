@@ -678,13 +678,34 @@ extern "C" int mtp_param_grad(mtp_model* m, const mtp_system* sys, const mtp_nli
   const int nchunks = (n + chunk - 1) / chunk;
   // the adjoint runs in binary64 whatever the model's precision
   const int split = m->split > 0 ? m->split : lanes_for(m->ncu, n);
-  const long nparts = pair_blocks(n, split);
+  long nparts = 0;
+  for (int i0 = 0; i0 < n; i0 += chunk) nparts += pair_blocks(std::min(chunk, n - i0), split);
+  // first pair of each chunk; the pair records of one chunk are kept at a time
+  std::vector<int> cut(nchunks + 1, 0);
+  cut[nchunks] = (int)use.n_pairs;
+  int window = cut[nchunks];
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  if (nchunks > 1) HIP_TRY(hipStreamIsCapturing(s, &capture));
+  const size_t record = L.adj.record * sizeof(double);
+  if (capture != hipStreamCaptureStatusNone) {
+    // the offsets cannot be read here: every chunk goes through windows of as many pairs as an earlier
+    // call left room for (a chunk's pairs lie in a few of them, the launches for the others find nothing
+    // to do), or through one of all pairs
+    const size_t room = m->rec.bytes / record;
+    if (room >= (size_t)(window / nchunks)) window = (int)std::max<size_t>(1, std::min<size_t>(room, window));
+  } else if (nchunks > 1) {
+    HIP_TRY(hipMemcpy2DAsync(cut.data(), sizeof(int), use.off, (size_t)chunk * sizeof(int), sizeof(int), nchunks,
+                             hipMemcpyDeviceToHost, s));
+    HIP_TRY(hipStreamSynchronize(s));
+    window = 0;
+    for (int k = 0; k < nchunks; ++k) window = std::max(window, cut[k + 1] - cut[k]);
+  }
   if ((rc = m->mom.reserve((size_t)L.nmom * ld * 8)) || (rc = m->cbar.reserve((size_t)L.ncomp * ld * 8)) ||
       (rc = m->mbar.reserve((size_t)L.nmom * ld * 8)) || (rc = m->mdot.reserve((size_t)L.nmom * ld * 8)) ||
       (rc = m->cbard.reserve((size_t)L.ncomp * ld * 8)) || (rc = m->mbard.reserve((size_t)L.nmom * ld * 8)) ||
       (rc = m->xout.reserve((size_t)na * ld * 8)) || (rc = m->eatom.reserve((size_t)n * 8)) ||
       (rc = m->dxi_part.reserve((size_t)na * nchunks * 8)) || (rc = m->cpart.reserve((size_t)nparts * K * 8)) ||
-      (rc = m->rec.reserve((size_t)std::max<long long>(use.n_pairs, 1) * L.adj.record * 8)) ||
+      (rc = m->rec.reserve(std::max(window, 1) * record)) ||
       (rc = m->rsum.reserve((size_t)std::max<long>(na, K) * kRowParts * 8)))
     return rc;
   SysArgs a = make_sys_args(m, sys, use);
@@ -694,6 +715,7 @@ extern "C" int mtp_param_grad(mtp_model* m, const mtp_system* sys, const mtp_nli
   double *xout = (double*)m->xout.p, *dxp = (double*)m->dxi_part.p, *cpart = (double*)m->cpart.p;
   double* rec = (double*)m->rec.p;
   int c = 0;
+  long blk = 0;
   for (int i0 = 0; i0 < n; i0 += chunk, ++c) {
     const int cn = std::min(chunk, n - i0);
     for (int g = 0; g < L.chain[0].nmgroup; ++g) {
@@ -729,16 +751,19 @@ extern "C" int mtp_param_grad(mtp_model* m, const mtp_system* sys, const mtp_nli
       ProfScope ps(&m->prof, P_TANGENT, s);
       L.adj.tan_reverse[g](mom, mdot, ld, cn, xi, cbar, cbard, mbard, s);
     }
-    {
+    const bool known = capture == hipStreamCaptureStatusNone;
+    const int begin = known ? cut[c] : 0, end = known ? cut[c + 1] : cut[nchunks];
+    long long lo = begin;
+    do {
+      const int hi = (int)std::min<long long>(lo + window, end);
       ProfScope ps(&m->prof, P_ADJ_PAIRS, s);
-      L.adj.adj_pairs(a, fbar, i0, cn, mbar, mbard, ld, ebar, rec, s);
-    }
+      L.adj.adj_pairs(a, fbar, i0, cn, mbar, mbard, ld, ebar, rec, (int)lo, hi, s);
+      L.adj.adj_radial(a, i0, cn, rec, (int)lo, hi, lo > begin, cpart + blk * K, s);
+      lo = hi;
+    } while (lo < end);
+    blk += pair_blocks(cn, split);
     ProfScope ps(&m->prof, P_REDUCE, s);
     launch_rowsum(xout, ld, 1, cn, na, nchunks > 1 ? dxp + c : d_linear, nchunks, s, (double*)m->rsum.p);
-  }
-  {
-    ProfScope ps(&m->prof, P_ADJ_PAIRS, s);
-    L.adj.adj_radial(a, n, rec, cpart, s);
   }
   {
     ProfScope ps(&m->prof, P_REDUCE, s);

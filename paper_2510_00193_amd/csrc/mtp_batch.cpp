@@ -309,7 +309,8 @@ static void run_impl(mtp_batch* b, const double* e_target, const double* f_targe
     {
       ProfScope ps(&m->prof, P_ADJ_PAIRS, s);
       a.queue = q();
-      L.adj.adj_pairs(a, fbar, (int)i0, cn, (const double*)b->mbar.p, (const double*)b->mbard.p, ld, 0.0, rec, s);
+      L.adj.adj_pairs(a, fbar, (int)i0, cn, (const double*)b->mbar.p, (const double*)b->mbard.p, ld, 0.0, rec, 0,
+                      (int)b->npairs, s);
     }
     ProfScope ps(&m->prof, P_REDUCE, s);
     launch_rowsum((const double*)b->xout.p, ld, 1, cn, L.nalpha,
@@ -318,7 +319,7 @@ static void run_impl(mtp_batch* b, const double* e_target, const double* f_targe
   {
     ProfScope ps(&m->prof, P_ADJ_PAIRS, s);
     a.perm = (const int*)b->perm_sp.p;
-    L.adj.adj_radial(a, n, rec, cpart, s);
+    L.adj.adj_radial(a, 0, n, rec, 0, (int)b->npairs, false, cpart, s);
   }
   ProfScope ps(&m->prof, P_REDUCE, s);
   if (nchunks > 1) launch_rowsum(dxp, nchunks, 1, nchunks, L.nalpha, d_linear, 1, s);

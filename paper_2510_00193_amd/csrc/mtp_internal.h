@@ -73,11 +73,13 @@ struct AdjOps {
   void (*tan_reverse[kMaxRevParts])(const double* m, const double* md, long ld, int n, const double* xi,
                                     const double* cb, const double* cbd, double* mbd, hipStream_t s);
   int nrtpart;
-  // adj_pairs leaves a record of `record` doubles per pair (indexed by the list), adj_radial sums the
-  // records of atoms 0 .. n - 1 into cpart [split_tiles(n, a.split)][nsp * nsp * nmu * ncheb]
+  // of the pairs lo .. hi - 1 of the list adj_pairs leaves a record of `record` doubles each (pair p at
+  // p - lo), and adj_radial sums those of atoms i0 .. i0 + n - 1 into (add: onto)
+  // cpart [split_tiles(n, a.split)][nsp * nsp * nmu * ncheb]
   void (*adj_pairs)(const SysArgs& a, const double* fbar, int i0, int n, const double* mb, const double* mbd,
-                    long ld, double ebar, double* rec, hipStream_t s);
-  void (*adj_radial)(const SysArgs& a, int n, const double* rec, double* cpart, hipStream_t s);
+                    long ld, double ebar, double* rec, int lo, int hi, hipStream_t s);
+  void (*adj_radial)(const SysArgs& a, int i0, int n, const double* rec, int lo, int hi, bool add, double* cpart,
+                     hipStream_t s);
   int record;
 };
 
