@@ -78,11 +78,12 @@ typedef struct {
   double grade_select;   /* grade_max above this returns MTP_GRADE_SELECT; <= 0 disables */
   double grade_break;    /* grade_max above this returns MTP_GRADE_BREAK; <= 0 disables */
   int lanes_per_atom;    /* lanes that share one atom's neighbour loop in the binary64 pair
-                            kernels (moments, pair gradients) of a single system: 1, 2, 4 or 8,
-                            or 0 = chosen from the system size so that the waves cover the
-                            GPU's SIMDs (small systems; cf. the paper's block-parallel variant
-                            for small atom counts, Section 2.1).  The binary32 form and batches
-                            use one lane per atom. */
+                            kernels, of single systems and of batches (moments, pair gradients,
+                            and those of the coefficient gradient, which is binary64 whatever
+                            the precision): 1, 2, 4 or 8, or 0 = chosen from the number of
+                            atoms so that the waves cover the GPU's SIMDs (small systems; cf.
+                            the paper's block-parallel variant for small atom counts, Section
+                            2.1).  Evaluations in the binary32 form use one lane per atom. */
 } mtp_params;
 
 typedef struct {
@@ -243,13 +244,14 @@ int mtp_param_grad(mtp_model* m, const mtp_system* sys, const mtp_nlist* nl, dou
  *   replays without re-capture.
  * mtp_batch_tune: times the schedules on this batch and keeps the fastest: atom order (natural,
  *   or sorted by neighbour count so that a wave's lanes do similar work and the longest tiles
- *   come first), chunk of atoms per pass, and static grids or persistent pair kernels (one
- *   workgroup per SIMD pulling 64-atom tiles from a device counter inside the same launch
- *   sequence, zeroed by a kernel so that graph capture stays valid); with cache_path (text
+ *   come first), chunk of atoms per pass, and, with one lane per atom, static grids or persistent
+ *   pair kernels (one workgroup per SIMD pulling 64-atom tiles from a device counter inside the
+ *   same launch sequence, zeroed by a kernel so that graph capture stays valid); with cache_path (text
  *   file) the pick is read back for the same level, species, Chebyshev count and size bucket.
  *   choice (host [3], may be NULL) receives {sorted, chunk_atoms, persistent}.  Synchronizes.
  * mtp_batch_schedule: sets a schedule explicitly (sorted 0/1, chunk_atoms 0 = all atoms,
- *   persistent 0/1).
+ *   persistent 0/1; with more than one lane per atom, which small batches take unless
+ *   lanes_per_atom is 1, persistent counts as 0).  mtp_batch_sizes reports what runs.
  * mtp_batch_neighbors: device pointers of the batch's CSR list (global atom indices). */
 typedef struct mtp_batch mtp_batch;
 int mtp_batch_create(mtp_model* m, int n_cfg, const int* atom_off, const double* pos, const int* species,

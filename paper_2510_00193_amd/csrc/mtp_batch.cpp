@@ -81,9 +81,9 @@ static long chunk_of(const mtp_batch* b) {
   return std::max(1, std::min(std::min(b->chunk > 0 ? b->chunk : b->n, b->n), kMaxChunk));
 }
 
-// Lanes per atom: by the batch's size, as for one system (not by the chunk, and the same for every
+// Lanes per atom: the model's setting, or by the batch's size (not by the chunk, and the same for every
 // schedule, so that forces do not depend on it).
-static int batch_split(const mtp_batch* b) { return lanes_for(b->m->ncu, b->n); }
+static int batch_split(const mtp_batch* b) { return b->m->split > 0 ? b->m->split : lanes_for(b->m->ncu, b->n); }
 
 // Reserve every buffer the run needs for the current schedule (never called during capture).
 static int reserve_run(mtp_batch* b) {
@@ -138,7 +138,9 @@ static std::vector<int> order_by_count(const mtp_batch* b, const int* sp, int ns
 static int set_schedule(mtp_batch* b, int sorted, int chunk, int persistent) {
   b->sorted = sorted ? 1 : 0;
   b->chunk = chunk > 0 ? std::min(chunk, b->n) : b->n;
-  b->persistent = persistent ? 1 : 0;
+  // the kernels of more lanes per atom have no persistent form (their small batches are one round of
+  // workgroups): recorded as what runs
+  b->persistent = persistent && batch_split(b) == 1 ? 1 : 0;
   if (b->persistent) {
     // one workgroup per SIMD: the lane-per-atom pair kernels run one wave per SIMD
     int dev = 0, ncu = 256;
@@ -577,7 +579,7 @@ int mtp_batch_tune(mtp_batch* b, const char* cache_path, int* choice, void* stre
   for (int so = 0; so < 2; ++so) {
     for (int ch : chunks) {
       if (ch > 0 && ch >= b->n) continue;
-      for (int pe = 0; pe < 2; ++pe) {
+      for (int pe = 0; pe < (batch_split(b) == 1 ? 2 : 1); ++pe) {
         if ((rc = set_schedule(b, so, ch, pe))) return rc;
         const double* z = (const double*)b->zeros.p;
         run_impl(b, z, z, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, (double*)dl.p, (double*)dr.p,
