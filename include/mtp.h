@@ -245,8 +245,9 @@ int mtp_param_grad(mtp_model* m, const mtp_system* sys, const mtp_nlist* nl, dou
  * mtp_batch_tune: times the schedules on this batch and keeps the fastest: atom order (natural,
  *   or sorted by neighbour count so that a wave's lanes do similar work and the longest tiles
  *   come first), chunk of atoms per pass, and, with one lane per atom, static grids or persistent
- *   pair kernels (one workgroup per SIMD pulling 64-atom tiles from a device counter inside the
- *   same launch sequence, zeroed by a kernel so that graph capture stays valid); with cache_path (text
+ *   pair kernels (as many workgroups as the GPU runs at a time, pulling 64-atom tiles from a device
+ *   counter inside the same launch sequence, zeroed by a kernel so that graph capture stays valid);
+ *   with cache_path (text
  *   file) the pick is read back for the same level, species, Chebyshev count and size bucket.
  *   choice (host [3], may be NULL) receives {sorted, chunk_atoms, persistent}.  Synchronizes.
  * mtp_batch_schedule: sets a schedule explicitly (sorted 0/1, chunk_atoms 0 = all atoms,

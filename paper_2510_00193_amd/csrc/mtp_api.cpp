@@ -386,7 +386,6 @@ SysArgs make_sys_args(const mtp_model* m, const mtp_system* sys, const mtp_nlist
   a.nmu = m->ops.nmu;
   a.ncheb = m->ncheb;
   a.queue = nullptr;
-  a.pgrid = 0;
   a.simds = 4 * m->ncu;
   a.split = pair_split(m, sys->n_atoms);
   return a;

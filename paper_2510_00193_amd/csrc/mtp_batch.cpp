@@ -44,7 +44,6 @@ struct mtp_batch {
   DevBuf eatom, watom, g, fown, forces, energy, virial, mom, cbar, mbar, mdot, cbard, mbard, xout, dxi_part,
       cpart, wpart, ebar_cfg, fbar, parts, zeros, rsum;
   DevBuf queue;                    // tile counters of the persistent pair-kernel launches
-  int pgrid = 0;                   // workgroups of a persistent launch
   // schedule
   int sorted = 0, chunk = 0, persistent = 0;
   // graph
@@ -142,10 +141,6 @@ static int set_schedule(mtp_batch* b, int sorted, int chunk, int persistent) {
   // workgroups): recorded as what runs
   b->persistent = persistent && batch_split(b) == 1 ? 1 : 0;
   if (b->persistent) {
-    // one workgroup per SIMD: the lane-per-atom pair kernels run one wave per SIMD
-    int dev = 0, ncu = 256;
-    if (hipGetDevice(&dev) == hipSuccess) (void)hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
-    b->pgrid = 4 * ncu;
     int rc = b->queue.reserve((size_t)pair_launches(b) * sizeof(int));
     if (rc) return rc;
   }
@@ -198,7 +193,7 @@ static void run_impl(mtp_batch* b, const double* e_target, const double* f_targe
   a.nmu = L.nmu;
   a.ncheb = m->ncheb;
   a.queue = nullptr;
-  a.pgrid = b->pgrid;
+  a.simds = 4 * m->ncu;
   a.split = batch_split(b);
   // persistent schedule: one zeroed tile counter per pair-kernel launch (a kernel, not a memset,
   // so that the sequence can be captured into a graph)

@@ -28,11 +28,10 @@ struct SysArgs {
   double sa, sb, rcut;    // u = sa r + sb
   int nsp, nmu, ncheb;
   // persistent launches of the pair kernels: a device counter from which workgroups pull their
-  // 64-atom tiles (zeroed before the launch), and the number of workgroups; null for a grid of
-  // one workgroup per tile
+  // 64-atom tiles (zeroed before the launch), in as many workgroups as the device holds at a time; null
+  // for a grid of one workgroup per tile
   int* queue;
-  int pgrid;
-  int simds;  // SIMDs of the device (single systems)
+  int simds;  // SIMDs of the device
   // lanes per atom of the pair kernels (1, 2, 4 or 8): with more than one, the
   // lanes of an atom take every split-th pair of its row and combine their sums
   int split;

@@ -87,7 +87,14 @@ __device__ __forceinline__ double wave_sum(double v) {
   return v;
 }
 
-inline int pair_grid(const SysArgs& a, int nb) { return a.queue && a.split == 1 ? std::max(1, std::min(nb, a.pgrid)) : nb; }
+// Workgroups of a pair kernel: one per tile (nb), or, persistent, as many of `waves` waves as the SIMDs hold:
+// two waves each where a tile is cut into `parts`, else one.  Passes with persistent kernels, workgroups for
+// one wave per SIMD -> for two, ms: 540,428 atoms of level 20 16.79 -> 15.96, 272,280 of level 16 2.44 -> 2.33
+// (one-shot 15.89, 2.33), but 540,428 of level 10 in sorted order 2.58 -> 2.87.
+inline int pair_grid(const SysArgs& a, int nb, int parts, int waves) {
+  if (!a.queue || a.split != 1) return nb;
+  return std::max(1, std::min(nb, a.simds * (parts > 1 ? 2 : 1) / waves));
+}
 
 // Accessors of [row][atom] arrays in global memory.  The address of a row is the same for the
 // whole wave (scalar registers) and each lane adds its byte offset, so a load takes the
@@ -1591,7 +1598,7 @@ constexpr bool may_run_alone() { return std::is_same_v<R, double> && !BATCH && L
 
 template <class L, int G, class R, bool BATCH, bool PERSIST, int K = 1>
 void launch_moments_gp(const SysArgs& a, int i0, int n, void* m, long ld, hipStream_t s) {
-  const int nb = pair_grid(a, split_tiles(n, K) * (std::is_same_v<R, double> ? L::NPART : 1));
+  const int nb = pair_grid(a, split_tiles(n, K) * (std::is_same_v<R, double> ? L::NPART : 1), L::NPART, 1);
   if constexpr (may_run_alone<L, R, BATCH>()) {
     if (nb <= a.simds) return launch_moments_nc<L, G, R, BATCH, PERSIST, K, true>(a, nb, i0, n, m, ld, s);
   }
@@ -1620,7 +1627,7 @@ void launch_rev_g(const void* m, long ld, int n, const void* cb, void* mb, hipSt
 template <class L, int G, class R, bool BATCH, bool PERSIST, int K, int NC>
 void launch_backward_nc(const SysArgs& a, int i0, int n, const void* mb, long ld, double* g, double* wpart,
                         double* watom, double* fown, hipStream_t s) {
-  const int nb = pair_grid(a, split_tiles(n, K));
+  const int nb = pair_grid(a, split_tiles(n, K), L::NPART, L::NPART);
   const unsigned sh = radial_bytes<R>(a);
   if constexpr (std::is_same_v<R, double> && L::NPART > 1) {
     hipLaunchKernelGGL((k_backward_stages<L, BATCH, NC, PERSIST, K>), dim3(nb), dim3(kLaneBlock * L::NPART), sh, s, a,
@@ -1737,7 +1744,7 @@ template <class L>
 struct AdjImpl {
   template <int NC, bool PERSIST, int K>
   static void tan_moments_k(const SysArgs& a, const double* fbar, int i0, int n, double* md, long ld, hipStream_t s) {
-    const int nb = pair_grid(a, split_tiles(n, K) * L::NTPART);
+    const int nb = pair_grid(a, split_tiles(n, K) * L::NTPART, L::NTPART, 1);
     hipLaunchKernelGGL((k_tan_moments<L, NC, PERSIST, K>), dim3(nb), dim3(kLaneBlock), radial_bytes<double>(a), s, a,
                        fbar, i0, n, md, ld);
   }
@@ -1777,7 +1784,7 @@ struct AdjImpl {
   template <bool PERSIST, int K>
   static void adj_pairs_k(const SysArgs& a, const double* fbar, int i0, int n, const double* mb, const double* mbd,
                           long ld, double ebar, double* rec, int lo, int hi, hipStream_t s) {
-    const int nb = pair_grid(a, split_tiles(n, K));
+    const int nb = pair_grid(a, split_tiles(n, K), L::NASTAGE, L::NASTAGE);
     if (PERSIST || (lo == 0 && hi == a.npairs))
       hipLaunchKernelGGL((k_adj_stages<L, PERSIST, K>), dim3(nb), dim3(kLaneBlock * L::NASTAGE), 0, s, a, fbar, i0, n, mb,
                          mbd, ld, ebar, rec, lo, hi);
