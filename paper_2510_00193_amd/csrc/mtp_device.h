@@ -62,19 +62,27 @@ __device__ __forceinline__ double dist2_exact(double dx, double dy, double dz) {
   return (dx * dx + dy * dy) + dz * dz;
 }
 
-// r = sqrt(dd) and 1/r from the hardware estimate (2^-24) by two Newton steps on r and one more
-// on 1/r: within an ulp, without the scaling and special-value selects of sqrt and the division
-// sequence of 1/r (together about 30 instructions less per pair).  dd = 0 gives r = 0; below
-// 1e-290 r is not accurate (it is zero to rounding next to any other term).
-__device__ __forceinline__ void root_and_inverse(double dd, double& r, double& rinv) {
-  const double y = __builtin_amdgcn_rsq(fmax(dd, 1e-290));
+// r = sqrt(dd) and 1/r from an estimate y0 of 1/sqrt(dd) to 2^-23 or better: one step of Goldschmidt's
+// coupled iteration on (sqrt(dd), 1/(2 sqrt(dd))), a closing Newton step on r and one on 1/r.  r is
+// within 0.501 ulp of the root and 1/r within 0.501 ulp of the inverse of that r, where sqrt and a division
+// would be within 0.5.  dd = 0 gives r = 0 and 1/r infinite (pairs at no
+// distance have no direction: their gradients are not numbers), dd NaN gives NaN; below 1e-290 r is not
+// accurate (it is zero to rounding next to any other term).
+__host__ __device__ __forceinline__ void root_from_estimate(double dd, double y0, double& r, double& rinv) {
+  const double y = fmin(y0, 1e145);
   double g = dd * y, h = 0.5 * y;
   const double e = fma(-h, g, 0.5);
   g = fma(g, e, g);
   h = fma(h, e, h);
   r = fma(fma(-g, g, dd), h, g);
   const double y1 = 2.0 * h;
-  rinv = fma(fma(-r, y1, 1.0), y1, y1);
+  rinv = fma(fma(-r, y1, 1.0), y0, y1);  // the residual times y0, not y1: infinite at dd = 0
+}
+
+// The same from the hardware's estimate (2^-24), without the scaling and special-value selects of sqrt
+// and the division sequence of 1/r (together about 30 instructions less per pair).
+__device__ __forceinline__ void root_and_inverse(double dd, double& r, double& rinv) {
+  root_from_estimate(dd, __builtin_amdgcn_rsq(dd), r, rinv);
 }
 
 // Radial functions of one pair: f_mu = w^2 A_mu, f'_mu = w (a w D_mu - 2 A_mu), with
