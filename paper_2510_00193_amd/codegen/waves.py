@@ -31,12 +31,19 @@ PIECE = 12
 AHEAD = 24  # values from memory held for the next block
 LDS_ROWS = 318  # rows of 64 doubles in the 160 KB of a compute unit, less the static variables
 
-# Waves per tile by level: forward, reverse, forward tangent, reverse tangent.  At level 20 four waves of
-# 512 registers hold the accumulators of the reverse programs (no spills; eight of 256 would spill).
+# Waves per tile by level: forward, reverse, forward tangent, reverse tangent.  From level 18 on four waves
+# of 512 registers hold the accumulators of the reverse programs (no spills; eight of 256 would spill).
 # Up to level 10 one lane runs the whole program, which holds all of it in registers: two waves gave
 # 0.5 % less at 250,000 atoms, 1 % more in a fit of 2048 configurations and 4 % less in a coefficient
-# gradient of 50,000 atoms.  At level 12 two waves give 1.1 % (338 against 341 us at 250,000 atoms) and
-# 2.2 % (1692 against 1729 us, the fit), at level 16 7 % and at level 20 66 % of the programs' time.
+# gradient of 50,000 atoms.  Both programs (for grades the forward alone), one lane -> waves, us:
+#   level 12:   9,000 atoms 7.3 -> 7.2, 20,000 8.0 -> 8.2, 51,000 11.5 -> 11.9, 119,000 21.8 -> 21.9,
+#               250,000 44.5 -> 36.7 (forward 6.4 -> 6.3, 6.8 -> 6.7, 10.7 -> 10.9, 16.0 -> 16.7, 34.8 -> 29.3);
+#               a minibatch of 64 configurations as a whole 340 -> 344, a fit of 2048 1729 -> 1692: even up to
+#               100,000 atoms, and kept for what is larger
+#   level 14:   9,000 atoms 12.5 -> 9.4, 63,000 23.1 -> 22.0, 250,000 86.8 -> 70.3 (forward 62.9 -> 60.2)
+#   level 16:   1008 atoms 20 -> 12.9, 1,024,000 742 -> 588
+#   level 18:   1024 atoms 70 -> 30, 250,000 625 -> 550 (forward 190 -> 149)
+#   level 20:   31,416 atoms 385 -> 130
 WAVES = {12: (2, 2, 2, 2), 14: (4, 4, 4, 4), 16: (4, 4, 4, 4), 18: (8, 4, 8, 4), 20: (8, 4, 8, 4)}
 
 
