@@ -2,9 +2,11 @@
 // (struct LvXX with the straight-line program) and then this file, and instantiates the
 // launchers with MTP_DEFINE_CHAIN / MTP_DEFINE_ADJ / MTP_DEFINE_ADJ_FWD / MTP_DEFINE_ADJ_REV.
 //
-// Every kernel maps one lane to one atom: the per-atom state (moments, contraction
-// outputs, adjoints) lives in registers with compile-time indices, the neighbour loop of
-// the lane walks the atom's CSR row.
+// The pair kernels give an atom one lane, or two, four or eight where there are few atoms; levels of many
+// entries cut them over waves that each hold a part of the atom's moments or adjoints in registers (with
+// compile-time indices) and walk the same CSR row, or hand its pairs on along a pipeline.  The contraction
+// programs run one lane per atom up to level 10 and in binary32, above in several waves per 64 atoms with
+// the moments in LDS.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -339,8 +341,9 @@ __device__ __forceinline__ void for_pairs(const SysArgs& a, int* lst, int i, int
   }
 }
 
-// The same with T steps in every lane, for the first wave of a pipeline of waves: a lane past its len
-// pairs repeats the last one, a lane without pairs takes atom i itself (its results are dropped).
+// The same with T steps in every lane, for the first wave of a pipeline of waves.  A lane past its len pairs
+// repeats its last one, or, without pairs in the present stage of its row, takes atom i itself, at no
+// distance; the results of these steps are dropped.
 template <int K, bool TAN, class F>
 __device__ __forceinline__ void for_steps(const SysArgs& a, int* lst, int i, int lane, int p0, int len, int T,
                                           const double* H, const Partner<TAN>& own, const double* __restrict__ fbar,
@@ -427,8 +430,8 @@ __device__ __forceinline__ void cell_of(const SysArgs& a, int i, double* H) {
 }
 
 // One part of the moments (binary64) or one group of the layout (binary32) of one atom: K lanes
-// per atom (single systems) each accumulate every K-th pair of the row, the partial moments are
-// summed over the atom's lanes and its first lane writes them.
+// per atom each accumulate every K-th pair of the row, the partial moments are summed over the atom's
+// lanes and its first lane writes them.
 template <class L, int P, class R, bool BATCH, int NC, int K>
 __device__ __forceinline__ void moments_of_atom(const SysArgs& a, const R* csh, int* lst, int i, int li, int sub,
                                                 R* __restrict__ mout, long ld) {
@@ -467,7 +470,7 @@ __device__ __forceinline__ void moments_of_atom(const SysArgs& a, const R* csh, 
 // entries of level 16 filled the registers of a SIMD by itself, moved a third of its accumulators
 // through accumulation registers for every pair and stood waiting on its loads a quarter of the
 // time.  The parts repeat a pair's geometry and radial functions, but two waves share a SIMD:
-// 0.73 -> 0.59 ms at 1,024,000 atoms of level 16 (the vector unit is busy three quarters of it),
+// 0.73 -> 0.59 ms at 1,024,000 atoms of level 16 (the vector unit is busy about 0.6 of it),
 // 1.93 -> 1.17 ms at level 20 (545,505 atoms; it took three passes before).
 // Binary32: group G of the layout.
 // ALONE: one wave per SIMD (launch_moments_g).
@@ -588,8 +591,9 @@ __global__ __launch_bounds__(kLaneBlock) void k_program(const R* __restrict__ mo
 // or more read) are staged in LDS once ([row][atom]).  With one lane running the whole program the re-reads of shared
 // moments missed L2 (twice the moments fetched at level 16, 5 times at level 20) and the single wave
 // of a SIMD stood waiting for them four fifths of its time at level 20, where the contraction values
-// and adjoints of 160 components also went to scratch (up to 8.9 KB per lane).  Now the arithmetic is
-// half to three quarters of a tile's time, waits for LDS most of the rest.  Measured before -> after, us:
+// and adjoints of 160 components also went to scratch (up to 8.9 KB per lane).  Now the
+// vector unit is busy 0.27 of the time at level 16, where 2.1 GB at a million atoms and waits for LDS take
+// the rest.  Measured before -> after, us:
 //   level 16: 1008 atoms 20 -> 12.9 (both programs); 1,024,000 atoms 742 -> 588 (2.1 GB moved: 3.6 TB/s)
 //   level 20: 31,416 atoms 385 -> 130 (forward 42, reverse 88)
 //   level 20, 540,480 atoms in a batch: forward 2200 -> 650, reverse 2460 -> 1500, tangent of the forward
@@ -886,7 +890,7 @@ constexpr int gradient_occupancy(int entries) { return entries > 64 ? 1 : 2; }
 // g[p] (+)= dE_i/dd_ij restricted to the entries of group G (binary32; binary64 levels of one part
 // take the whole adjoint by pair_part); per-workgroup virial partials;
 // fown[i] (+)= sum of the atom's own g over its row (the first half of its force), when given.
-// K lanes per atom (single systems): each takes every K-th pair of the row; the own sums are
+// K lanes per atom: each takes every K-th pair of the row; the own sums are
 // combined over the atom's lanes, the virial partial over the workgroup as before.
 template <class L, int G, class R, bool BATCH, int NC, bool PERSIST = false, int K = 1, bool ALONE = false>
 __global__ __launch_bounds__(kLaneBlock)
@@ -960,8 +964,8 @@ void k_backward(SysArgs a, int i0, int n, const R* __restrict__ mbar, long ld, d
 // leaves displacement, gradient so far and the radial factors of the other parts in an LDS slot;
 // each further wave adds its part one step later, the wave of part 0 stores the gradient and
 // takes the sums.  One barrier per step; a ring of NPART slots keeps the stages apart.  All lanes
-// run the same number of steps (the longest row of the tile); a lane past its row repeats its
-// last pair and its result is dropped.
+// run the same number of steps (the longest row of the tile); what a lane does past its
+// row is dropped.
 // One wave holding all 130 adjoints of level 16 filled a SIMD, read 100 accumulation registers per
 // pair and stood waiting a quarter of its time: 1.27 ms at 1,024,000 atoms with the monomial form and
 // list reads pair by pair, 0.95 with Horner's scheme and staged rows, 0.85 as a pipeline; at level 20
@@ -1650,7 +1654,7 @@ void launch_backward_gp(const SysArgs& a, int i0, int n, const void* mb, long ld
   else if (a.ncheb == 10) launch_backward_nc<L, G, R, BATCH, PERSIST, K, 10>(a, i0, n, mb, ld, g, wpart, watom, fown, s);
   else launch_backward_nc<L, G, R, BATCH, PERSIST, K, 0>(a, i0, n, mb, ld, g, wpart, watom, fown, s);
 }
-// the virial partials: one per workgroup, split_tiles(n, a.split) of them for a single system
+// the virial partials: one per tile, split_tiles(n, a.split) of them
 template <class L, int G, class R, bool BATCH>
 void launch_backward_g(const SysArgs& a, int i0, int n, const void* mb, long ld, double* g,
                        double* wpart, double* watom, double* fown, hipStream_t s) {
