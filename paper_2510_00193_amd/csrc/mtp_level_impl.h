@@ -164,19 +164,30 @@ struct RegMoments {
 };
 
 // radial coefficient table staged in LDS (in the arithmetic type of the kernel); dynamic shared
-// memory of radial_bytes at the launch, so that a small table leaves room for more waves
-template <class R>
+// memory of radial_bytes at the launch, so that a small table leaves room for more waves.  The rows of two
+// species are an odd number of values apart: lanes of a wave read the same place of different rows, and
+// rows of a multiple of 32 values (8 Chebyshev functions of 4 radial functions) would meet in the same
+// banks.  The parts of a tile each read the table: grade of 101,306 atoms at level 16, 16 functions and
+// four species, 399 us in one part with rows end to end, 479 in two parts, 278 with odd rows.
+template <int NMU, int NC = 0>
+__host__ __device__ __forceinline__ int radial_row(int ncheb) { return NMU * (NC > 0 ? NC : ncheb) | 1; }
+
+template <class R, int NMU>
 __device__ __forceinline__ R* stage_radial(const SysArgs& a) {
   extern __shared__ __align__(16) double radial_table_[];
   R* sh = reinterpret_cast<R*>(radial_table_);
-  const int n = a.nsp * a.nsp * a.nmu * a.ncheb;
-  for (int k = threadIdx.x; k < n; k += blockDim.x) sh[k] = (R)a.radial[k];
+  const int row = NMU * a.ncheb, n = a.nsp * a.nsp * row;
+  if (row & 1 || a.nsp == 1) {
+    for (int k = threadIdx.x; k < n; k += blockDim.x) sh[k] = (R)a.radial[k];
+  } else {
+    for (int k = threadIdx.x; k < n; k += blockDim.x) sh[k + (unsigned)k / (unsigned)row] = (R)a.radial[k];
+  }
   __syncthreads();
   return sh;
 }
-template <class R>
+template <class R, int NMU>
 inline unsigned radial_bytes(const SysArgs& a) {
-  return (unsigned)(a.nsp * a.nsp * a.nmu * a.ncheb * (int)sizeof(R));
+  return (unsigned)(a.nsp * a.nsp * radial_row<NMU>(a.ncheb) * (int)sizeof(R));
 }
 
 // One lane per atom: the lanes of a wave read 64 different rows of the list, so each 4-byte read
@@ -445,10 +456,10 @@ __device__ __forceinline__ void moments_of_atom(const SysArgs& a, const R* csh, 
   for (int e = 0; e < NE; ++e) m[e] = R(0);
   Partner<false> own;
   own.load(a, nullptr, i);
-  const R* cz = csh + clamp_species(own.s, a.nsp) * a.nsp * L::NMU * a.ncheb;
+  const R* cz = csh + clamp_species(own.s, a.nsp) * a.nsp * radial_row<L::NMU, NC>(a.ncheb);
   for_pairs<K, R, false>(a, lst, i, sub, H, own, nullptr, [&](int, const Pair& t) {
     R f[L::NMU];
-    radial_values<R, L::NMU, NC>((R)t.r, (R)a.sa, (R)a.sb, (R)a.rcut, cz + t.zj * L::NMU * a.ncheb, a.ncheb, f);
+    radial_values<R, L::NMU, NC>((R)t.r, (R)a.sa, (R)a.sb, (R)a.rcut, cz + t.zj * radial_row<L::NMU, NC>(a.ncheb), a.ncheb, f);
     if constexpr (PARTS) L::template acc_part<P>(m, f, (R)t.dx, (R)t.dy, (R)t.dz);
     else L::template acc_moments<P>(m, f, (R)t.dx, (R)t.dy, (R)t.dz);
   });
@@ -480,7 +491,7 @@ __attribute__((amdgpu_waves_per_eu(std::is_same_v<R, double> && !ALONE ? 2 : 1, 
 void k_moments(SysArgs a, int i0, int n, R* __restrict__ mout, long ld) {
   constexpr int NP = std::is_same_v<R, double> ? L::NPART : 1;
   __shared__ int lst[K == 1 ? kStageInts : 1];
-  const R* csh = stage_radial<R>(a);
+  const R* csh = stage_radial<R, L::NMU>(a);
   MTP_FOR_TILES_K(a, n, K, NP, b) {
   // parts of a tile in consecutive workgroups: they read the same rows
   const int li = (b / NP) * (kLaneBlock / K) + (int)threadIdx.x / K, sub = (int)threadIdx.x % K;
@@ -904,7 +915,7 @@ void k_backward(SysArgs a, int i0, int n, const R* __restrict__ mbar, long ld, d
   constexpr int NG = PARTS ? L::NMOM : L::GROUP_HI[PARTS ? 0 : G] - LO;
   static_assert(!PARTS || L::NPART == 1, "levels of several parts take k_backward_stages");
   __shared__ int lst[K == 1 ? kStageInts : 1];
-  const R* csh = stage_radial<R>(a);
+  const R* csh = stage_radial<R, L::NMU>(a);
   MTP_FOR_TILES_K(a, n, K, 1, b) {
   const int li = b * (kLaneBlock / K) + (int)threadIdx.x / K, sub = (int)threadIdx.x % K;
   double w[6] = {0, 0, 0, 0, 0, 0};
@@ -923,7 +934,7 @@ void k_backward(SysArgs a, int i0, int n, const R* __restrict__ mbar, long ld, d
     }
     Partner<false> own;
     own.load(a, nullptr, i);
-    const R* cz = csh + clamp_species(own.s, a.nsp) * a.nsp * L::NMU * a.ncheb;
+    const R* cz = csh + clamp_species(own.s, a.nsp) * a.nsp * radial_row<L::NMU, NC>(a.ncheb);
     for_pairs<K, R, false>(a, lst, i, sub, H, own, nullptr, [&](int p, const Pair& t) {
       const double dx = t.dx, dy = t.dy, dz = t.dz;
       double old[3] = {0.0, 0.0, 0.0};  // loaded ahead of the arithmetic
@@ -933,7 +944,7 @@ void k_backward(SysArgs a, int i0, int n, const R* __restrict__ mbar, long ld, d
         __builtin_amdgcn_sched_barrier(0);
       }
       R f[L::NMU], fp[L::NMU];
-      radial<R, L::NMU, NC>((R)t.r, (R)a.sa, (R)a.sb, (R)a.rcut, cz + t.zj * L::NMU * a.ncheb, a.ncheb, f, fp);
+      radial<R, L::NMU, NC>((R)t.r, (R)a.sa, (R)a.sb, (R)a.rcut, cz + t.zj * radial_row<L::NMU, NC>(a.ncheb), a.ncheb, f, fp);
       R rgx = R(0), rgy = R(0), rgz = R(0), ru = R(0);
       double ur;
       if constexpr (PARTS) {
@@ -990,11 +1001,11 @@ __device__ __forceinline__ void gradient_stage_first(const SysArgs& a, const dou
   for (int e = 0; e < NE; ++e) mb[e] = mbar[(long)L::PART_ENTRY[P][e] * ld + li];
   Partner<false> own;
   own.load(a, nullptr, i);
-  const double* cz = csh + clamp_species(own.s, a.nsp) * a.nsp * L::NMU * a.ncheb;
+  const double* cz = csh + clamp_species(own.s, a.nsp) * a.nsp * radial_row<L::NMU, NC>(a.ncheb);
   int slot = 0;
   for_steps<K, false>(a, lst, i, lane, p0, len, T, H, own, nullptr, [&](int, const Pair& t) {
     double f[L::NMU], h[L::NMU];
-    radial<double, L::NMU, NC>(t.r, a.sa, a.sb, a.rcut, cz + t.zj * L::NMU * a.ncheb, a.ncheb, f, h);
+    radial<double, L::NMU, NC>(t.r, a.sa, a.sb, a.rcut, cz + t.zj * radial_row<L::NMU, NC>(a.ncheb), a.ncheb, f, h);
 #pragma unroll
     for (int mu = 0; mu < L::NMU; ++mu) h[mu] *= t.rinv;
     double gx = 0.0, gy = 0.0, gz = 0.0, u = 0.0;
@@ -1067,7 +1078,7 @@ void k_backward_stages(SysArgs a, int i0, int n, const double* __restrict__ mbar
   static_assert(L::NPART <= 4, "pair-gradient stages");
   __shared__ int lst[K == 1 ? kStageInts : 1];
   __shared__ StageSlots<L> slots;
-  const double* csh = stage_radial<double>(a);
+  const double* csh = stage_radial<double, L::NMU>(a);
   const int lane = (int)threadIdx.x & (kLaneBlock - 1);
   const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kLaneBlock);
   MTP_FOR_TILES_K(a, n, K, 1, b) {
@@ -1111,10 +1122,10 @@ __device__ __forceinline__ void tangents_of_atom(const SysArgs& a, const double*
   for (int e = 0; e < NE; ++e) md[e] = 0.0;
   Partner<true> own;
   own.load(a, fbar, i);
-  const double* cz = csh + clamp_species(own.s, a.nsp) * a.nsp * L::NMU * a.ncheb;
+  const double* cz = csh + clamp_species(own.s, a.nsp) * a.nsp * radial_row<L::NMU, NC>(a.ncheb);
   for_pairs<K, double, true>(a, lst, i, sub, H, own, fbar, [&](int, const Pair& t) {
     double f[L::NMU], fd[L::NMU];
-    radial<double, L::NMU, NC>(t.r, a.sa, a.sb, a.rcut, cz + t.zj * L::NMU * a.ncheb, a.ncheb, f, fd);
+    radial<double, L::NMU, NC>(t.r, a.sa, a.sb, a.rcut, cz + t.zj * radial_row<L::NMU, NC>(a.ncheb), a.ncheb, f, fd);
     const double rdot = (t.dx * t.ex + t.dy * t.ey + t.dz * t.ez) * t.rinv;
 #pragma unroll
     for (int mu = 0; mu < L::NMU; ++mu) fd[mu] *= rdot;
@@ -1139,7 +1150,7 @@ void k_tan_moments(SysArgs a, const double* __restrict__ fbar, int i0, int n, do
   constexpr int NP = L::NTPART;
   static_assert(NP <= 5, "moment-tangent parts");
   __shared__ int lst[K == 1 ? kStageInts : 1];
-  const double* csh = stage_radial<double>(a);
+  const double* csh = stage_radial<double, L::NMU>(a);
   MTP_FOR_TILES_K(a, n, K, NP, b) {
   const int li = (b / NP) * (kLaneBlock / K) + (int)threadIdx.x / K, sub = (int)threadIdx.x % K;
   if (li >= n) continue;
@@ -1584,7 +1595,7 @@ void k_adj_radial(SysArgs a, int i0, int n, const double* __restrict__ rec, int 
 // runtime-count form for the rest.
 template <class L, int G, class R, bool BATCH, bool PERSIST, int K, bool ALONE>
 void launch_moments_nc(const SysArgs& a, int nb, int i0, int n, void* m, long ld, hipStream_t s) {
-  const unsigned sh = radial_bytes<R>(a);
+  const unsigned sh = radial_bytes<R, L::NMU>(a);
   if (a.ncheb == 8)
     hipLaunchKernelGGL((k_moments<L, G, R, BATCH, 8, PERSIST, K, ALONE>), dim3(nb), dim3(kLaneBlock), sh, s, a, i0, n, (R*)m, ld);
   else if (a.ncheb == 10)
@@ -1632,7 +1643,7 @@ template <class L, int G, class R, bool BATCH, bool PERSIST, int K, int NC>
 void launch_backward_nc(const SysArgs& a, int i0, int n, const void* mb, long ld, double* g, double* wpart,
                         double* watom, double* fown, hipStream_t s) {
   const int nb = pair_grid(a, split_tiles(n, K), L::NPART, L::NPART);
-  const unsigned sh = radial_bytes<R>(a);
+  const unsigned sh = radial_bytes<R, L::NMU>(a);
   if constexpr (std::is_same_v<R, double> && L::NPART > 1) {
     hipLaunchKernelGGL((k_backward_stages<L, BATCH, NC, PERSIST, K>), dim3(nb), dim3(kLaneBlock * L::NPART), sh, s, a,
                        i0, n, (const double*)mb, ld, g, wpart, watom, fown);
@@ -1749,7 +1760,8 @@ struct AdjImpl {
   template <int NC, bool PERSIST, int K>
   static void tan_moments_k(const SysArgs& a, const double* fbar, int i0, int n, double* md, long ld, hipStream_t s) {
     const int nb = pair_grid(a, split_tiles(n, K) * L::NTPART, L::NTPART, 1);
-    hipLaunchKernelGGL((k_tan_moments<L, NC, PERSIST, K>), dim3(nb), dim3(kLaneBlock), radial_bytes<double>(a), s, a,
+    const unsigned sh = radial_bytes<double, L::NMU>(a);
+    hipLaunchKernelGGL((k_tan_moments<L, NC, PERSIST, K>), dim3(nb), dim3(kLaneBlock), sh, s, a,
                        fbar, i0, n, md, ld);
   }
   template <int NC>
