@@ -481,7 +481,7 @@ __device__ __forceinline__ void moments_of_atom(const SysArgs& a, const R* csh, 
 // entries of level 16 filled the registers of a SIMD by itself, moved a third of its accumulators
 // through accumulation registers for every pair and stood waiting on its loads a quarter of the
 // time.  The parts repeat a pair's geometry and radial functions, but two waves share a SIMD:
-// 0.73 -> 0.59 ms at 1,024,000 atoms of level 16 (the vector unit is busy about 0.6 of it),
+// 0.73 -> 0.57 ms at 1,024,000 atoms of level 16 (the vector unit is busy about 0.6 of it),
 // 1.93 -> 1.17 ms at level 20 (545,505 atoms; it took three passes before).
 // Binary32: group G of the layout.
 // ALONE: one wave per SIMD (launch_moments_g).
